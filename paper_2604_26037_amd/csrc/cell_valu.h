@@ -2,7 +2,9 @@
 // translation units that instantiate it (kernels_cell_valu.hip: K + V on
 // cells of one size; kernels_cell_gen_f32.hip / _f64.hip: per-cell geometry,
 // the GGA term and the mass term; kernels_cell_step.hip /
-// kernels_cell_step_gen.hip: the filter's fused Chebyshev step).
+// kernels_cell_step_gen.hip: the filter's fused Chebyshev step).  Launches with
+// enough items run the one-wave split of the same contractions instead
+// (cell_wave.h).
 //
 // Local (cell) part of the Hamiltonian on the vector ALUs:
 // Y += alpha (K + V [+ GGA]) X over the cells of one colour (eq. "FEM Ham
@@ -1135,6 +1137,12 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   }
 }
 
+}  // namespace pawfe
+
+#include "cell_wave.h"
+
+namespace pawfe {
+
 namespace {
 
 template <auto K, int NT>
@@ -1173,11 +1181,19 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
   const T fx = (T)(0.5 * op->detJ * (2.0 / op->h[0]) * (2.0 / op->h[0]));
   const T fy = (T)(0.5 * op->detJ * (2.0 / op->h[1]) * (2.0 / op->h[1]));
   const T fz = (T)(0.5 * op->detJ * (2.0 / op->h[2]) * (2.0 / op->h[2]));
+  bool wave = false;
+  if constexpr (is_wave_mode(MODE)) wave = wave_pays<T, NP, MODE>(op, a.ncols);
   for (int c = 0; c < op->ncolour; ++c) {
     const int c0 = op->colour_off[c], c1 = op->colour_off[c + 1];
     if (c1 == c0) continue;
     CellArgs<T> ac = a;
     ac.cells = op->d.cell_pack + c0;
+    if constexpr (is_wave_mode(MODE)) {
+      if (wave) {
+        launch_wave<T, NP, NQ, MODE>(ac, c1 - c0, fx, fy, fz, s);
+        continue;
+      }
+    }
     const int nitems = (c1 - c0) * ncoltiles;
     const dim3 grid(valu_grid<k_cell_valu<T, NP, NQ, MODE>, kNT<T>>(nitems)), block(kNT<T>);
     hipLaunchKernelGGL((k_cell_valu<T, NP, NQ, MODE>), grid, block, 0, s, ac, ncoltiles, nitems, fx, fy, fz);

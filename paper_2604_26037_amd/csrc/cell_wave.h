@@ -1,0 +1,437 @@
+// Cell operators with one wavefront per item (a cell and one column tile):
+// the same contractions, modes and arguments as cell_valu.h, split over the
+// lanes by node planes instead of over a workgroup by lines.
+//
+// Lane (col, c, h) owns column `col` of the tile and the z plane c of the
+// cell (FP64 elements of degree 5 and 6: the half h of that plane), so the x
+// and y contractions run in registers with no exchange at all (FP64 halves
+// trade rows for columns with v_permlane32_swap) and only the z contraction
+// goes through LDS, in a slab that belongs to the wave: no barrier anywhere,
+// a wave waits for its own memory operations only, and the waves of a CU
+// drift apart so that one's loads and stores run under another's arithmetic.
+//   V:  planes By Bx -> slab, lines Bz, V(q) W_q, Bz^T in place, planes By^T Bx^T
+//   M:  planes My Mx -> slab, lines fz Kz (residual: - lambda det J Mz too)
+//   K:  planes fx My Kx + fy Ky Mx -> slab, lines Mz, added to M's lines
+// and the sum is added to Y (first visits of the step as in cell_valu.h).
+// The gathered rows are wave-uniform for x and y, so their addresses are
+// scalar; the lanes only carry the offset of their plane and column.
+//
+// Bound by the memory system and the vector ALU about equally (degree 6,
+// 1000 cells x 256 columns a launch): FP32 step 1.54e9 B of HBM traffic (1.03x
+// its algorithmic bytes) and 161,000 vector instructions per SIMD.  Per launch,
+// against the workgroup kernel: step FP32 0.538 -> 0.397 ms (3.9 TB/s), FP64
+// 0.988 -> 0.736; K + V FP32 0.436 -> 0.307, FP64 0.852 -> 0.603; mass FP32
+// 0.411 -> 0.299, FP64 0.798 -> 0.580.
+//
+// Slab: element (line L, plane c, col) at (L NP + c) CB + col.  A plane
+// access (L fixed) is contiguous; a line access strides by NP CB elements,
+// 56 words at degree 6, which spreads the eight lines of a 32-lane half over
+// all banks.
+
+#pragma once
+
+#include "cell_valu.h"
+
+namespace pawfe {
+
+namespace {
+
+template <typename T, int NP, int NQ>
+struct Wave {
+  static constexpr int H = (sizeof(T) == 8 && NP >= 6) ? 2 : 1;   // halves of a plane
+  static constexpr int PS = NP <= 4 ? 4 : 8;                      // plane slots
+  static constexpr int CB = 64 / (PS * H);                        // columns per item
+  static constexpr int G = PS * H;                                // line groups of the z passes
+  static constexpr int RB = (NP + H - 1) / H;                     // rows (or columns) of a half plane
+  static constexpr int QB = (NQ + H - 1) / H;                     // Gauss columns of a half plane
+  static constexpr int NPX = RB * H, NQX = QB * H;
+  static constexpr int slab = NQ * NQ * NP * CB;
+};
+
+// order a wave's own LDS accesses (they execute in order; this keeps the
+// compiler from moving them across)
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a value the compiler cannot look through: what is computed from it is
+// computed after this point
+template <typename T>
+__device__ __forceinline__ void opaque(T& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void opaque_s(uint64_t& v) { asm volatile("" : "+s"(v)); }
+
+// upper 32 lanes of `lo` <-> lower 32 lanes of `hi`
+template <typename T>
+__device__ __forceinline__ void swap_halves(T& lo, T& hi) {
+  constexpr int W = sizeof(T) / 4;
+  unsigned a[W], b[W];
+  __builtin_memcpy(a, &lo, sizeof(T));
+  __builtin_memcpy(b, &hi, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    auto r = __builtin_amdgcn_permlane32_swap(a[i], b[i], false, false);
+    a[i] = r[0];
+    b[i] = r[1];
+  }
+  __builtin_memcpy(&lo, a, sizeof(T));
+  __builtin_memcpy(&hi, b, sizeof(T));
+}
+
+}  // namespace
+
+template <typename T, int NP, int NQ, int MODE>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
+  using W = Wave<T, NP, NQ>;
+  constexpr int H = W::H, CB = W::CB, G = W::G, RB = W::RB, QB = W::QB, NPX = W::NPX, NQX = W::NQX;
+  constexpr bool GEN = is_general_mode(MODE);
+  constexpr bool MASS = MODE == kValuGenMass || MODE == kValuMass;
+  constexpr bool RES = MODE == kValuHRes;
+  constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep;
+  constexpr bool SC = STEP;
+  constexpr int NQ2 = NQ * NQ, NP2 = NP * NP, NQ3 = NQ * NQ * NQ;
+  __shared__ T sl[W::slab];
+  __shared__ T sv[MASS ? 1 : NQ3];
+  const int lane = threadIdx.x;
+  const int col = lane % CB;
+  const int slot = (lane / CB) % W::PS;
+  const int h = H == 2 ? lane >> 5 : 0;
+  const int g = lane / CB;                     // line group
+  const bool pl = slot < NP;                   // the lane's plane exists
+  const int c = pl ? slot : NP - 1;
+  const int p = NP - 1;
+  const int Gx = A.n0 * p, Gy = A.n1 * p, Gz = A.n2 * p;
+  const uint32_t ldxb = (uint32_t)(A.ldx * (int64_t)sizeof(T)), ldyb = (uint32_t)(A.ldy * (int64_t)sizeof(T));
+  const uint64_t ld64b = STEP ? (uint64_t)A.ldy64 * 8 : 0;
+  typedef const __attribute__((address_space(4))) int* ConstIntP;
+  const ConstIntP cells = (ConstIntP)A.cells;
+  const int xcd = blockIdx.x & 7;
+  const int i_end = (int)((int64_t)nitems * (xcd + 1) / 8);
+  const int item = (int)((int64_t)nitems * xcd / 8) + (int)(blockIdx.x >> 3);
+  if (item >= i_end) return;
+  const int cc = item / ncoltiles;
+  const int packed = cells[cc];
+  const int ci = packed & 1023, cj = (packed >> 10) & 1023, ck = (packed >> 20) & 1023;
+  const int e = ci + A.n0 * (cj + A.n1 * ck);
+  const int n = (item - cc * ncoltiles) * CB + col;
+  const bool valid = n < A.ncols;
+  const int nn = valid ? n : 0;
+  const bool lastx = ci + 1 == A.n0;
+  // rows of the lane's half plane: b = RB h + r (past the last: the last row)
+  auto row_class = [&](int r) { const int b = RB * h + r; return b == 0 ? 0 : (b >= NP - 1 ? 6 : 3); };
+  auto lrow = [&](int r) { const int b = RB * h + r; return b < NP ? b : NP - 1; };
+
+  // byte offsets of the cell's node columns in an array (scalar; opaque, so
+  // that they are not folded into a 64-bit vector multiply per access)
+  auto xoffs = [&](uint64_t ldb, uint64_t(&o)[NP]) {
+    sfor<NP>([&](auto a) {
+      o[a] = (uint64_t)(a == NP - 1 && lastx ? 0 : ci * p + a) * ldb;
+      opaque_s(o[a]);
+    });
+  };
+  // the lane's row r of array `base` (`ldb` bytes per row), without the node
+  // column; recomputed for each use rather than held in registers
+  auto rowptr = [&](auto* base, uint64_t ldb, int r) {
+    using P = decltype(base);
+    using C = typename std::conditional<std::is_const<typename std::remove_pointer<P>::type>::value, const char,
+                                        char>::type;
+    int gz = ck * p + c, gy = cj * p + lrow(r);
+    asm volatile("" : "+v"(gz));
+    gz = gz >= Gz ? gz - Gz : gz;
+    gy = gy >= Gy ? gy - Gy : gy;
+    return reinterpret_cast<C*>(base + nn) + (uint64_t)(uint32_t)(Gx * (gy + Gy * gz)) * (uint32_t)ldb;
+  };
+
+  T x[RB][NP];
+  uint64_t xo[NP];
+  xoffs(ldxb, xo);
+  sfor<RB>([&](auto r) {
+    const char* q = rowptr(A.X, ldxb, r);
+    sfor<NP>([&](auto a) { x[r][a] = *(const T*)(q + xo[a]); });
+  });
+  // the factor of the result goes into V(q) W_q and the kinetic factors
+  T f = A.alpha, ifx = fx, ify = fy, ifz = fz, idet = A.detJ;
+  if constexpr (GEN) {
+    typedef const __attribute__((address_space(4))) T* ConstTP;
+    const ConstTP gg = (ConstTP)A.geo + 4 * e;
+    ifx = gg[0];
+    ify = gg[1];
+    ifz = gg[2];
+    idet = gg[3];
+  }
+  if constexpr (STEP && GEN) f = f / idet;   // the cell's det J of M_D^{-1}
+  if constexpr (MASS) f = f * idet * ((MODE == kValuGenMass && A.lam) ? (T)(-A.lam[nn]) : T(1));
+  ifx *= f;
+  ify *= f;
+  ifz *= f;
+  if constexpr (!MASS) {
+    constexpr int NV = (NQ3 + 63) / 64;
+    T v[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (NQ3 % 64 == 0 || lane + 64 * i < NQ3) v[i] = A.Vw[(int64_t)e * NQ3 + lane + 64 * i];
+    wave_lds_order();
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (NQ3 % 64 == 0 || lane + 64 * i < NQ3) sv[lane + 64 * i] = f * v[i];
+  }
+  // general step: face factors of the lumped mass (see cell_valu.h), applied
+  // to a copy of each row on its way into the contractions
+  T rf[STEP && GEN ? 4 : 1], rz = T(1);
+  if constexpr (STEP && GEN) {
+    typedef const __attribute__((address_space(4))) T* ConstTP;
+    const ConstTP q = (ConstTP)A.frho + 6 * e;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rf[k] = q[k];
+    const T z0 = q[4], z1 = q[5];
+    rz = c == 0 ? z0 : (c == NP - 1 ? z1 : T(1));
+  }
+  auto row = [&](auto r, T(&o)[NP]) {
+    sfor<NP>([&](auto a) { o[a] = x[r][a]; });
+    if constexpr (STEP && GEN) {
+      const int b = RB * h + r;
+      const T f = rz * (b == 0 ? rf[2] : (b == NP - 1 ? rf[3] : T(1)));
+      sfor<NP>([&](auto a) { o[a] *= a == 0 ? f * rf[0] : (a == NP - 1 ? f * rf[1] : f); });
+    }
+  };
+
+  // slab addresses
+  T* const pb = sl + slot * CB + col;                        // plane accesses: + line * NP CB
+  T* const zb = sl + g * NP * CB + col;                      // line accesses: + round * G NP CB + plane * CB
+  constexpr int LS = NP * CB;
+
+  T acc[RB][NP];
+  // ---- V term ------------------------------------------------------------
+  if constexpr (!MASS) {
+    T u[RB][NQX];
+    sfor<RB>([&](auto r) {
+      T xr[NP], y[NQ];
+      row(r, xr);
+      line_B<NP, NQ, SC>(xr, y);
+      sfor<NQX>([&](auto q) { u[r][q] = q < NQ ? y[q < NQ ? (int)q : 0] : T(0); });
+      if constexpr (H == 2) sfor<QB>([&](auto j) { swap_halves(u[r][j], u[r][QB + j]); });
+    });
+    wave_lds_order();
+    if (pl) {
+      sfor<QB>([&](auto j) {   // qx = QB h + j
+        T xc[NP], y[NQ];
+        sfor<NP>([&](auto b) { xc[b] = u[b % RB][j + QB * (b / RB)]; });
+        line_B<NP, NQ, SC>(xc, y);
+        if (H == 1 || NQX == NQ || QB * h + j < NQ)
+          sfor<NQ>([&](auto q) { pb[(q * NQ + QB * h + j) * LS] = y[q]; });
+      });
+    }
+    wave_lds_order();
+    constexpr int ZR = (NQ2 + G - 1) / G;
+    sfor<ZR>([&](auto i) {
+      if (NQ2 % G == 0 || i < ZR - 1 || g + G * i < NQ2) {
+        T m[NP], y[NQ], o[NP];
+        sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+        line_B<NP, NQ, SC>(m, y);
+        sfor<NQ>([&](auto q) { y[q] *= sv[g + G * i + NQ2 * q]; });
+        line_Bt<NP, NQ>(y, o);
+        sfor<NP>([&](auto k) { zb[(i * G * NP + k) * CB] = o[k]; });
+      }
+    });
+    wave_lds_order();
+    T w[NPX][QB];
+    sfor<QB>([&](auto j) {
+      T y[NQ], o[NP];
+      const int qx = (H == 1 || NQX == NQ) ? QB * h + j : (QB * h + j < NQ ? QB * h + j : NQ - 1);
+      sfor<NQ>([&](auto q) { y[q] = pb[(q * NQ + qx) * LS]; });
+      line_Bt<NP, NQ>(y, o);
+      sfor<NPX>([&](auto b) { w[b][j] = b < NP ? o[b < NP ? (int)b : 0] : T(0); });
+    });
+    sfor<RB>([&](auto r) {
+      if constexpr (H == 2) sfor<QB>([&](auto j) { swap_halves(w[r][j], w[(int)r + RB < NPX ? (int)r + RB : 0][j]); });
+      T y[NQ], o[NP];
+      sfor<NQ>([&](auto q) { y[q] = w[r + RB * (q / QB)][q % QB]; });
+      line_Bt<NP, NQ>(y, o);
+      sfor<NP>([&](auto a) { acc[r][a] = o[a]; });
+    });
+  }
+  // step: the rows' part of the node update (-a c R_Y' at first visits)
+  unsigned cm = 0;
+  if constexpr (STEP) {
+    typedef const __attribute__((address_space(4))) unsigned* ConstUP;
+    cm = ((ConstUP)A.own)[e] >> (c == 0 ? 0 : (c == NP - 1 ? 18 : 9));   // the lane's 9 (x, y) classes
+    const T mac = (T)(-A.sac);
+    sfor<RB>([&](auto r) {
+      // opaque: the products are formed here, not kept beside x from the load on
+      sfor<NP>([&](auto a) { opaque(x[r][a]); });
+      const unsigned cr = cm >> row_class(r);
+      sfor<NP>([&](auto a) { acc[r][a] += ((cr >> (a == 0 ? 0 : (a == NP - 1 ? 2 : 1))) & 1u) ? mac * x[r][a] : T(0); });
+      sfor<NP>([&](auto a) { opaque(acc[r][a]); });
+    });
+  }
+  // ---- M and K terms -----------------------------------------------------
+  constexpr int ZK = (NP2 + G - 1) / G;
+  T mx[RB][NPX], kx[MASS ? 1 : RB][NPX];
+  sfor<RB>([&](auto r) {
+    T xr[NP], y[NP];
+    row(r, xr);
+    const EOIn<NP, T> eo = split_eo<NP>(xr);
+    line_sym<NP, NQ, false, SC>(eo, y);
+    sfor<NPX>([&](auto a) { mx[r][a] = a < NP ? y[a < NP ? (int)a : 0] : T(0); });
+    if constexpr (!MASS) {
+      line_sym<NP, NQ, true, SC>(eo, y);
+      sfor<NPX>([&](auto a) { kx[r][a] = a < NP ? y[a < NP ? (int)a : 0] : T(0); });
+    }
+    if constexpr (H == 2) sfor<RB>([&](auto j) {
+      swap_halves(mx[r][j], mx[r][RB + j]);
+      if constexpr (!MASS) swap_halves(kx[r][j], kx[r][RB + j]);
+    });
+  });
+  wave_lds_order();
+  // columns a = RB h + j: M -> slab, fx My K + fy Ky M stays in kx
+  if (pl) {
+    sfor<RB>([&](auto j) {
+      T mc[NP], y[NP];
+      sfor<NP>([&](auto b) { mc[b] = mx[b % RB][j + RB * (b / RB)]; });
+      const EOIn<NP, T> em = split_eo<NP>(mc);
+      line_sym<NP, NQ, false, SC>(em, y);
+      const bool on = H == 1 || NPX == NP || RB * h + j < NP;
+      if (on) sfor<NP>([&](auto b) { pb[(b * NP + RB * h + j) * LS] = y[b]; });
+      if constexpr (!MASS) {
+        T kc[NP], mk[NP];
+        sfor<NP>([&](auto b) { kc[b] = kx[b % RB][j + RB * (b / RB)]; });
+        line_sym<NP, NQ, false, SC>(split_eo<NP>(kc), mk);
+        line_sym<NP, NQ, true, SC>(em, y);
+        sfor<NP>([&](auto b) { kx[b % RB][j + RB * (b / RB)] = fma_t(ifx, mk[b], ify * y[b]); });
+      }
+    });
+  }
+  wave_lds_order();
+  T zl[MASS ? 1 : ZK][NP];
+  const T ml = RES ? -(T)A.lam[nn] * idet * f : T(0);
+  sfor<ZK>([&](auto i) {
+    if (NP2 % G == 0 || i < ZK - 1 || g + G * i < NP2) {
+      T m[NP], y[NP];
+      sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+      const EOIn<NP, T> em = split_eo<NP>(m);
+      if constexpr (MASS) {
+        line_sym<NP, NQ, false, SC>(em, y);
+        sfor<NP>([&](auto k) { zb[(i * G * NP + k) * CB] = y[k]; });
+      } else {
+        line_sym<NP, NQ, true, SC>(em, y);
+        sfor<NP>([&](auto k) { zl[i][k] = ifz * y[k]; });
+        if constexpr (RES) {
+          line_sym<NP, NQ, false, SC>(em, y);
+          sfor<NP>([&](auto k) { zl[i][k] = fma_t(ml, y[k], zl[i][k]); });
+        }
+      }
+    }
+  });
+  if constexpr (!MASS) {
+    wave_lds_order();
+    if (pl) {
+      sfor<RB>([&](auto j) {
+        if (H == 1 || NPX == NP || RB * h + j < NP)
+          sfor<NP>([&](auto b) { pb[(b * NP + RB * h + j) * LS] = kx[b % RB][j + RB * (b / RB)]; });
+      });
+    }
+    wave_lds_order();
+  }
+  // old rows and, of the step, the first FP64 residual rows: requested here,
+  // used after the last z pass
+  T yo[RB][NP];
+  xoffs(ldyb, xo);
+  sfor<RB>([&](auto r) {
+    const char* q = rowptr((const T*)A.Y, ldyb, r);
+    sfor<NP>([&](auto a) { yo[r][a] = *(const T*)(q + xo[a]); });
+  });
+  uint64_t x64[STEP ? NP : 1];
+  if constexpr (STEP) xoffs(ld64b, x64);
+  double yr[STEP ? RB : 1][NP];
+  auto load_y = [&](auto r) {
+    const unsigned cr = cm >> row_class(r);
+    const char* q = rowptr(A.y64, ld64b, r);
+    sfor<NP>([&](auto a) { yr[r][a] = 0.0; });
+    if (cr & 1u) yr[r][0] = *(const double*)(q + x64[0]);
+    if (cr & 2u) sfor<NP - 2>([&](auto a) { yr[r][a + 1] = *(const double*)(q + x64[a + 1]); });
+    if (cr & 4u) yr[r][NP - 1] = *(const double*)(q + x64[NP - 1]);
+  };
+  constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;
+  opaque(cm);
+  if constexpr (STEP) sfor<kAhead>([&](auto r) { load_y(r); });
+  if constexpr (!MASS) {
+    sfor<ZK>([&](auto i) {
+      if (NP2 % G == 0 || i < ZK - 1 || g + G * i < NP2) {
+        T m[NP], y[NP];
+        sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+        line_sym<NP, NQ, false, SC>(split_eo<NP>(m), y);
+        sfor<NP>([&](auto k) { zb[(i * G * NP + k) * CB] = y[k] + zl[i][k]; });
+      }
+    });
+  }
+  wave_lds_order();
+  sfor<RB>([&](auto r) {
+    const int b = lrow(r);
+    sfor<NP>([&](auto a) {
+      const T k = pb[(b * NP + a) * LS];
+      if constexpr (MASS) acc[r][a] = k; else acc[r][a] += k;
+    });
+  });
+  // ---- assembly ----------------------------------------------------------
+  const double ly = STEP ? A.sa * A.lamY[nn] : 0.0;
+  const T zz = STEP ? (T)A.szz : T(0);
+  sfor<RB>([&](auto r) {
+    if constexpr (STEP) {
+      if constexpr (r + kAhead < RB) load_y(std::integral_constant<int, (r + kAhead < RB ? r + kAhead : 0)>{});
+      const unsigned cr = cm >> row_class(r);
+      sfor<NP>([&](auto a) {
+        const T upd = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly);
+        yo[r][a] = ((cr >> (a == 0 ? 0 : (a == NP - 1 ? 2 : 1))) & 1u) ? upd : yo[r][a];
+      });
+    }
+    if (pl && valid && (H == 1 || NPX == NP || RB * h + r < NP)) {
+      char* q = rowptr(A.Y, ldyb, r);
+      sfor<NP>([&](auto a) { *(T*)(q + xo[a]) = yo[r][a] + (MASS ? f * acc[r][a] : acc[r][a]); });
+    }
+  });
+}
+
+namespace {
+
+// Modes that have a one-wave variant.
+constexpr bool is_wave_mode(int mode) {
+  return mode == kValuH || mode == kValuHRes || mode == kValuMass || mode == kValuStep || mode == kValuGenH ||
+         mode == kValuGenMass || mode == kValuGenStep;
+}
+
+// Where the one-wave split pays, by the cell columns (cells x columns) of an
+// average colour: an item takes one wave longer than it takes a workgroup, so
+// a launch has to hold enough items to fill the chip.  Measured per launch
+// (workgroup -> wave): step at degree 6 FP32 19.0 -> 21.1 us at 6,900 cell
+// columns, 39.5 -> 38.9 at 16,400, 74 -> 63 at 32,000; FP64 34.6 -> 35.7 at
+// 8,000, 71.6 -> 63.0 at 16,400; degree 3 FP64 7.7 -> 7.7 at 4,100, FP32 7.4
+// -> 7.5 at 6,900; degree 2 FP32 even at any size, FP64 5.0 -> 5.4 at 2,000
+// and 8.7 -> 5.9 at 6,900.  The mass term is too short to lose: 5.2 -> 4.7 us
+// at 128 cell columns.
+template <typename T, int NP, int MODE>
+bool wave_pays(const pawfe_op* op, int ncols) {
+  if (MODE == kValuMass || MODE == kValuGenMass) return true;
+  const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
+  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : 16000)
+                                       : (NP == 3 ? 3000 : NP == 4 ? 4000 : 8000);
+  return per_colour >= least;
+}
+
+template <typename T, int NP, int NQ, int MODE>
+void launch_wave(const CellArgs<T>& a, int ncells, T fx, T fy, T fz, hipStream_t s) {
+  constexpr int CB = Wave<T, NP, NQ>::CB;
+  const int ncoltiles = (a.ncols + CB - 1) / CB;
+  // one item per workgroup of one wave, XCD x takes the x-th eighth of the
+  // items (workgroup w runs on XCD w % 8).  A resident set that strides over
+  // the items was slower (degree-6 K + V of 1000 cells x 256 columns, FP32:
+  // 0.39 against 0.30 ms)
+  const int nitems = ncells * ncoltiles;
+  hipLaunchKernelGGL((k_cell_wave<T, NP, NQ, MODE>), dim3((unsigned)((nitems + 7) / 8) * 8), dim3(64), 0, s, a,
+                     ncoltiles, nitems, fx, fy, fz);
+}
+
+}  // namespace
+
+}  // namespace pawfe
