@@ -4,7 +4,7 @@
 // Non-local action (eq. "FE nonlocal contribution"): the projector
 // coefficients c_a = C^a^T s X (s = 1 or M_D^{-1}) are a long-K skinny
 // reduction over the support nodes of each atom (K <= 19^3 rows, M = nproj,
-// N = columns): one workgroup per (atom, 256-row chunk, 64-column tile),
+// N = columns): one workgroup per (atom, 128-row chunk, column tile),
 // lane <-> column so every row read is one coalesced 512-byte segment and the
 // C^a row is wave-uniform (scalar loads).  Partial sums go to a workspace and
 // a second kernel adds the chunks of each atom in a fixed order (no atomics,
@@ -25,31 +25,55 @@ namespace {
 
 constexpr int kRowsPerWaveGroup = 4;   // waves per 256-thread block in row-wise kernels
 
-// One workgroup per (item, 256-column slab): wave w owns the 64 columns
-// [64 w, 64 w + 64) of the slab and walks all rows of the item, so no
-// cross-wave reduction is needed.  Rows are taken kUnroll at a time with all
-// their loads issued before the FMAs (memory-level parallelism).
+// A workgroup of four waves takes an item's rows: SPLIT = 1, each wave owns 64
+// of 256 columns and walks all rows; SPLIT = 4, the waves share one 64-column
+// tile, a quarter of the rows each, and their sums meet in LDS, added in FP64.
+// Rows are taken kUnroll at a time with all their loads issued before the
+// FMAs (memory-level parallelism).  The walk over the rows is a chain of
+// memory latencies (node list, then rows): it is the whole time of a small
+// launch, which the split quarters (FP64, three 18-projector atoms x 40
+// columns: 47.7 -> 17.1 us), while a launch that fills the chip without it
+// only loses residency to the LDS (FP64, 128 atoms x 256 columns: 0.43 ->
+// 0.60 ms; 27 atoms x 192 columns 107 -> 132 us; 16 complex atoms x 192
+// real columns 86 -> 62 us).
 constexpr int kUnroll = 8;
+
+// sum of the four waves' partials of projector rows [0, npj) and 64 columns,
+// written to the item's block
+template <typename T, int NPJ>
+__device__ __forceinline__ void store_partials(const T (&red)[kRowsPerWaveGroup][NPJ][64], int npj, int ncols,
+                                               int n, int po, double* __restrict__ part) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (n >= ncols) return;
+  for (int al = w; al < npj; al += kRowsPerWaveGroup)
+    part[(int64_t)(po + al) * ncols + n] = (((double)red[0][al][lane] + (double)red[1][al][lane]) +
+                                            ((double)red[2][al][lane] + (double)red[3][al][lane]));
+}
 
 // Complex operators (CPLX): the columns are (re, im) pairs of the complex
 // columns and c = C^H x mixes them: c[n] = sum Cr x[n] + s' Ci x[n ^ 1],
 // s' = +1 on real and -1 on imaginary columns; the partner value comes from
 // the neighbouring lane.
-template <typename T, int NPJ, bool SCALE, bool CPLX = false>
+template <typename T, int NPJ, bool SCALE, bool CPLX, int SPLIT>
 __global__ void __launch_bounds__(256) k_nl_reduce(const T* __restrict__ X, int64_t ldx, int ncols,
                                                    const T* __restrict__ Minv,
                                                    const T* __restrict__ Cv, DeviceTables d,
-                                                   double* __restrict__ part, const T* __restrict__ Cvi = nullptr) {
+                                                   double* __restrict__ part, const T* __restrict__ Cvi) {
+  __shared__ T red[SPLIT == 4 ? kRowsPerWaveGroup : 1][SPLIT == 4 ? NPJ : 1][64];
   const int item = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = (blockIdx.y * kRowsPerWaveGroup + w) * 64 + lane;
-  if ((blockIdx.y * kRowsPerWaveGroup + w) * 64 >= ncols) return;   // wave-uniform
+  const int tile = SPLIT == 4 ? blockIdx.y : blockIdx.y * kRowsPerWaveGroup + w;
+  if (SPLIT == 1 && tile * 64 >= ncols) return;   // wave-uniform
+  const int n = tile * 64 + lane;
   const bool valid = n < ncols;
   const int nc = valid ? n : 0;
   const int a = d.item_atom[item];
   const int npj = d.nproj[a];
-  const int r0 = d.item_row0[item], r1 = d.item_row1[item];
+  const int i0 = d.item_row0[item], i1 = d.item_row1[item];
+  const int per = (i1 - i0 + SPLIT - 1) / SPLIT;
+  const int r0 = SPLIT == 1 ? i0 : std::min(i0 + w * per, i1), r1 = std::min(r0 + per, i1);
   const int noff = d.atom_noff[a], coff = d.atom_coff[a];
   T acc[NPJ];
 #pragma unroll
@@ -96,17 +120,25 @@ __global__ void __launch_bounds__(256) k_nl_reduce(const T* __restrict__ X, int6
     }
   };
   if (npj == NPJ) rows(std::true_type{}); else rows(std::false_type{});
-  if (!valid) return;
   const int po = d.item_poff[item];
+  if constexpr (SPLIT == 4) {
 #pragma unroll
-  for (int al = 0; al < NPJ; ++al)
-    if (al < npj) part[(int64_t)(po + al) * ncols + n] = (double)acc[al];
+    for (int al = 0; al < NPJ; ++al) red[w][al][lane] = acc[al];
+    __syncthreads();
+    store_partials<T, NPJ>(red, npj, ncols, n, po, part);
+  } else {
+    if (!valid) return;
+#pragma unroll
+    for (int al = 0; al < NPJ; ++al)
+      if (al < npj) part[(int64_t)(po + al) * ncols + n] = (double)acc[al];
+  }
 }
 
 // The same reduction on the matrix cores (real operators, FP32 data), as
 // the long-K skinny product  c[alpha][n] = sum_r C[r][alpha] x[r][n]:
 // projectors alpha on the M side (two 16-blocks), support rows r on K,
-// columns n on N.  Each wave owns 64 columns (four 16-column blocks).
+// columns n on N.  Each wave owns 64 columns (four 16-column blocks), 16 rows
+// at a time: their indices first, then all rows, then the products.
 //   FP32:   v_mfma_f32_16x16x4f32, 4 rows per step; A[i][k] (lane i + 16k) =
 //           C[r0 + k][16 b + i], B[k][j] (lane j + 16k) = x[r0 + k][n + j].
 //   bf16x3: v_mfma_f32_16x16x16_bf16, 16 rows per step; lane (i, g) holds rows
@@ -124,19 +156,22 @@ __device__ __forceinline__ short nl_bf16(float x, float& back) {
   return (short)(u >> 16);
 }
 
-template <bool SCALE, bool BF3>
+template <bool SCALE, bool BF3, int SPLIT>
 __global__ void __launch_bounds__(256) k_nl_reduce_mfma(const float* __restrict__ X, int64_t ldx, int ncols,
                                                         const float* __restrict__ Minv,
                                                         const float* __restrict__ Cv, DeviceTables d,
                                                         double* __restrict__ part) {
+  __shared__ float red[SPLIT == 4 ? kRowsPerWaveGroup : 1][SPLIT == 4 ? 32 : 1][64];
   const int item = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nbase = (blockIdx.y * kRowsPerWaveGroup + w) * 64;
-  if (nbase >= ncols) return;   // wave-uniform
+  const int nbase = (SPLIT == 4 ? blockIdx.y : blockIdx.y * kRowsPerWaveGroup + w) * 64;
+  if (SPLIT == 1 && nbase >= ncols) return;   // wave-uniform
   const int a = d.item_atom[item];
   const int npj = d.nproj[a];
-  const int r0 = d.item_row0[item], r1 = d.item_row1[item];
+  const int i0 = d.item_row0[item], i1 = d.item_row1[item];
+  const int per = (i1 - i0 + SPLIT - 1) / SPLIT;
+  const int r0 = SPLIT == 1 ? i0 : std::min(i0 + w * per, i1), r1 = std::min(r0 + per, i1);
   const int noff = d.atom_noff[a], coff = d.atom_coff[a];
   const int i = lane & 15, g = lane >> 4;
   RF4 acc[2][4];
@@ -144,36 +179,48 @@ __global__ void __launch_bounds__(256) k_nl_reduce_mfma(const float* __restrict_
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[b][cb] = RF4{0.f, 0.f, 0.f, 0.f};
-  constexpr int RPS = BF3 ? 16 : 4;            // support rows per step
-  constexpr int RPL = BF3 ? 4 : 1;             // of them per lane
-  for (int rb = r0; rb < r1; rb += RPS) {
-    float xv[4][RPL], cv[2][RPL];
+  for (int rb = r0; rb < r1; rb += 16) {
+    // the lane's four rows of these sixteen: FP32 step q takes row 4 q + g,
+    // bf16x3 takes rows 4 g + q in one step
+    float xv[4][4], cv[2][4], m[4];
+    int I[4], rr[4];
+    bool rin[4];
 #pragma unroll
-    for (int e = 0; e < RPL; ++e) {
-      const int r = rb + g * RPL + e;
-      const bool rin = r < r1;
-      const int rr = rin ? r : r1 - 1;
-      const int I = d.atom_nodes[noff + rr];
-      const float m = SCALE ? Minv[I] : 1.0f;
+    for (int q = 0; q < 4; ++q) {
+      const int r = rb + (BF3 ? 4 * g + q : 4 * q + g);
+      rin[q] = r < r1;
+      rr[q] = rin[q] ? r : r1 - 1;
+      I[q] = d.atom_nodes[noff + rr[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      m[q] = SCALE ? Minv[I[q]] : 1.0f;
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
         const int n = nbase + 16 * cb + i;
-        const float v = X[(int64_t)I * ldx + (n < ncols ? n : 0)];
-        xv[cb][e] = (rin && n < ncols) ? v * m : 0.0f;
+        xv[cb][q] = X[(int64_t)I[q] * ldx + (n < ncols ? n : 0)];
       }
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const int al = 16 * b + i;
-        const float c = Cv[coff + (int64_t)rr * npj + (al < npj ? al : 0)];
-        cv[b][e] = al < npj ? c : 0.0f;
+        cv[b][q] = Cv[coff + (int64_t)rr[q] * npj + (al < npj ? al : 0)];
       }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) xv[cb][q] = (rin[q] && nbase + 16 * cb + i < ncols) ? xv[cb][q] * m[q] : 0.0f;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) cv[b][q] = 16 * b + i < npj ? cv[b][q] : 0.0f;
     }
     if constexpr (!BF3) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-          acc[b][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[b][0], xv[cb][0], acc[b][cb], 0, 0, 0);
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int cb = 0; cb < 4; ++cb)
+            acc[b][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[b][q], xv[cb][q], acc[b][cb], 0, 0, 0);
     } else {
       RB4 chi[2], clo[2], xhi[4], xlo[4];
 #pragma unroll
@@ -205,14 +252,17 @@ __global__ void __launch_bounds__(256) k_nl_reduce_mfma(const float* __restrict_
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int n = nbase + 16 * cb + i;
+    for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int al = 16 * b + 4 * g + e;
-        if (al < npj && n < ncols) part[(int64_t)(po + al) * ncols + n] = (double)acc[b][cb][e];
+        const int al = 16 * b + 4 * g + e, n = nbase + 16 * cb + i;
+        if constexpr (SPLIT == 4) red[w][al][16 * cb + i] = acc[b][cb][e];
+        else if (al < npj && n < ncols) part[(int64_t)(po + al) * ncols + n] = (double)acc[b][cb][e];
       }
-    }
+  if constexpr (SPLIT == 4) {
+    __syncthreads();
+    store_partials<float, 32>(red, npj, ncols, nbase + lane, po, part);
+  }
 }
 
 __global__ void __launch_bounds__(256) k_nl_final(const double* __restrict__ part, int ncols,
@@ -783,12 +833,18 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   const T* Cv = pick<T>(op->d.Cvals, op->d.Cvals_f);
   const T* Minv = pick<T>(op->d.Minv, op->d.Minv_f);
   const T* Cvi = pick<T>(op->d.Cvals_im, op->d.Cvals_im_f);
-  const dim3 grid(op->nitems, (ncols + 255) / 256), block(256);
+  // fewer than three waves per SIMD without the split: take it
+  static_assert(kRowsPerWaveGroup == 4, "waves of a reduction workgroup");
+  const bool split = (int64_t)op->nitems * ((ncols + 63) / 64) < 3000;
+  const dim3 grid(op->nitems, split ? (ncols + 63) / 64 : (ncols + 255) / 256), block(256);
   if constexpr (std::is_same<T, float>::value) {
     if (!op->cplx) {   // real operators in FP32: the matrix-core reduction
       auto go = [&](auto scale, auto b3) {
         constexpr bool SC = decltype(scale)::value, B3 = decltype(b3)::value;
-        hipLaunchKernelGGL((k_nl_reduce_mfma<SC, B3>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part);
+        if (split)
+          hipLaunchKernelGGL((k_nl_reduce_mfma<SC, B3, 4>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part);
+        else
+          hipLaunchKernelGGL((k_nl_reduce_mfma<SC, B3, 1>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part);
       };
       if (scale_minv) {
         if (bf3) go(std::true_type{}, std::true_type{}); else go(std::true_type{}, std::false_type{});
@@ -803,12 +859,18 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   }
   auto go = [&](auto scale, auto cplx) {
     constexpr bool SC = decltype(scale)::value, CX = decltype(cplx)::value;
-    if (op->npj_max <= 8)
-      hipLaunchKernelGGL((k_nl_reduce<T, 8, SC, CX>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part, Cvi);
-    else if (op->npj_max <= 18)
-      hipLaunchKernelGGL((k_nl_reduce<T, 18, SC, CX>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part, Cvi);
-    else
-      hipLaunchKernelGGL((k_nl_reduce<T, 32, SC, CX>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part, Cvi);
+    auto by_npj = [&](auto npj) {
+      constexpr int NPJ = decltype(npj)::value;
+      if (split)
+        hipLaunchKernelGGL((k_nl_reduce<T, NPJ, SC, CX, 4>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part,
+                           Cvi);
+      else
+        hipLaunchKernelGGL((k_nl_reduce<T, NPJ, SC, CX, 1>), grid, block, 0, s, X, ldx, ncols, Minv, Cv, op->d, part,
+                           Cvi);
+    };
+    if (op->npj_max <= 8) by_npj(std::integral_constant<int, 8>{});
+    else if (op->npj_max <= 18) by_npj(std::integral_constant<int, 18>{});
+    else by_npj(std::integral_constant<int, 32>{});
   };
   if (op->cplx) {
     if (scale_minv) go(std::true_type{}, std::true_type{}); else go(std::false_type{}, std::true_type{});
