@@ -112,8 +112,9 @@ template <typename T>
 pawfe_status do_apply(const pawfe_op* op, int which, const T* X, int64_t ldx, T* Y, int64_t ldy, int ncols,
                       const NlBufs& b, hipStream_t s, bool bf3 = false) {
   if (which == 0 || which == 1) {   // H or S
-    CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, false, b.part, b.c, s, bf3));
-    CHECK(launch_atom_mul(op, which == 0 ? op->d.dH : op->d.dS, nullptr, nullptr, 1.0, b.c, b.d, ncols, s));
+    CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, false, b.part, s, bf3));
+    CHECK(launch_atom_first(op, b.part, nullptr, which == 0 ? op->d.dH : op->d.dS, nullptr, nullptr, nullptr, ncols,
+                            nullptr, b.d, nullptr, s));
     if (op->natoms)
       CHECK(launch_node_nl_init<T>(op, b.d, ncols, Y, ldy, s));
     else
@@ -121,16 +122,17 @@ pawfe_status do_apply(const pawfe_op* op, int which, const T* X, int64_t ldx, T*
     return launch_cell<T>(op, which == 0 ? kModeH : kModeMass, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, bf3);
   }
   // Sinv_hat
-  CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, true, b.part, b.c, s, bf3));
-  CHECK(launch_atom_mul(op, op->d.dSinv, nullptr, nullptr, 1.0, b.c, b.d, ncols, s, op->d.dSinv_im));
+  CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, true, b.part, s, bf3));
+  CHECK(launch_atom_first(op, b.part, nullptr, op->d.dSinv, nullptr, nullptr, op->d.dSinv_im, ncols, nullptr, b.d,
+                          nullptr, s));
   return launch_node_sinv<T>(op, X, ldx, b.d, ncols, Y, ldy, s);
 }
 
 // Y = H X - S X diag(lam), FP64
 pawfe_status do_residual(const pawfe_op* op, const double* X, int64_t ldx, const double* lam, double* Y, int64_t ldy,
                          int ncols, const NlBufs& b, hipStream_t s) {
-  CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, b.c, s));
-  CHECK(launch_atom_mul(op, op->d.dH, op->d.dS, lam, 1.0, b.c, b.d, ncols, s));
+  CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, s));
+  CHECK(launch_atom_first(op, b.part, nullptr, op->d.dH, op->d.dS, lam, nullptr, ncols, nullptr, b.d, nullptr, s));
   CHECK(launch_node_nl_init<double>(op, op->natoms ? b.d : nullptr, ncols, Y, ldy, s));
   return launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s);
 }
@@ -189,7 +191,7 @@ size_t filter_ws_bytes(const pawfe_op* op, int64_t B, int32_t prec) {
   size_t b = align256((size_t)op->M * B * 8);            // Y
   if (fused_step(op, prec)) {
     b += 2 * align256((size_t)op->M * B * tr);                              // RX, RY
-    b += 4 * align256((size_t)std::max(op->npj_total, 1) * B * 8);         // c', d_prev, nw (two)
+    b += 3 * align256((size_t)std::max(op->npj_total, 1) * B * 8);         // d_prev, nw (two)
   } else {
     b += 3 * align256((size_t)op->M * B * tr);          // RX, RY, T
   }
@@ -232,12 +234,13 @@ pawfe_status filter_block(const pawfe_op* op, const double* X, int64_t ldx, cons
     const double znew = 1.0 / (gamma - zeta);
     const double a = 2.0 * znew / e;
     // projector coefficients of Sinv_hat R_Y and of H's non-local term on T
-    CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, nb.c, s, bf3));
-    CHECK(launch_atom_mul(op, op->d.dSinv, nullptr, nullptr, 1.0, nb.c, nb.d, nc, s, op->d.dSinv_im));
-    CHECK(launch_atom_gcorr(op, nb.c, nb.d, nb.t, nc, s));
-    CHECK(launch_atom_mul(op, op->d.dH, nullptr, nullptr, a, nb.t, nb.c, nc, s));   // q = a Dh t (into c)
+    CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, s, bf3));
+    CHECK(launch_atom_first(op, nb.part, nullptr, op->d.dSinv, nullptr, nullptr, op->d.dSinv_im, nc, nb.c, nb.d,
+                            nullptr, s));
+    CHECK(launch_atom_second(op, nb.c, nb.d, nullptr, nullptr, nb.t, nullptr, nullptr, nullptr, nullptr, nullptr, a,
+                             0.0, 0.0, nc, s));   // q = a Dh t (into t)
     // T = Sinv_hat R_Y; R_X <- -a c R_Y - zeta zeta' R_X + a C q + a Y Lambda_Y
-    CHECK(launch_node_cheb<TR>(op, RY, RX, Tb, ld, Yr, ldyr, nb.d, nb.c, lamY, lamX, lam_in, a, a * c,
+    CHECK(launch_node_cheb<TR>(op, RY, RX, Tb, ld, Yr, ldyr, nb.d, nb.t, lamY, lamX, lam_in, a, a * c,
                                zeta * znew, nc, s));
     // R_X += a H_loc T
     CHECK(launch_cell<TR>(op, kModeH, Tb, ld, RX, ld, nc, nullptr, a, s, bf3));
@@ -246,8 +249,9 @@ pawfe_status filter_block(const pawfe_op* op, const double* X, int64_t ldx, cons
     zeta = znew;
   }
   // step 5: Xout = Sinv_hat R_Y + X Lambda_Y
-  CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, nb.c, s, bf3));
-  CHECK(launch_atom_mul(op, op->d.dSinv, nullptr, nullptr, 1.0, nb.c, nb.d, nc, s, op->d.dSinv_im));
+  CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, s, bf3));
+  CHECK(launch_atom_first(op, nb.part, nullptr, op->d.dSinv, nullptr, nullptr, op->d.dSinv_im, nc, nullptr, nb.d,
+                          nullptr, s));
   return launch_node_finalize<TR>(op, RY, ld, nb.d, X, ldx, lamY, Xo, ldo, nc, s);
 }
 
@@ -272,7 +276,6 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
   TR* RY = cv.take<TR>((size_t)op->M * B);
   NlBufs nb = carve_nl(op, cv, B);
   const size_t na = (size_t)std::max(op->npj_total, 1) * B;
-  double* c2 = cv.take<double>(na);
   double* dprev = cv.take<double>(na);
   double* nwp = cv.take<double>(na);
   double* nwn = cv.take<double>(na);
@@ -302,17 +305,11 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
     const double znew = 1.0 / (gamma - zeta);
     const double a = 2.0 * znew / e;
     const double zz = zeta * znew;
-    CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, nb.c, s));
-    const double* cc = nb.c;
-    if (!first) {
-      CHECK(launch_atom_gcorr(op, nb.c, nwp, c2, nc, s));
-      cc = c2;
-    }
-    CHECK(launch_atom_mul(op, op->d.dSinv, nullptr, nullptr, 1.0, cc, dk, nc, s, op->d.dSinv_im));
-    CHECK(launch_atom_gcorr(op, cc, dk, nb.t, nc, s));
-    CHECK(launch_atom_mul(op, op->d.dH, nullptr, nullptr, a, nb.t, nb.c, nc, s));   // q = a Dh t (into c)
-    CHECK(launch_step_combine(op, nb.c, dk, first ? nullptr : dprev, first ? nullptr : nwp, nb.t, nwn, lamX, lamY,
-                              lam_in, a, a * c, zz, nc, s));
+    CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, s));
+    CHECK(launch_atom_first(op, nb.part, first ? nullptr : nwp, op->d.dSinv, nullptr, nullptr, op->d.dSinv_im, nc,
+                            nb.c, dk, nullptr, s));
+    CHECK(launch_atom_second(op, nb.c, dk, first ? nullptr : dprev, first ? nullptr : nwp, nullptr, nb.t, nwn, lamX,
+                             lamY, lam_in, a, a * c, zz, nc, s));
     CHECK(launch_node_fixup<TR>(op, nb.t, -1.0, nc, RY, ld, s));
     CHECK(launch_cell_step<TR>(op, RY, RX, ld, Yr, ldyr, lamY, a, a * c, zz, nc, s));
     std::swap(RX, RY);
@@ -323,15 +320,9 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
     zeta = znew;
   }
   // step 5: Xout = Sinv_hat R + X Lambda_Y with R = R~ + C w
-  CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, nb.c, s));
-  const double* cc = nb.c;
-  if (!first) {
-    CHECK(launch_atom_gcorr(op, nb.c, nwp, c2, nc, s));
-    cc = c2;
-  }
-  CHECK(launch_atom_mul(op, op->d.dSinv, nullptr, nullptr, 1.0, cc, dk, nc, s, op->d.dSinv_im));
-  CHECK(launch_step_combine(op, nullptr, dk, nullptr, first ? nullptr : nwp, nb.t, nullptr, nullptr, nullptr, nullptr,
-                            0.0, 0.0, 0.0, nc, s));   // v = nw + d
+  CHECK(launch_nl_reduce<TR>(op, RY, ld, nc, true, nb.part, s));
+  CHECK(launch_atom_first(op, nb.part, first ? nullptr : nwp, op->d.dSinv, nullptr, nullptr, op->d.dSinv_im, nc,
+                          nullptr, nullptr, nb.t, s));   // v = nw + d
   return launch_node_finalize<TR>(op, RY, ld, nb.t, X, ldx, lamY, Xo, ldo, nc, s);
 }
 
@@ -670,16 +661,11 @@ pawfe_status upload(pawfe_op* op, hipStream_t s) {
   CHECK(up(op, &d.dH, op->dH, s));
   CHECK(up(op, &d.dS, op->dS, s));
   CHECK(up(op, &d.dSinv, op->dSinv, s));
-  CHECK(up(op, &d.gp_ptr, op->gp_ptr, s));
-  CHECK(up(op, &d.gp_b, op->gp_b, s));
-  CHECK(up(op, &d.gp_off, op->gp_off, s));
+  CHECK(up(op, &d.gq_ptr, op->gq_ptr, s));
+  CHECK(up(op, &d.gq_row, op->gq_row, s));
+  CHECK(up(op, &d.gq_off, op->gq_off, s));
   CHECK(up(op, &d.Gvals, op->Gvals, s));
-  std::vector<int32_t> pa(op->npj_total), pal(op->npj_total), ga, gs, gt;
-  for (int a = 0; a < op->natoms; ++a)
-    for (int t = 0; t < op->nproj[a]; ++t) {
-      pa[op->poff[a] + t] = a;
-      pal[op->poff[a] + t] = t;
-    }
+  std::vector<int32_t> ga, gs, gt;
   for (int a = 0; a < op->natoms; ++a)
     for (int i = 0; i < op->nproj[a]; ++i)
       for (int j = 0; j < op->nproj[a]; ++j) {
@@ -687,8 +673,6 @@ pawfe_status upload(pawfe_op* op, hipStream_t s) {
         gs.push_back(i);
         gt.push_back(j);
       }
-  CHECK(up(op, &op->d_proj_atom, pa, s));
-  CHECK(up(op, &op->d_proj_alpha, pal, s));
   CHECK(up(op, &op->d_g2_atom, ga, s));
   CHECK(up(op, &op->d_g2_s, gs, s));
   CHECK(up(op, &op->d_g2_t, gt, s));
@@ -1395,7 +1379,8 @@ pawfe_status pawfe_band_energy_grad(const pawfe_op* cop, const void* Xv, int64_t
   }
   if (dE_dVq) CHECK(launch_density(op, X, ldx, (int)N, occ, dE_dVq, s));
   if (dE_dDH && op->natoms) {
-    CHECK(launch_nl_reduce<double>(op, X, ldx, (int)N, false, nb.part, nb.c, s));
+    CHECK(launch_nl_reduce<double>(op, X, ldx, (int)N, false, nb.part, s));
+    CHECK(launch_atom_first(op, nb.part, nullptr, nullptr, nullptr, nullptr, nullptr, (int)N, nb.c, nullptr, nullptr, s));
     CHECK(launch_grad_dh(op, nb.c, (int)N, occ, dE_dDH, s));
   }
   return PAWFE_OK;

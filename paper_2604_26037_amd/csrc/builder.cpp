@@ -649,20 +649,30 @@ pawfe_status build_host(const pawfe_op_desc* d, pawfe_op* op) {
       s0 = s1;
     }
   }
-  op->gp_ptr.assign(na + 1, 0);
-  op->gp_b.clear();
-  op->gp_off.clear();
+  // per atom one matrix over the projector rows of all its neighbours, in the
+  // order of the map (std::map iterates (a, b) in order)
+  op->gq_ptr.assign(na + 1, 0);
+  op->gq_row.clear();
+  op->gq_off.assign(na, 0);
   op->Gvals.clear();
-  for (auto& kv : Gab) op->gp_ptr[kv.first.first + 1]++;
-  for (int a = 0; a < na; ++a) op->gp_ptr[a + 1] += op->gp_ptr[a];
   op->Gvals_im.clear();
-  for (auto& kv : Gab) {   // std::map iterates (a, b) in order
-    op->gp_b.push_back(kv.first.second);
-    op->gp_off.push_back((int32_t)op->Gvals.size());
-    op->Gvals.insert(op->Gvals.end(), kv.second.begin(), kv.second.end());
-    if (op->cplx) {
-      const std::vector<double>& gi = Gab_im[kv.first];
-      op->Gvals_im.insert(op->Gvals_im.end(), gi.begin(), gi.end());
+  {
+    auto it = Gab.begin();
+    for (int a = 0; a < na; ++a) {
+      const auto first = it;
+      for (; it != Gab.end() && it->first.first == a; ++it)
+        for (int t = 0; t < op->nproj[it->first.second]; ++t) op->gq_row.push_back(op->poff[it->first.second] + t);
+      op->gq_ptr[a + 1] = (int32_t)op->gq_row.size();
+      op->gq_off[a] = (int32_t)op->Gvals.size();
+      for (int s = 0; s < op->nproj[a]; ++s)
+        for (auto k = first; k != it; ++k) {
+          const int nb = op->nproj[k->first.second];
+          op->Gvals.insert(op->Gvals.end(), &k->second[s * nb], &k->second[s * nb] + nb);
+          if (op->cplx) {
+            const std::vector<double>& gi = Gab_im[k->first];
+            op->Gvals_im.insert(op->Gvals_im.end(), &gi[s * nb], &gi[s * nb] + nb);
+          }
+        }
     }
   }
 

@@ -83,9 +83,9 @@ struct DeviceTables {
   double* dS = nullptr;
   double* dSinv = nullptr;
   double* dSinv_im = nullptr;     // complex operators with the exact G (else null)
-  int32_t* gp_ptr = nullptr;      // [natoms+1] neighbour pairs (a, b) sharing support nodes
-  int32_t* gp_b = nullptr;
-  int32_t* gp_off = nullptr;      // offset of G^{ab} (nproj_a x nproj_b, row-major)
+  int32_t* gq_ptr = nullptr;      // [natoms+1] projector rows of an atom's neighbours (atoms sharing support nodes)
+  int32_t* gq_row = nullptr;      // their rows in the atom vectors
+  int32_t* gq_off = nullptr;      // [natoms] offset of G^{a.} (nproj_a x its neighbours' rows, row-major)
   double* Gvals = nullptr;
   double* Gvals_im = nullptr;     // complex operators (else null)
   // general operators (graded mesh and / or the GGA term)
@@ -143,7 +143,7 @@ struct pawfe_op {
   std::vector<double> Cvals_im;        // imaginary parts (complex operators)
   std::vector<int32_t> atom_coff;
   std::vector<double> dH, dS, dSinv, dSinv_im;   // dSinv_im: complex operators, exact G
-  std::vector<int32_t> gp_ptr, gp_b, gp_off;
+  std::vector<int32_t> gq_ptr, gq_row, gq_off;
   std::vector<double> Gvals, Gvals_im;
   int64_t nsrow = 0, nent = 0;
   std::vector<int32_t> node2srow, srow_ptr, srow_atom, srow_coff;
@@ -156,8 +156,6 @@ struct pawfe_op {
   int64_t item_rows_total = 0;         // sum over items of nproj (partial rows per column)
   int sinv_mode;
   pawfe::DeviceTables d;
-  int32_t* d_proj_atom = nullptr;   // [npj_total] atom of each projector
-  int32_t* d_proj_alpha = nullptr;  // [npj_total] index inside its atom
   int32_t* d_g2_atom = nullptr;     // [npj2_total] (atom, s, t) of each Delta entry
   int32_t* d_g2_s = nullptr;
   int32_t* d_g2_t = nullptr;

@@ -106,31 +106,32 @@ pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t 
 
 // ---- non-local / node-wise kernels (kernels_nl.hip) ----
 
-// c[(poff_a + alpha) * ncols + n] = sum_{I in supp(a)} C^a[I][alpha] s_I X[I][n],
-// s_I = M_D^{-1}[I] if scale_minv, else 1.  part: >= item_rows_total*ncols doubles.
+// Partial sums (per work item of an atom's rows) of
+// c_a[alpha][n] = sum_{I in supp(a)} C^a[I][alpha] s_I X[I][n],
+// s_I = M_D^{-1}[I] if scale_minv, else 1; launch_atom_first adds them up.
+// part: >= item_rows_total*ncols doubles.
 // Real operators in FP32 run on the matrix cores (FP32, or bf16x3 split
 // products when bf3); FP64 and complex operators on the vector ALUs.
 template <typename T>
 pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int ncols, bool scale_minv,
-                              double* part, double* c, hipStream_t s, bool bf3 = false);
+                              double* part, hipStream_t s, bool bf3 = false);
 
-// out = (D1 - lam_n D2) in  (per atom block; D2 may be NULL), scaled by f.
-// D1i: imaginary part of D1 (complex operators, Delta_Sinv with the exact G);
-// the columns are then (re, im) pairs of complex columns.
-pawfe_status launch_atom_mul(const pawfe_op* op, const double* D1, const double* D2, const double* lam,
-                             double f, const double* in, double* out, int ncols, hipStream_t s,
-                             const double* D1i = nullptr);
+// From the partials of launch_nl_reduce: c_a (- sum_b G^{ab} nw_b when nw is
+// given), d_a = (D1 - lam_n D2) c_a per atom block (D2 may be null), v = nw + d.
+// c, dv, v may be null (not wanted); D1 null: c only.  D1i: imaginary part of
+// D1 (complex operators, Delta_Sinv with the exact G); the columns are then
+// (re, im) pairs of complex columns.  Rows are [poff_a + alpha][ncols].
+pawfe_status launch_atom_first(const pawfe_op* op, const double* part, const double* nw, const double* D1,
+                               const double* D2, const double* lam, const double* D1i, int ncols, double* c,
+                               double* dv, double* v, hipStream_t s);
 
-// out_a = c_a - sum_b G^{ab} d_b
-pawfe_status launch_atom_gcorr(const pawfe_op* op, const double* c, const double* d, double* out,
-                               int ncols, hipStream_t s);
-
-// Projector part of the fused Chebyshev step: v = nw_prev + d,
-// nw = -q + ac d + zz d_prev, lamX = a lamY lam_in - ac lamY - zz lamX
-// (nw_prev, d_prev null: zero; q null: v only)
-pawfe_status launch_step_combine(const pawfe_op* op, const double* q, const double* d, const double* dprev,
-                                 const double* nwprev, double* v, double* nw, double* lamX, const double* lamY,
-                                 const double* lam_in, double a, double ac, double zz, int ncols, hipStream_t s);
+// t_a = c_a - sum_b G^{ab} d_b,  q = a Delta_H t;  qv (if given) = q;  v (if
+// given) = nw_prev + d, nw = -q + ac d + zz d_prev (nw_prev, d_prev null:
+// zero);  lamX (if given) = a lamY lam_in - ac lamY - zz lamX
+pawfe_status launch_atom_second(const pawfe_op* op, const double* c, const double* dv, const double* dprev,
+                                const double* nwprev, double* qv, double* v, double* nw, double* lamX,
+                                const double* lamY, const double* lam_in, double a, double ac, double zz, int ncols,
+                                hipStream_t s);
 
 // out1 += s1 C v1 on the support rows (atom colour by colour)
 template <typename T>

@@ -9,7 +9,7 @@
 // C^a row is wave-uniform (scalar loads).  Partial sums go to a workspace and
 // a second kernel adds the chunks of each atom in a fixed order (no atomics,
 // deterministic).  The atom-block products (Delta x c, G^{ab} corrections)
-// are tiny and run one thread per (projector, column).  The add-back
+// are small and run in two launches (k_atom_first, k_atom_second).  The add-back
 // sum_a C^a q_a on the support rows is a separate pass per atom colour
 // (k_nl_fixup) after the node-wise kernels that stream the rows.
 
@@ -265,111 +265,201 @@ __global__ void __launch_bounds__(256) k_nl_reduce_mfma(const float* __restrict_
   }
 }
 
-__global__ void __launch_bounds__(256) k_nl_final(const double* __restrict__ part, int ncols,
-                                                  const int32_t* __restrict__ proj_atom,
-                                                  const int32_t* __restrict__ proj_alpha, DeviceTables d,
-                                                  double* __restrict__ c) {
-  const int g = blockIdx.x;
-  const int n = blockIdx.y * 256 + threadIdx.x;
-  if (n >= ncols) return;
-  const int a = proj_atom[g], al = proj_alpha[g];
-  const int i0 = d.item_ptr[a], i1 = d.item_ptr[a + 1];
-  // the partials of all items are independent loads: eight in flight at a
-  // time, summed in item order
-  double s = 0.0;
-  for (int it = i0; it < i1; it += 8) {
-    double v[8];
+// The atom-block algebra of a step, one workgroup per (atom, 16 columns), in
+// two launches (every atom's d is needed before any t):
+//   k_atom_first:   c = sum of the items' partials (- sum_b G^{ab} nw_b),
+//                   d = (D1 - lam_n D2) c,  v = nw + d
+//   k_atom_second:  t = c - sum_b G^{ab} d_b,  q = a Delta_H t,
+//                   v = nw + d,  nw' = -q + ac d + zz d_prev  and the
+//                   recurrence of Lambda_X
+// The sum over the neighbours is one contraction (npj x about 150 rows at the
+// paper's density x 16 columns) on the FP64 matrix cores
+// (v_mfma_f64_16x16x4: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
+// D[4 e + lane / 16][lane % 16] in element e); the four waves take every
+// fourth step of four rows, whose loads are all in flight together, and add
+// up in LDS.  The work is a few latencies long whatever the size, so a step
+// has two such launches (128 atoms x 256 columns 71 + 35 us, 16 atoms x 192
+// 18 + 11 us) in place of one per product, which read the neighbours' vectors
+// once per projector (six launches, 182 us and 54 us).
+// Complex operators: the columns are (re, im) pairs and an imaginary part
+// mixes them: D c adds s Di c[n ^ 1], s = -1 on real, +1 on imaginary columns.
+typedef double D4 __attribute__((ext_vector_type(4)));
+
+struct AtomTile {
+  double g[4][kNpjMax][17];   // the waves' sums of G x
+  double c[kNpjMax][17];      // the atom's own vector
+};
+
+// the waves' parts of sum_b G^{ab} x_b, into L.g
+__device__ __forceinline__ void gab_parts(const DeviceTables& d, int a, int npj, int n, int ncols,
+                                          const double* __restrict__ x, AtomTile& L) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 15, k = lane >> 4;
+  const int k0 = d.gq_ptr[a], K = d.gq_ptr[a + 1] - k0;
+  const double* G = d.Gvals + d.gq_off[a];
+  const double* Gi = d.Gvals_im ? d.Gvals_im + d.gq_off[a] : nullptr;
+  const double sg = (n & 1) ? 1.0 : -1.0;
+  D4 acc[2] = {D4{0, 0, 0, 0}, D4{0, 0, 0, 0}};
+  constexpr int U = 5;   // steps in flight
+  for (int j0 = 4 * w; j0 < K; j0 += 16 * U) {
+    double b[U], a0[U], a1[U], i0[U], i1[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = it + u < i1 ? it + u : i1 - 1;
-      v[u] = part[(int64_t)(d.item_poff[k] + al) * ncols + n];
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 16 * u + k, jj = j < K ? j : K - 1;
+      b[u] = x[(int64_t)d.gq_row[k0 + jj] * ncols + n];
+      const bool in0 = j < K && i < npj, in1 = j < K && 16 + i < npj;
+      a0[u] = G[in0 ? (int64_t)i * K + j : 0];
+      a1[u] = G[in1 ? (int64_t)(16 + i) * K + j : 0];
+      if (!in0) a0[u] = 0.0;
+      if (!in1) a1[u] = 0.0;
+      if (Gi) {
+        i0[u] = in0 ? Gi[(int64_t)i * K + j] : 0.0;
+        i1[u] = in1 ? Gi[(int64_t)(16 + i) * K + j] : 0.0;
+      }
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (it + u < i1) s += v[u];
+    for (int u = 0; u < U; ++u) {
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u], b[u], acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u], b[u], acc[1], 0, 0, 0);
+      if (Gi) {
+        const double p = sg * __shfl_xor(b[u], 1);
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(i0[u], p, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(i1[u], p, acc[1], 0, 0, 0);
+      }
+    }
   }
-  c[(int64_t)g * ncols + n] = s;
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) L.g[w][16 * m + 4 * e + k][i] = acc[m][e];
 }
 
-// D1i (complex D1 = D1 + i D1i; complex operators): the columns are (re, im)
-// pairs, D1 c mixes them: + s D1i c[n ^ 1], s = -1 on real, +1 on imaginary
-// columns.
-__global__ void __launch_bounds__(256) k_atom_mul(const double* __restrict__ D1, const double* __restrict__ D2,
-                                                  const double* __restrict__ lam, double f,
-                                                  const double* __restrict__ in, double* __restrict__ out,
-                                                  int ncols, const int32_t* __restrict__ proj_atom,
-                                                  const int32_t* __restrict__ proj_alpha, DeviceTables d,
-                                                  const double* __restrict__ D1i) {
-  const int g = blockIdx.x;
-  const int n = blockIdx.y * 256 + threadIdx.x;
-  if (n >= ncols) return;
-  const int a = proj_atom[g], s = proj_alpha[g];
+__device__ __forceinline__ double gab_sum(const AtomTile& L, int s, int j) {
+  return (L.g[0][s][j] + L.g[1][s][j]) + (L.g[2][s][j] + L.g[3][s][j]);
+}
+
+// row s, column j of D c (c in L.c), with the imaginary part Di
+__device__ __forceinline__ double block_row(const double* __restrict__ D, const double* __restrict__ Di, int s, int j,
+                                            int npj, int n, const AtomTile& L) {
+  double o = 0.0;
+#pragma unroll 9
+  for (int t = 0; t < npj; ++t) o += D[s * npj + t] * L.c[t][j];
+  if (Di) {
+    double oi = 0.0;
+#pragma unroll 9
+    for (int t = 0; t < npj; ++t) oi += Di[s * npj + t] * L.c[t][j ^ 1];
+    o += (n & 1) ? oi : -oi;
+  }
+  return o;
+}
+
+// thread -> column j of the tile and rows s = tid / 16, + 16
+__global__ void __launch_bounds__(256)
+k_atom_first(const double* __restrict__ part, const double* __restrict__ nw, const double* __restrict__ D1,
+             const double* __restrict__ D2, const double* __restrict__ lam, const double* __restrict__ D1i, int ncols,
+             double* __restrict__ c, double* __restrict__ dv, double* __restrict__ v, DeviceTables d) {
+  __shared__ AtomTile L;
+  const int a = blockIdx.x;
+  const int j = threadIdx.x & 15, s0 = threadIdx.x >> 4;
+  const int n0 = blockIdx.y * 16 + j;
+  const bool valid = n0 < ncols;
+  const int n = valid ? n0 : (ncols > 1 ? n0 & 1 : 0);   // in range, of the column's parity
   const int npj = d.nproj[a], po = d.poff[a];
-  const double* r1 = D1 + d.poff2[a] + s * npj;
-  double acc = 0.0, acc2 = 0.0;
-  for (int t = 0; t < npj; ++t) acc += r1[t] * in[(int64_t)(po + t) * ncols + n];
-  if (D1i) {
-    const double* ri = D1i + d.poff2[a] + s * npj;
-    double ai = 0.0;
-    for (int t = 0; t < npj; ++t) ai += ri[t] * in[(int64_t)(po + t) * ncols + (n ^ 1)];
-    acc += (n & 1) ? ai : -ai;
+  const int i0 = d.item_ptr[a], ni = d.item_ptr[a + 1] - i0;
+  if (nw) gab_parts(d, a, npj, n, ncols, nw, L);
+  // the partials of all items are independent loads: up to 24 of both rows in
+  // flight at a time, summed in item order
+  constexpr int U = 24;
+  const double* src = part + (int64_t)d.item_poff[i0] * ncols + n;
+  const int64_t gs = (int64_t)npj * ncols;
+  const int sa = s0 < npj ? s0 : 0, sb = s0 + 16 < npj ? s0 + 16 : sa;
+  double acc[2] = {0.0, 0.0};
+  for (int it = 0; it < ni; it += U) {
+    double p[U], q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double* g = src + (it + u < ni ? it + u : it) * gs;
+      p[u] = g[(int64_t)sa * ncols];
+      if (npj > 16) q[u] = g[(int64_t)sb * ncols];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (it + u < ni) {
+        acc[0] += p[u];
+        if (npj > 16) acc[1] += q[u];
+      }
   }
-  if (D2) {
-    const double* r2 = D2 + d.poff2[a] + s * npj;
-    for (int t = 0; t < npj; ++t) acc2 += r2[t] * in[(int64_t)(po + t) * ncols + n];
-    acc -= lam[n] * acc2;
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int s = s0 + 16 * h;
+    if (s >= npj) break;
+    if (nw) acc[h] -= gab_sum(L, s, j);
+    L.c[s][j] = acc[h];
+    if (c && valid) c[(int64_t)(po + s) * ncols + n] = acc[h];
   }
-  out[(int64_t)g * ncols + n] = f * acc;
+  if (!D1) return;
+  __syncthreads();
+  if (!valid) return;
+  const double l = D2 ? lam[n] : 0.0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int s = s0 + 16 * h;
+    if (s >= npj) break;
+    double o = block_row(D1 + d.poff2[a], D1i ? D1i + d.poff2[a] : nullptr, s, j, npj, n, L);
+    if (D2) o -= l * block_row(D2 + d.poff2[a], nullptr, s, j, npj, n, L);
+    const int64_t g = (int64_t)(po + s) * ncols + n;
+    if (dv) dv[g] = o;
+    if (v) v[g] = (nw ? nw[g] : 0.0) + o;
+  }
 }
 
-__global__ void __launch_bounds__(256) k_atom_gcorr(const double* __restrict__ c, const double* __restrict__ dv,
-                                                    double* __restrict__ out, int ncols,
-                                                    const int32_t* __restrict__ proj_atom,
-                                                    const int32_t* __restrict__ proj_alpha, DeviceTables d) {
-  const int g = blockIdx.x;
-  const int n = blockIdx.y * 256 + threadIdx.x;
-  if (n >= ncols) return;
-  const int a = proj_atom[g], s = proj_alpha[g];
-  double acc = c[(int64_t)g * ncols + n];
-  for (int k = d.gp_ptr[a]; k < d.gp_ptr[a + 1]; ++k) {
-    const int b = d.gp_b[k], nb = d.nproj[b], pb = d.poff[b];
-    const double* G = d.Gvals + d.gp_off[k] + s * nb;
-#pragma unroll 6
-    for (int u = 0; u < nb; ++u) acc -= G[u] * dv[(int64_t)(pb + u) * ncols + n];
-    if (d.Gvals_im) {   // complex operators: (re, im) column pairs mix
-      const double* Gi = d.Gvals_im + d.gp_off[k] + s * nb;
-      double ai = 0.0;
-      for (int u = 0; u < nb; ++u) ai += Gi[u] * dv[(int64_t)(pb + u) * ncols + (n ^ 1)];
-      acc -= (n & 1) ? ai : -ai;
+// nw, dprev may be null (zero: the first step); qv gets q where it is wanted
+// by itself (the step with an explicit T: v, nw' and lamX null).  natoms = 0:
+// the recurrence of Lambda_X only.
+__global__ void __launch_bounds__(256)
+k_atom_second(int natoms, int ncols, const double* __restrict__ c, const double* __restrict__ dv,
+              const double* __restrict__ dprev, const double* __restrict__ nwprev, const double* __restrict__ dH,
+              double* __restrict__ qv, double* __restrict__ v, double* __restrict__ nw, double* __restrict__ lamX,
+              const double* __restrict__ lamY, const double* __restrict__ lam_in, double a_, double ac, double zz,
+              DeviceTables d) {
+  __shared__ AtomTile L;
+  const int a = blockIdx.x;
+  const int j = threadIdx.x & 15, s0 = threadIdx.x >> 4;
+  const int n0 = blockIdx.y * 16 + j;
+  const bool valid = n0 < ncols;
+  if (lamX && a == 0 && s0 == 0 && valid)
+    lamX[n0] = a_ * lamY[n0] * lam_in[n0] - ac * lamY[n0] - zz * lamX[n0];
+  if (a >= natoms) return;
+  const int n = valid ? n0 : (ncols > 1 ? n0 & 1 : 0);
+  const int npj = d.nproj[a], po = d.poff[a];
+  gab_parts(d, a, npj, n, ncols, dv, L);
+  double acc[2], dd[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int s = s0 + 16 * h;
+    if (s >= npj) break;
+    acc[h] = c[(int64_t)(po + s) * ncols + n];
+    dd[h] = dv[(int64_t)(po + s) * ncols + n];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (s0 + 16 * h < npj) L.c[s0 + 16 * h][j] = acc[h] - gab_sum(L, s0 + 16 * h, j);
+  __syncthreads();
+  if (!valid) return;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int s = s0 + 16 * h;
+    if (s >= npj) break;
+    const double q = a_ * block_row(dH + d.poff2[a], nullptr, s, j, npj, n, L);
+    const int64_t g = (int64_t)(po + s) * ncols + n;
+    if (qv) qv[g] = q;
+    if (v) {
+      v[g] = (nwprev ? nwprev[g] : 0.0) + dd[h];
+      nw[g] = -q + ac * dd[h] + (dprev ? zz * dprev[g] : 0.0);
     }
   }
-  out[(int64_t)g * ncols + n] = acc;
-}
-
-// Projector part of the fused Chebyshev step (per projector row g, column n;
-// nw = -w, w the vector whose C w the step still owes R_X):
-//   v  = nw_prev + d                  (the step's fix-up R_Y -= C v)
-//   nw = -q + ac d + zz d_prev        (q already scaled by a)
-// and, on row 0, lamX = a lamY lam_in - ac lamY - zz lamX.  nw_prev and
-// d_prev may be null (zero: the first step); q null: v only, no nw, no lambda.
-__global__ void __launch_bounds__(256) k_step_combine(int npj, int ncols, const double* __restrict__ q,
-                                                      const double* __restrict__ dv,
-                                                      const double* __restrict__ dprev,
-                                                      const double* __restrict__ nwprev, double* __restrict__ v,
-                                                      double* __restrict__ nw, double* __restrict__ lamX,
-                                                      const double* __restrict__ lamY,
-                                                      const double* __restrict__ lam_in, double a, double ac,
-                                                      double zz) {
-  const int g = blockIdx.x;
-  const int n = blockIdx.y * 256 + threadIdx.x;
-  if (n >= ncols) return;
-  if (g < npj) {
-    const int64_t i = (int64_t)g * ncols + n;
-    const double d = dv[i];
-    v[i] = (nwprev ? nwprev[i] : 0.0) + d;
-    if (q) nw[i] = -q[i] + ac * d + (dprev ? zz * dprev[i] : 0.0);
-  }
-  if (g == 0 && q) lamX[n] = a * lamY[n] * lam_in[n] - ac * lamY[n] - zz * lamX[n];
 }
 
 // Row-wise kernels.  A 256-thread block is 4 waves; a wave takes R
@@ -827,8 +917,8 @@ const T* pick(const double* d64, const float* d32) {
 // ---------------------------------------------------------------------------
 
 template <typename T>
-pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int ncols, bool scale_minv,
-                              double* part, double* c, hipStream_t s, bool bf3) {
+pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int ncols, bool scale_minv, double* part,
+                              hipStream_t s, bool bf3) {
   if (op->natoms == 0 || ncols <= 0) return PAWFE_OK;
   const T* Cv = pick<T>(op->d.Cvals, op->d.Cvals_f);
   const T* Minv = pick<T>(op->d.Minv, op->d.Minv_f);
@@ -851,8 +941,6 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
       } else {
         if (bf3) go(std::false_type{}, std::true_type{}); else go(std::false_type{}, std::false_type{});
       }
-      const dim3 g2(op->npj_total, (ncols + 255) / 256);
-      hipLaunchKernelGGL(k_nl_final, g2, block, 0, s, part, ncols, op->d_proj_atom, op->d_proj_alpha, op->d, c);
       PAWFE_HIP(hipGetLastError());
       return PAWFE_OK;
     }
@@ -877,22 +965,31 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   } else {
     if (scale_minv) go(std::true_type{}, std::false_type{}); else go(std::false_type{}, std::false_type{});
   }
-  const dim3 g2(op->npj_total, (ncols + 255) / 256);
-  hipLaunchKernelGGL(k_nl_final, g2, block, 0, s, part, ncols, op->d_proj_atom, op->d_proj_alpha, op->d, c);
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }
-template pawfe_status launch_nl_reduce<double>(const pawfe_op*, const double*, int64_t, int, bool, double*, double*,
+template pawfe_status launch_nl_reduce<double>(const pawfe_op*, const double*, int64_t, int, bool, double*,
                                                hipStream_t, bool);
-template pawfe_status launch_nl_reduce<float>(const pawfe_op*, const float*, int64_t, int, bool, double*, double*,
-                                              hipStream_t, bool);
+template pawfe_status launch_nl_reduce<float>(const pawfe_op*, const float*, int64_t, int, bool, double*, hipStream_t,
+                                              bool);
 
-pawfe_status launch_atom_mul(const pawfe_op* op, const double* D1, const double* D2, const double* lam, double f,
-                             const double* in, double* out, int ncols, hipStream_t s, const double* D1i) {
+pawfe_status launch_atom_first(const pawfe_op* op, const double* part, const double* nw, const double* D1,
+                               const double* D2, const double* lam, const double* D1i, int ncols, double* c,
+                               double* dv, double* v, hipStream_t s) {
   if (op->natoms == 0 || ncols <= 0) return PAWFE_OK;
-  const dim3 grid(op->npj_total, (ncols + 255) / 256), block(256);
-  hipLaunchKernelGGL(k_atom_mul, grid, block, 0, s, D1, D2, lam, f, in, out, ncols, op->d_proj_atom,
-                     op->d_proj_alpha, op->d, D1i);
+  hipLaunchKernelGGL(k_atom_first, dim3(op->natoms, (ncols + 15) / 16), dim3(256), 0, s, part, nw, D1, D2, lam, D1i,
+                     ncols, c, dv, v, op->d);
+  PAWFE_HIP(hipGetLastError());
+  return PAWFE_OK;
+}
+
+pawfe_status launch_atom_second(const pawfe_op* op, const double* c, const double* dv, const double* dprev,
+                                const double* nwprev, double* qv, double* v, double* nw, double* lamX,
+                                const double* lamY, const double* lam_in, double a, double ac, double zz, int ncols,
+                                hipStream_t s) {
+  if (ncols <= 0 || (op->natoms == 0 && !lamX)) return PAWFE_OK;
+  hipLaunchKernelGGL(k_atom_second, dim3(std::max(op->natoms, 1), (ncols + 15) / 16), dim3(256), 0, s, op->natoms,
+                     ncols, c, dv, dprev, nwprev, op->d.dH, qv, v, nw, lamX, lamY, lam_in, a, ac, zz, op->d);
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }
@@ -909,27 +1006,6 @@ __global__ void k_dup_pairs(const double* __restrict__ in, double* __restrict__ 
 pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t s) {
   if (n <= 0) return PAWFE_OK;
   hipLaunchKernelGGL(k_dup_pairs, dim3((n + 255) / 256), dim3(256), 0, s, in, out, n);
-  PAWFE_HIP(hipGetLastError());
-  return PAWFE_OK;
-}
-
-pawfe_status launch_step_combine(const pawfe_op* op, const double* q, const double* d, const double* dprev,
-                                 const double* nwprev, double* v, double* nw, double* lamX, const double* lamY,
-                                 const double* lam_in, double a, double ac, double zz, int ncols, hipStream_t s) {
-  if (ncols <= 0) return PAWFE_OK;
-  if (op->npj_total == 0 && !q) return PAWFE_OK;
-  const dim3 grid(std::max(op->npj_total, 1), (ncols + 255) / 256), block(256);
-  hipLaunchKernelGGL(k_step_combine, grid, block, 0, s, op->npj_total, ncols, q, d, dprev, nwprev, v, nw, lamX, lamY,
-                     lam_in, a, ac, zz);
-  PAWFE_HIP(hipGetLastError());
-  return PAWFE_OK;
-}
-
-pawfe_status launch_atom_gcorr(const pawfe_op* op, const double* c, const double* dv, double* out, int ncols,
-                               hipStream_t s) {
-  if (op->natoms == 0 || ncols <= 0) return PAWFE_OK;
-  const dim3 grid(op->npj_total, (ncols + 255) / 256), block(256);
-  hipLaunchKernelGGL(k_atom_gcorr, grid, block, 0, s, c, dv, out, ncols, op->d_proj_atom, op->d_proj_alpha, op->d);
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }
