@@ -47,6 +47,12 @@ struct Wave {
   static constexpr int NPX = RB * H, NQX = QB * H;
   static constexpr int slab = NQ * NQ * NP * CB;
 };
+// Waves (neighbouring column tiles of one cell) per workgroup.  The mass term,
+// which is all memory, takes four: they read the same 128-byte lines through
+// one L1 (0.292 -> 0.264 ms FP32, 0.574 -> 0.507 FP64).  The others lose more
+// by starting and ending together (K + V 0.299 -> 0.320, step 0.392 -> 0.438).
+template <int MODE>
+constexpr int kWaveTiles = (MODE == kValuMass || MODE == kValuGenMass) ? 4 : 1;
 
 // order a wave's own LDS accesses (they execute in order; this keeps the
 // compiler from moving them across)
@@ -82,7 +88,7 @@ __device__ __forceinline__ void swap_halves(T& lo, T& hi) {
 }  // namespace
 
 template <typename T, int NP, int NQ, int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(64 * kWaveTiles<MODE>) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   using W = Wave<T, NP, NQ>;
   constexpr int H = W::H, CB = W::CB, G = W::G, RB = W::RB, QB = W::QB, NPX = W::NPX, NQX = W::NQX;
@@ -92,9 +98,13 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep;
   constexpr bool SC = STEP;
   constexpr int NQ2 = NQ * NQ, NP2 = NP * NP, NQ3 = NQ * NQ * NQ;
-  __shared__ T sl[W::slab];
+  constexpr int WT = kWaveTiles<MODE>;
+  static_assert(MASS || WT == 1, "V(q) W_q is staged by one wave");
+  __shared__ T slabs[WT][W::slab];
   __shared__ T sv[MASS ? 1 : NQ3];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = WT == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  T* const sl = slabs[wave];
   const int col = lane % CB;
   const int slot = (lane / CB) % W::PS;
   const int h = H == 2 ? lane >> 5 : 0;
@@ -115,7 +125,9 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   const int packed = cells[cc];
   const int ci = packed & 1023, cj = (packed >> 10) & 1023, ck = (packed >> 20) & 1023;
   const int e = ci + A.n0 * (cj + A.n1 * ck);
-  const int n = (item - cc * ncoltiles) * CB + col;
+  const int tile = (item - cc * ncoltiles) * WT + wave;
+  if (WT > 1 && tile * CB >= A.ncols) return;   // wave-uniform
+  const int n = tile * CB + col;
   const bool valid = n < A.ncols;
   const int nn = valid ? n : 0;
   const bool lastx = ci + 1 == A.n0;
@@ -131,24 +143,38 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       opaque_s(o[a]);
     });
   };
-  // the lane's row r of array `base` (`ldb` bytes per row), without the node
-  // column; recomputed for each use rather than held in registers
-  auto rowptr = [&](auto* base, uint64_t ldb, int r) {
+  // the lane's plane of array `base` (`ldb` bytes per row): its pointer is
+  // formed for each use rather than held in registers
+  auto planeptr = [&](auto* base, uint64_t ldb) {
     using P = decltype(base);
     using C = typename std::conditional<std::is_const<typename std::remove_pointer<P>::type>::value, const char,
                                         char>::type;
-    int gz = ck * p + c, gy = cj * p + lrow(r);
-    asm volatile("" : "+v"(gz));
+    int gz = ck * p + c;
+    opaque(gz);
     gz = gz >= Gz ? gz - Gz : gz;
+    return reinterpret_cast<C*>(base + nn) + (uint64_t)(uint32_t)(gz * (Gx * Gy)) * (uint32_t)ldb;
+  };
+  // its row r, without the node column; scalar steps except where the halves
+  // of a plane (rows r and RB + r) may wrap differently
+  auto rowptr = [&](auto* plane, uint64_t ldb, int r) {
+    if (H == 1 || r < NP - 1 - RB) {
+      int gy = cj * p + r;
+      gy = H == 1 && gy >= Gy ? gy - Gy : gy;
+      plane += (uint64_t)(uint32_t)(gy * Gx) * (uint32_t)ldb;
+      if (H == 2) plane += h ? (uint64_t)(uint32_t)(RB * Gx) * (uint32_t)ldb : 0;
+      return plane;
+    }
+    int gy = cj * p + lrow(r);
     gy = gy >= Gy ? gy - Gy : gy;
-    return reinterpret_cast<C*>(base + nn) + (uint64_t)(uint32_t)(Gx * (gy + Gy * gz)) * (uint32_t)ldb;
+    return plane + (uint64_t)(uint32_t)(gy * Gx) * (uint32_t)ldb;
   };
 
   T x[RB][NP];
   uint64_t xo[NP];
   xoffs(ldxb, xo);
+  const char* xp = planeptr(A.X, ldxb);
   sfor<RB>([&](auto r) {
-    const char* q = rowptr(A.X, ldxb, r);
+    const char* q = rowptr(xp, ldxb, r);
     sfor<NP>([&](auto a) { x[r][a] = *(const T*)(q + xo[a]); });
   });
   // the factor of the result goes into V(q) W_q and the kinetic factors
@@ -172,7 +198,6 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       if (NQ3 % 64 == 0 || lane + 64 * i < NQ3) v[i] = A.Vw[(int64_t)e * NQ3 + lane + 64 * i];
-    wave_lds_order();
 #pragma unroll
     for (int i = 0; i < NV; ++i)
       if (NQ3 % 64 == 0 || lane + 64 * i < NQ3) sv[lane + 64 * i] = f * v[i];
@@ -259,11 +284,15 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     cm = ((ConstUP)A.own)[e] >> (c == 0 ? 0 : (c == NP - 1 ? 18 : 9));   // the lane's 9 (x, y) classes
     const T mac = (T)(-A.sac);
     sfor<RB>([&](auto r) {
-      // opaque: the products are formed here, not kept beside x from the load on
+      // opaque: the products are formed here, not kept beside x from the load
+      // on, and the sums not left until the end
       sfor<NP>([&](auto a) { opaque(x[r][a]); });
       const unsigned cr = cm >> row_class(r);
-      sfor<NP>([&](auto a) { acc[r][a] += ((cr >> (a == 0 ? 0 : (a == NP - 1 ? 2 : 1))) & 1u) ? mac * x[r][a] : T(0); });
-      sfor<NP>([&](auto a) { opaque(acc[r][a]); });
+      const T m0 = cr & 1u ? mac : T(0), m1 = cr & 2u ? mac : T(0), m2 = cr & 4u ? mac : T(0);
+      sfor<NP>([&](auto a) {
+        acc[r][a] = fma_t(a == 0 ? m0 : (a == NP - 1 ? m2 : m1), x[r][a], acc[r][a]);
+        opaque(acc[r][a]);
+      });
     });
   }
   // ---- M and K terms -----------------------------------------------------
@@ -338,22 +367,27 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   // used after the last z pass
   T yo[RB][NP];
   xoffs(ldyb, xo);
+  const char* yp = planeptr((const T*)A.Y, ldyb);
   sfor<RB>([&](auto r) {
-    const char* q = rowptr((const T*)A.Y, ldyb, r);
+    const char* q = rowptr(yp, ldyb, r);
     sfor<NP>([&](auto a) { yo[r][a] = *(const T*)(q + xo[a]); });
   });
   uint64_t x64[STEP ? NP : 1];
   if constexpr (STEP) xoffs(ld64b, x64);
-  double yr[STEP ? RB : 1][NP];
-  auto load_y = [&](auto r) {
+  const char* y6 = STEP ? planeptr(A.y64, ld64b) : nullptr;
+  double yr[STEP ? RB : 1][NP];   // set at first visits only
+  // f(a) at the row's first visits, position class by position class
+  auto first_visits = [&](auto r, auto&& f) {
     const unsigned cr = cm >> row_class(r);
-    const char* q = rowptr(A.y64, ld64b, r);
-    sfor<NP>([&](auto a) { yr[r][a] = 0.0; });
-    if (cr & 1u) yr[r][0] = *(const double*)(q + x64[0]);
-    if (cr & 2u) sfor<NP - 2>([&](auto a) { yr[r][a + 1] = *(const double*)(q + x64[a + 1]); });
-    if (cr & 4u) yr[r][NP - 1] = *(const double*)(q + x64[NP - 1]);
+    if (cr & 1u) f(std::integral_constant<int, 0>{});
+    if (cr & 2u) sfor<NP - 2>([&](auto a) { f(std::integral_constant<int, a + 1>{}); });
+    if (cr & 4u) f(std::integral_constant<int, NP - 1>{});
   };
-  constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;
+  auto load_y = [&](auto r) {
+    const char* q = rowptr(y6, ld64b, r);
+    first_visits(r, [&](auto a) { yr[r][a] = *(const double*)(q + x64[a]); });
+  };
+  constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;   // rows ahead (4 and 2: 1 % slower)
   opaque(cm);
   if constexpr (STEP) sfor<kAhead>([&](auto r) { load_y(r); });
   if constexpr (!MASS) {
@@ -375,19 +409,16 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     });
   });
   // ---- assembly ----------------------------------------------------------
+  char* yw = planeptr(A.Y, ldyb);
   const double ly = STEP ? A.sa * A.lamY[nn] : 0.0;
   const T zz = STEP ? (T)A.szz : T(0);
   sfor<RB>([&](auto r) {
     if constexpr (STEP) {
       if constexpr (r + kAhead < RB) load_y(std::integral_constant<int, (r + kAhead < RB ? r + kAhead : 0)>{});
-      const unsigned cr = cm >> row_class(r);
-      sfor<NP>([&](auto a) {
-        const T upd = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly);
-        yo[r][a] = ((cr >> (a == 0 ? 0 : (a == NP - 1 ? 2 : 1))) & 1u) ? upd : yo[r][a];
-      });
+      first_visits(r, [&](auto a) { yo[r][a] = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly); });
     }
     if (pl && valid && (H == 1 || NPX == NP || RB * h + r < NP)) {
-      char* q = rowptr(A.Y, ldyb, r);
+      char* q = rowptr(yw, ldyb, r);
       sfor<NP>([&](auto a) { *(T*)(q + xo[a]) = yo[r][a] + (MASS ? f * acc[r][a] : acc[r][a]); });
     }
   });
@@ -422,13 +453,14 @@ bool wave_pays(const pawfe_op* op, int ncols) {
 template <typename T, int NP, int NQ, int MODE>
 void launch_wave(const CellArgs<T>& a, int ncells, T fx, T fy, T fz, hipStream_t s) {
   constexpr int CB = Wave<T, NP, NQ>::CB;
-  const int ncoltiles = (a.ncols + CB - 1) / CB;
+  constexpr int WT = kWaveTiles<MODE>;
+  const int ncoltiles = (a.ncols + CB * WT - 1) / (CB * WT);
   // one item per workgroup of one wave, XCD x takes the x-th eighth of the
   // items (workgroup w runs on XCD w % 8).  A resident set that strides over
   // the items was slower (degree-6 K + V of 1000 cells x 256 columns, FP32:
   // 0.39 against 0.30 ms)
   const int nitems = ncells * ncoltiles;
-  hipLaunchKernelGGL((k_cell_wave<T, NP, NQ, MODE>), dim3((unsigned)((nitems + 7) / 8) * 8), dim3(64), 0, s, a,
+  hipLaunchKernelGGL((k_cell_wave<T, NP, NQ, MODE>), dim3((unsigned)((nitems + 7) / 8) * 8), dim3(64 * WT), 0, s, a,
                      ncoltiles, nitems, fx, fy, fz);
 }
 
