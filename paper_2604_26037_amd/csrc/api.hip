@@ -115,11 +115,16 @@ pawfe_status do_apply(const pawfe_op* op, int which, const T* X, int64_t ldx, T*
     CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, false, b.part, s, bf3));
     CHECK(launch_atom_first(op, b.part, nullptr, which == 0 ? op->d.dH : op->d.dS, nullptr, nullptr, nullptr, ncols,
                             nullptr, b.d, nullptr, s));
-    if (op->natoms)
-      CHECK(launch_node_nl_init<T>(op, b.d, ncols, Y, ldy, s));
-    else
-      CHECK(launch_node_nl_init<T>(op, nullptr, ncols, Y, ldy, s));
-    return launch_cell<T>(op, which == 0 ? kModeH : kModeMass, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, bf3);
+    const int mode = which == 0 ? kModeH : kModeMass;
+    if constexpr (std::is_same<T, float>::value) {
+      if (bf3) {
+        CHECK(launch_node_nl_init(op, b.d, ncols, Y, ldy, s));
+        return launch_cell<T>(op, mode, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, true);
+      }
+    }
+    // the first visit of each DOF writes Y, so it needs no clearing before
+    CHECK(launch_cell<T>(op, mode, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, false, true));
+    return launch_node_fixup<T>(op, b.d, 1.0, ncols, Y, ldy, s);
   }
   // Sinv_hat
   CHECK(launch_nl_reduce<T>(op, X, ldx, ncols, true, b.part, s, bf3));
@@ -133,8 +138,8 @@ pawfe_status do_residual(const pawfe_op* op, const double* X, int64_t ldx, const
                          int ncols, const NlBufs& b, hipStream_t s) {
   CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, s));
   CHECK(launch_atom_first(op, b.part, nullptr, op->d.dH, op->d.dS, lam, nullptr, ncols, nullptr, b.d, nullptr, s));
-  CHECK(launch_node_nl_init<double>(op, op->natoms ? b.d : nullptr, ncols, Y, ldy, s));
-  return launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s);
+  CHECK(launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s, false, true));
+  return launch_node_fixup<double>(op, b.d, 1.0, ncols, Y, ldy, s);
 }
 
 // PAWFE_BF16X3: FP32 data, the cell contractions as bf16x3 split products

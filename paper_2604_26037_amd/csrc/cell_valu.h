@@ -596,10 +596,10 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     pk[j] = ((off_fits ? (unsigned)(a + Gx * (b + Gy * c)) : 0u) << kLdsBits) |
             (unsigned)((offU<T>(a, b, c) + col) * (int)sizeof(T));
   }
-  // step mode: the position class (0-26, 31 past the last node) of each of
-  // the thread's gathered nodes, 5 bits per node in one register
+  // the position class (0-26, 31 past the last node) of each of the thread's
+  // gathered nodes, 5 bits per node in one register (first visits)
   unsigned cls_pack = 0;
-  if constexpr (STEP) {
+  {
     static_assert(NJ * 5 <= 32, "position classes must fit one register");
     auto cls1 = [](int a) { return a == 0 ? 0 : (a == NP - 1 ? 2 : 1); };
 #pragma unroll
@@ -762,8 +762,18 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       int node[NJ];
       nodes_of(cp, node);
       const int nn = valid ? n : 0;
+      unsigned cm = 0;   // nodes the cell visits first, where those overwrite Y
+      if (!STEP && A.own) {
+        typedef const __attribute__((address_space(4))) unsigned* ConstUP;
+        cm = ((ConstUP)A.own)[cp.e];
+      }
+      unsigned cpk = cls_pack;
+      asm volatile("" : "+v"(cpk));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) yo[j] = *elem(A.Y, ldyb, nn, node[j]);
+      for (int j = 0; j < NJ; ++j) {
+        yo[j] = T(0);
+        if (STEP || !((cm >> ((cpk >> (5 * j)) & 31u)) & 1u)) yo[j] = *elem(A.Y, ldyb, nn, node[j]);
+      }
     }
     // step mode: which of the thread's nodes this cell visits first (the
     // cell of the lowest colour sharing a DOF), this item's gathered X (kept
@@ -1236,6 +1246,7 @@ pawfe_status launch_cell_gen_impl(const pawfe_op* op, int mode, const CellArgs<T
   if (mode == kModeMass || mode == kModeHRes) {
     CellArgs<T> m = c;
     m.lam = mode == kModeHRes ? a.lam : nullptr;
+    if (mode == kModeHRes) m.own = nullptr;   // added to the K + V just written
     return run_by_degree<T, kValuGenMass>(op, m, s);
   }
   return PAWFE_OK;

@@ -18,10 +18,10 @@
 //
 // Bound by the memory system and the vector ALU about equally (degree 6,
 // 1000 cells x 256 columns a launch): FP32 step 1.54e9 B of HBM traffic (1.03x
-// its algorithmic bytes) and 161,000 vector instructions per SIMD.  Per launch,
-// against the workgroup kernel: step FP32 0.538 -> 0.397 ms (3.9 TB/s), FP64
-// 0.988 -> 0.736; K + V FP32 0.436 -> 0.307, FP64 0.852 -> 0.603; mass FP32
-// 0.411 -> 0.299, FP64 0.798 -> 0.580.
+// its algorithmic bytes) and 146,000 vector instructions per SIMD.  Per launch,
+// against the workgroup kernel: step FP32 0.538 -> 0.393 ms (3.9 TB/s), FP64
+// 0.988 -> 0.718; K + V FP32 0.436 -> 0.298, FP64 0.852 -> 0.586; mass FP32
+// 0.411 -> 0.267, FP64 0.798 -> 0.504.
 //
 // Slab: element (line L, plane c, col) at (L NP + c) CB + col.  A plane
 // access (L fixed) is contiguous; a line access strides by NP CB elements,
@@ -277,11 +277,15 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       sfor<NP>([&](auto a) { acc[r][a] = o[a]; });
     });
   }
-  // step: the rows' part of the node update (-a c R_Y' at first visits)
+  // first visits of the lane's nodes, by their 9 (x, y) classes (none where
+  // the result is added to what Y holds)
   unsigned cm = 0;
-  if constexpr (STEP) {
+  if (STEP || A.own) {
     typedef const __attribute__((address_space(4))) unsigned* ConstUP;
-    cm = ((ConstUP)A.own)[e] >> (c == 0 ? 0 : (c == NP - 1 ? 18 : 9));   // the lane's 9 (x, y) classes
+    cm = ((ConstUP)A.own)[e] >> (c == 0 ? 0 : (c == NP - 1 ? 18 : 9));
+  }
+  // step: the rows' part of the node update (-a c R_Y' at first visits)
+  if constexpr (STEP) {
     const T mac = (T)(-A.sac);
     sfor<RB>([&](auto r) {
       // opaque: the products are formed here, not kept beside x from the load
@@ -363,14 +367,24 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     }
     wave_lds_order();
   }
-  // old rows and, of the step, the first FP64 residual rows: requested here,
-  // used after the last z pass
+  // old rows (except at a first visit that overwrites them) and, of the step,
+  // the first FP64 residual rows: requested here, used after the last z pass
+  opaque(cm);
   T yo[RB][NP];
   xoffs(ldyb, xo);
   const char* yp = planeptr((const T*)A.Y, ldyb);
   sfor<RB>([&](auto r) {
     const char* q = rowptr(yp, ldyb, r);
-    sfor<NP>([&](auto a) { yo[r][a] = *(const T*)(q + xo[a]); });
+    auto get = [&](auto a) { yo[r][a] = *(const T*)(q + xo[a]); };
+    if constexpr (STEP) {
+      sfor<NP>(get);
+    } else {
+      const unsigned cr = cm >> row_class(r);
+      sfor<NP>([&](auto a) { yo[r][a] = T(0); });
+      if (!(cr & 1u)) get(std::integral_constant<int, 0>{});
+      if (!(cr & 2u)) sfor<NP - 2>([&](auto a) { get(std::integral_constant<int, a + 1>{}); });
+      if (!(cr & 4u)) get(std::integral_constant<int, NP - 1>{});
+    }
   });
   uint64_t x64[STEP ? NP : 1];
   if constexpr (STEP) xoffs(ld64b, x64);
@@ -388,7 +402,6 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     first_visits(r, [&](auto a) { yr[r][a] = *(const double*)(q + x64[a]); });
   };
   constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;   // rows ahead (4 and 2: 1 % slower)
-  opaque(cm);
   if constexpr (STEP) sfor<kAhead>([&](auto r) { load_y(r); });
   if constexpr (!MASS) {
     sfor<ZK>([&](auto i) {

@@ -28,8 +28,10 @@ struct CellArgs {
   const T* vg;         // [E][3][nq^3] W_q det J (2/h_d) V_GGA,d (GGA term), or null
   T detJ;              // det J of every cell (residual mode of the vector-ALU kernel)
   T gk[3];             // complex operators: -k_d det J (2/h_d) (imaginary k term)
+  // [E] first-visit bits per local position class: step variants, and the
+  // others where the first visit of a DOF overwrites Y (null: all add to it)
+  const uint32_t* own;
   // Chebyshev step of the filter (vector-ALU step variants)
-  const uint32_t* own;   // [E] first-visit bits per local position class
   const double* y64;     // residual block Y (FP64), row stride ldy64
   int64_t ldy64;
   const double* lamY;    // per-column Lambda_Y
@@ -58,9 +60,10 @@ struct DensArgs {
 //                  s_n = -1 on real and +1 on imaginary columns
 //  bf3: (FP32 only) the cell contractions as bf16x3 split products on the
 //  bf16 matrix cores, FP32 accumulation.
+//  overwrite: Y = alpha * A_loc X instead, whatever Y held (not with bf3).
 template <typename T>
-pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy,
-                         int ncols, const double* lam, double alpha, hipStream_t s, bool bf3 = false);
+pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy, int ncols,
+                         const double* lam, double alpha, hipStream_t s, bool bf3 = false, bool overwrite = false);
 
 // bf16x3 split products on the matrix cores (kernels_cell_mfma.hip): K + V
 // (kModeH), the mass term (kModeMass) and the imaginary k term (kModeImg) of
@@ -138,9 +141,9 @@ template <typename T>
 pawfe_status launch_node_fixup(const pawfe_op* op, const double* v1, double s1, int ncols, T* out1, int64_t ld1,
                                hipStream_t s);
 
-// Y[I][n] = sum_{a: I in supp(a)} C^a[I] . q_a[n]   (0 outside the supports)
-template <typename T>
-pawfe_status launch_node_nl_init(const pawfe_op* op, const double* q, int ncols, T* Y, int64_t ldy,
+// Y[I][n] = sum_{a: I in supp(a)} C^a[I] . q_a[n]   (0 outside the supports):
+// what the bf16x3 cell kernel adds its term to
+pawfe_status launch_node_nl_init(const pawfe_op* op, const double* q, int ncols, float* Y, int64_t ldy,
                                  hipStream_t s);
 
 // Y = M_D^{-1} (X - sum_a C^a d_a)

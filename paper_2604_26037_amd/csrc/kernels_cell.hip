@@ -106,8 +106,9 @@ __global__ void __launch_bounds__(256) k_cell_density(DensArgs A, const Tab1D<do
 
 template <typename T>
 pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy,
-                         int ncols, const double* lam, double alpha, hipStream_t s, bool bf3) {
+                         int ncols, const double* lam, double alpha, hipStream_t s, bool bf3, bool overwrite) {
   if (ncols <= 0) return PAWFE_OK;
+  if (bf3 && overwrite) return fail(PAWFE_EUNSUPPORTED, "internal: the matrix-core cell kernel adds to Y");
   if (bf3 && sizeof(T) != 4) return fail(PAWFE_EINVAL, "bf16x3 needs FP32 data");
   CellArgs<T> a{};
   a.bf3 = bf3 ? 1 : 0;
@@ -123,6 +124,7 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   a.n0 = op->n[0];
   a.n1 = op->n[1];
   a.n2 = op->n[2];
+  a.own = overwrite ? op->d.cell_own : nullptr;
   if (op->general) {   // graded mesh / GGA term: every local term on the vector-ALU variants
     if (bf3) return fail(PAWFE_EUNSUPPORTED, "bf16x3 is not built for graded meshes or the GGA term");
     return launch_cell_gen<T>(op, mode, a, s);
@@ -132,6 +134,7 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   // K + V, the residual K + V - lambda M and the mass term in FP32 or FP64:
   // vector-ALU kernel (the matrix-core kernel keeps bf16x3)
   if ((mode == kModeH || mode == kModeHRes || mode == kModeMass) && !bf3) st = launch_cell_valu(op, mode, a, s, &done);
+  if (st == PAWFE_OK && !done && overwrite) return fail(PAWFE_EUNSUPPORTED, "internal: no cell variant that overwrites Y");
   if (st == PAWFE_OK && !done) st = launch_cell_mfma<T>(op, mode, a, s);
   if (done) return st;   // the vector-ALU variants include the imaginary k term
   // complex operators on the matrix cores: the imaginary local term, on the
@@ -141,9 +144,9 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
 }
 
 template pawfe_status launch_cell<double>(const pawfe_op*, int, const double*, int64_t, double*, int64_t,
-                                          int, const double*, double, hipStream_t, bool);
+                                          int, const double*, double, hipStream_t, bool, bool);
 template pawfe_status launch_cell<float>(const pawfe_op*, int, const float*, int64_t, float*, int64_t,
-                                         int, const double*, double, hipStream_t, bool);
+                                         int, const double*, double, hipStream_t, bool, bool);
 
 pawfe_status launch_density(const pawfe_op* op, const double* X, int64_t ldx, int ncols,
                             const double* occ, double* out, hipStream_t s) {

@@ -1041,22 +1041,22 @@ pawfe_status nl_fixup(const pawfe_op* op, int ncols, const double* v1, double s1
   return PAWFE_OK;
 }
 
-template <typename T>
-pawfe_status launch_node_nl_init(const pawfe_op* op, const double* q, int ncols, T* Y, int64_t ldy, hipStream_t s) {
+pawfe_status launch_node_nl_init(const pawfe_op* op, const double* q, int ncols, float* Y, int64_t ldy,
+                                 hipStream_t s) {
   if (ncols <= 0) return PAWFE_OK;
-  constexpr int V = 16 / sizeof(T);
+  constexpr int V = 4;
   if (vec_ok(V, ncols, {{Y, ldy}})) {
-    const RowGrid g = row_grid<k_node_zero<T, V, kRowsPerWave>>(op->M, ncols, V, kRowsPerWave);
-    hipLaunchKernelGGL((k_node_zero<T, V, kRowsPerWave>), g.grid, dim3(256), 0, s, op->M, ncols, g.ncoltiles, Y, ldy);
+    const RowGrid g = row_grid<k_node_zero<float, V, kRowsPerWave>>(op->M, ncols, V, kRowsPerWave);
+    hipLaunchKernelGGL((k_node_zero<float, V, kRowsPerWave>), g.grid, dim3(256), 0, s, op->M, ncols, g.ncoltiles, Y,
+                       ldy);
   } else {
-    const RowGrid g = row_grid<k_node_zero<T, 1, kRowsPerWave>>(op->M, ncols, 1, kRowsPerWave);
-    hipLaunchKernelGGL((k_node_zero<T, 1, kRowsPerWave>), g.grid, dim3(256), 0, s, op->M, ncols, g.ncoltiles, Y, ldy);
+    const RowGrid g = row_grid<k_node_zero<float, 1, kRowsPerWave>>(op->M, ncols, 1, kRowsPerWave);
+    hipLaunchKernelGGL((k_node_zero<float, 1, kRowsPerWave>), g.grid, dim3(256), 0, s, op->M, ncols, g.ncoltiles, Y,
+                       ldy);
   }
   PAWFE_HIP(hipGetLastError());
-  return nl_fixup<T, T, false, false>(op, ncols, q, 1.0, Y, ldy, nullptr, (T*)nullptr, 0, s);
+  return nl_fixup<float, float, false, false>(op, ncols, q, 1.0, Y, ldy, nullptr, (float*)nullptr, 0, s);
 }
-template pawfe_status launch_node_nl_init<double>(const pawfe_op*, const double*, int, double*, int64_t, hipStream_t);
-template pawfe_status launch_node_nl_init<float>(const pawfe_op*, const double*, int, float*, int64_t, hipStream_t);
 
 template <typename T>
 pawfe_status launch_node_fixup(const pawfe_op* op, const double* v1, double s1, int ncols, T* out1, int64_t ld1,

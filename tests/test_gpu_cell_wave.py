@@ -67,3 +67,25 @@ def test_local_terms(p, graded, prec):
         from oracle.chfsi import rchfsi_filter
         _close(host(out), rchfsi_filter(ref, x, ln, 2, b0, bW, bU), 1e-9)
     op.close()
+
+
+@pytest.mark.parametrize("graded", [False, True])
+@pytest.mark.parametrize("p", [2, 3, 6])
+@pytest.mark.parametrize("nc", [5, NC])
+def test_applies_overwrite(p, graded, nc):
+    """H X and S X into a buffer of NaN: the first visit of each DOF writes it
+    (few columns: the workgroup variants, many: the one-wave variants)."""
+    from oracle.paw import PAWOperator
+    from paper_2604_26037_amd import Operator
+    s = _system(p, graded)
+    ref, op = PAWOperator(s), Operator(s)
+    j = np.arange(nc) if nc < 10 else _sample()
+    jd = torch.from_numpy(j).cuda()
+    X = torch.randn(op.ndof, nc, device="cuda", dtype=torch.float64, generator=torch.Generator(device="cuda").manual_seed(p))
+    x = X[:, jd].cpu().numpy()
+    for apply, want in ((op.apply_H, ref.apply_H(x)), (op.apply_S, ref.apply_S(x))):
+        out = torch.full_like(X, float("nan"))
+        _close(apply(X, out=out)[:, jd].cpu().numpy(), want, 1e-12)
+        o32 = torch.full(X.shape, float("nan"), device="cuda", dtype=torch.float32)
+        _close(apply(X.float(), out=o32, prec="fp32")[:, jd].double().cpu().numpy(), want, 2e-5)
+    op.close()
