@@ -628,10 +628,6 @@ pawfe_status upload(pawfe_op* op, hipStream_t s) {
   }
   CHECK(up(op, &d.cell_pack, cpk, s));
   CHECK(up(op, &d.cell_own, op->cell_own, s));
-  CHECK(up(op, &d.node2srow, op->node2srow, s));
-  CHECK(up(op, &d.srow_ptr, op->srow_ptr, s));
-  CHECK(up(op, &d.srow_atom, op->srow_atom, s));
-  CHECK(up(op, &d.srow_coff, op->srow_coff, s));
   CHECK(up(op, &d.Cvals, op->Cvals, s));
   std::vector<float> cf = to_f32(op->Cvals);
   CHECK(up(op, &d.Cvals_f, cf, s));
@@ -643,7 +639,6 @@ pawfe_status upload(pawfe_op* op, hipStream_t s) {
     CHECK(up(op, &d.Gvals_im, op->Gvals_im, s));
     if (!op->dSinv_im.empty()) CHECK(up(op, &d.dSinv_im, op->dSinv_im, s));
   }
-  std::vector<int32_t> an(op->atom_nodes.begin(), op->atom_nodes.end());
   {
     // padded so that batched reads of consecutive rows never leave the list
     std::vector<int32_t> an(op->atom_nodes);
@@ -658,6 +653,10 @@ pawfe_status upload(pawfe_op* op, hipStream_t s) {
   CHECK(up(op, &d.fix_atom, op->fix_atom, s));
   CHECK(up(op, &d.fix_row0, op->fix_row0, s));
   CHECK(up(op, &d.fix_row1, op->fix_row1, s));
+  CHECK(up(op, &d.fixs_ptr, op->fixs_ptr, s));
+  CHECK(up(op, &d.fixs_nat, op->fixs_nat, s));
+  CHECK(up(op, &d.fixs_nrow, op->fixs_nrow, s));
+  CHECK(up(op, &d.fixs_data, op->fixs_data, s));
   CHECK(up(op, &d.atom_noff, op->atom_noff, s));
   CHECK(up(op, &d.atom_coff, op->atom_coff, s));
   CHECK(up(op, &d.nproj, op->nproj, s));

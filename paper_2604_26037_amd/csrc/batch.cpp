@@ -146,15 +146,15 @@ pawfe_status time_filter(const pawfe_filter_job& j, int32_t block, int32_t m, in
 
 // kernel launches of one filter of job j with the given block (an upper
 // bound: the step sequence of pawfe_cheb_filter, one launch per non-empty
-// cell colour and atom colour; complex operators add the imaginary-term cell
-// launches and the lambda duplication)
+// cell colour; complex operators add the imaginary-term cell launches and the
+// lambda duplication)
 int64_t est_launches(const pawfe_filter_job& J, int32_t block) {
   const pawfe_op* op = J.op;
-  int64_t nC = 0, nA = 0;
+  int64_t nC = 0;
   for (int c = 0; c < op->ncolour; ++c) nC += op->colour_off[c + 1] > op->colour_off[c];
-  for (int c = 0; c < op->natom_colours; ++c) nA += op->fix_colour_off[c + 1] > op->fix_colour_off[c];
   const int64_t cx = op->cplx ? 1 : 0, cell = nC * (1 + cx);
-  const int64_t residual = 4 + nA + cell, step = 6 + nA + cell, final = 4 + nA;
+  // projector kernels (reduction, atom blocks, add-back) and node kernels
+  const int64_t residual = 4 + cell * (op->general ? 2 : 1), step = 5 + cell, final = 4;
   const int64_t per_block = residual + cx + 1 + (int64_t)(J.degree - 1) * step + final;
   return per_block * ((J.nvec + block - 1) / block);
 }

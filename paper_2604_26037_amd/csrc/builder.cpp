@@ -591,27 +591,14 @@ pawfe_status build_host(const pawfe_op_desc* d, pawfe_op* op) {
     }
   }
 
-  // node-major support rows: every DOF in some support, with its (atom, C row) entries
+  // every DOF in some support, with its (atom, C row) entries
   std::vector<std::pair<int64_t, std::pair<int, int>>> ent;   // (dof, (atom, row)), sorted
   for (int a = 0; a < na; ++a)
     for (int64_t r = op->supp_node_off[a]; r < op->supp_node_off[a + 1]; ++r)
       ent.push_back({op->supp_nodes[r], {a, (int)(r - op->supp_node_off[a])}});
   std::sort(ent.begin(), ent.end());
-  op->nent = (int64_t)ent.size();
-  op->node2srow.assign(op->M, -1);
-  op->srow_ptr.assign(1, 0);
-  op->srow_atom.clear();
-  op->srow_coff.clear();
-  for (size_t x = 0; x < ent.size(); ++x) {
-    if (x > 0 && ent[x].first != ent[x - 1].first) op->srow_ptr.push_back((int32_t)x);
-    if (x == 0 || ent[x].first != ent[x - 1].first) op->node2srow[ent[x].first] = (int32_t)op->srow_ptr.size() - 1;
-    const int a = ent[x].second.first;
-    op->srow_atom.push_back(a);
-    op->srow_coff.push_back(op->atom_coff[a] + ent[x].second.second * op->nproj[a]);
-  }
-  if (!ent.empty()) op->srow_ptr.push_back((int32_t)ent.size());
-  op->nsrow = (int64_t)op->srow_ptr.size() - 1;
-
+  op->nsrow = 0;
+  for (size_t x = 0; x < ent.size(); ++x) op->nsrow += x == 0 || ent[x].first != ent[x - 1].first;
   // G^{ab} = C^a^H M_D^{-1} C^b over shared support nodes (imaginary part in
   // Gab_im for complex operators)
   std::map<std::pair<int, int>, std::vector<double>> Gab, Gab_im;
@@ -722,46 +709,74 @@ pawfe_status build_host(const pawfe_op_desc* d, pawfe_op* op) {
   op->nitems = (int)op->item_atom.size();
   op->item_rows_total = prow;
 
-  // greedy colouring of the atom overlap graph (atoms sharing a support node)
-  std::vector<std::vector<int>> nbr(na);
-  for (int64_t sr = 0; sr < op->nsrow; ++sr)
-    for (int32_t k = op->srow_ptr[sr]; k < op->srow_ptr[sr + 1]; ++k)
-      for (int32_t k2 = k + 1; k2 < op->srow_ptr[sr + 1]; ++k2) {
-        nbr[op->srow_atom[k]].push_back(op->srow_atom[k2]);
-        nbr[op->srow_atom[k2]].push_back(op->srow_atom[k]);
-      }
-  std::vector<int> acol(na, -1);
-  int ncol = 0;
-  for (int a = 0; a < na; ++a) {
-    std::vector<char> used(ncol + 1, 0);
-    for (int b : nbr[a])
-      if (acol[b] >= 0) used[acol[b]] = 1;
-    int c = 0;
-    while (used[c]) ++c;
-    acol[a] = c;
-    ncol = std::max(ncol, c + 1);
-  }
-  op->natom_colours = ncol;
-  const int kFixRows = 16;   // rows per add-back work item
-  op->fix_atom.clear();
-  op->fix_row0.clear();
-  op->fix_row1.clear();
-  op->fix_colour_off.assign(1, 0);
-  for (int c = 0; c < ncol; ++c) {
-    for (int a = 0; a < na; ++a) {
-      if (acol[a] != c) continue;
-      const int64_t nrow = op->supp_node_off[a + 1] - op->supp_node_off[a];
-      for (int64_t r0 = 0; r0 < nrow; r0 += kFixRows) {
-        op->fix_atom.push_back(a);
-        op->fix_row0.push_back((int32_t)r0);
-        op->fix_row1.push_back((int32_t)std::min<int64_t>(nrow, r0 + kFixRows));
-      }
-    }
-    op->fix_colour_off.push_back((int32_t)op->fix_atom.size());
-  }
+  // add-back work: every support row is written by one item, so one launch
+  // serves all atoms.  Rows of one atom alone come first in the atom's device
+  // list (contiguous rows of C^a), in items of kFixRows; rows shared by several
+  // atoms are grouped by their set of atoms, in items of kFixShared rows.
   op->atom_noff.assign(na + 1, 0);
   for (int a = 0; a <= na; ++a) op->atom_noff[a] = (int32_t)op->supp_node_off[a];
   op->atom_nodes.assign(op->supp_nodes.begin(), op->supp_nodes.end());
+  std::vector<int> shared(op->supp_nodes.size(), 0);       // 1: another atom has the row too
+  std::map<std::vector<int>, std::vector<size_t>> sets;    // atoms -> first entries of their rows
+  for (size_t x0 = 0, x1; x0 < ent.size(); x0 = x1) {
+    for (x1 = x0; x1 < ent.size() && ent[x1].first == ent[x0].first;) ++x1;
+    if (x1 - x0 < 2) continue;
+    std::vector<int> key;
+    for (size_t x = x0; x < x1; ++x) {
+      key.push_back(ent[x].second.first);
+      shared[op->supp_node_off[key.back()] + ent[x].second.second] = 1;
+    }
+    sets[key].push_back(x0);
+  }
+  const int kFixRows = 16;
+  std::vector<int32_t> newrow(op->supp_nodes.size());      // row of the device list, per row of supp_nodes
+  op->fix_atom.clear();
+  op->fix_row0.clear();
+  op->fix_row1.clear();
+  std::vector<double> tmp;
+  for (int a = 0; a < na; ++a) {
+    const int64_t r0 = op->supp_node_off[a], nrow = op->supp_node_off[a + 1] - r0;
+    int32_t next = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int64_t r = 0; r < nrow; ++r)
+        if (shared[r0 + r] == pass) newrow[r0 + r] = next++;
+      if (pass == 0)
+        for (int32_t q = 0; q < next; q += kFixRows) {
+          op->fix_atom.push_back(a);
+          op->fix_row0.push_back(q);
+          op->fix_row1.push_back(std::min(next, q + kFixRows));
+        }
+    }
+    const int npj = op->nproj[a];
+    for (int64_t r = 0; r < nrow; ++r) op->atom_nodes[r0 + newrow[r0 + r]] = (int32_t)op->supp_nodes[r0 + r];
+    for (int part = 0; part < (op->cplx ? 2 : 1); ++part) {
+      double* C = (part ? op->Cvals_im.data() : op->Cvals.data()) + op->atom_coff[a];
+      tmp.assign(C, C + nrow * npj);
+      for (int64_t r = 0; r < nrow; ++r)
+        std::copy(&tmp[r * npj], &tmp[r * npj] + npj, C + (int64_t)newrow[r0 + r] * npj);
+    }
+  }
+  op->fixs_ptr.assign(1, 0);
+  op->fixs_nat.clear();
+  op->fixs_nrow.clear();
+  op->fixs_data.clear();
+  for (const auto& kv : sets)
+    for (size_t q = 0; q < kv.second.size(); q += kFixShared) {
+      const int n = (int)std::min<size_t>(kFixShared, kv.second.size() - q);
+      op->fixs_nat.push_back((int32_t)kv.first.size());
+      op->fixs_nrow.push_back(n);
+      // rows past the last repeat it (read, not written)
+      auto first = [&](int u) { return kv.second[q + std::min(u, n - 1)]; };
+      for (int u = 0; u < kFixShared; ++u) op->fixs_data.push_back((int32_t)ent[first(u)].first);
+      for (size_t k = 0; k < kv.first.size(); ++k) {
+        const int a = kv.first[k];
+        op->fixs_data.push_back(a);
+        for (int u = 0; u < kFixShared; ++u)
+          op->fixs_data.push_back(op->atom_coff[a] +
+                                  newrow[op->supp_node_off[a] + ent[first(u) + k].second.second] * op->nproj[a]);
+      }
+      op->fixs_ptr.push_back((int32_t)op->fixs_data.size());
+    }
   return PAWFE_OK;
 }
 

@@ -14,6 +14,7 @@ namespace pawfe {
 constexpr int kNpMax = 7;    // degree <= 6
 constexpr int kNqMax = 8;    // Gauss points per direction
 constexpr int kNpjMax = 32;  // projectors per atom
+constexpr int kFixShared = 8;  // rows of an add-back item of rows shared by several atoms
 constexpr int kMaxConcBlocks = 4;   // column blocks of a filter in flight at once
 
 // Error helper: records the message for pawfe_last_error and returns the code.
@@ -57,11 +58,7 @@ struct DeviceTables {
   int32_t* cell_pack = nullptr;        // [E] the same cells as i | j << 10 | k << 20
   uint32_t* cell_own = nullptr;        // [E] bit ca + 3 cb + 9 cc: the cell visits those nodes first
   // projector structure
-  int32_t* node2srow = nullptr;   // [M]  support row of a DOF, -1 if none
-  int32_t* srow_ptr = nullptr;    // [nsrow+1]
-  int32_t* srow_atom = nullptr;   // [nent]
-  int32_t* srow_coff = nullptr;   // [nent] offset of the C row in Cvals
-  double* Cvals = nullptr;        // atom-major rows of C^a on support nodes
+  double* Cvals = nullptr;        // atom-major rows of C^a on support nodes (rows of this atom alone first)
   float* Cvals_f = nullptr;
   double* Cvals_im = nullptr;     // imaginary parts (complex operators; else null)
   float* Cvals_im_f = nullptr;
@@ -71,9 +68,15 @@ struct DeviceTables {
   int32_t* item_row1 = nullptr;
   int32_t* item_poff = nullptr;   // offset of the item's partial block (in units of ncols)
   int32_t* item_ptr = nullptr;    // [natoms+1] items of each atom
-  int32_t* fix_atom = nullptr;    // add-back work items (atom, row range), ordered by atom colour
+  int32_t* fix_atom = nullptr;    // add-back work items on rows of one atom (atom, row range)
   int32_t* fix_row0 = nullptr;
   int32_t* fix_row1 = nullptr;
+  // add-back items on rows that several atoms share: at fixs_data + fixs_ptr,
+  // kFixShared nodes, then per atom its index and kFixShared offsets into Cvals
+  int32_t* fixs_ptr = nullptr;
+  int32_t* fixs_nat = nullptr;
+  int32_t* fixs_nrow = nullptr;
+  int32_t* fixs_data = nullptr;
   int32_t* atom_noff = nullptr;   // [natoms+1] offsets into atom_nodes
   int32_t* atom_coff = nullptr;   // [natoms]   offsets into Cvals
   int32_t* nproj = nullptr;       // [natoms]
@@ -145,14 +148,10 @@ struct pawfe_op {
   std::vector<double> dH, dS, dSinv, dSinv_im;   // dSinv_im: complex operators, exact G
   std::vector<int32_t> gq_ptr, gq_row, gq_off;
   std::vector<double> Gvals, Gvals_im;
-  int64_t nsrow = 0, nent = 0;
-  std::vector<int32_t> node2srow, srow_ptr, srow_atom, srow_coff;
   std::vector<int32_t> item_atom, item_row0, item_row1, item_poff, item_ptr, atom_noff, atom_nodes;
   int nitems = 0;
-  // atoms coloured so that atoms of one colour share no support node; the
-  // add-back of C^a q_a runs one colour at a time without write conflicts
-  int natom_colours = 0;
-  std::vector<int32_t> fix_atom, fix_row0, fix_row1, fix_colour_off;
+  int64_t nsrow = 0;   // DOFs in some support
+  std::vector<int32_t> fix_atom, fix_row0, fix_row1, fixs_ptr, fixs_nat, fixs_nrow, fixs_data;   // add-back items
   int64_t item_rows_total = 0;         // sum over items of nproj (partial rows per column)
   int sinv_mode;
   pawfe::DeviceTables d;

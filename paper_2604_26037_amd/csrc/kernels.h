@@ -136,7 +136,7 @@ pawfe_status launch_atom_second(const pawfe_op* op, const double* c, const doubl
                                 const double* lamY, const double* lam_in, double a, double ac, double zz, int ncols,
                                 hipStream_t s);
 
-// out1 += s1 C v1 on the support rows (atom colour by colour)
+// out1 += s1 C v1 on the support rows
 template <typename T>
 pawfe_status launch_node_fixup(const pawfe_op* op, const double* v1, double s1, int ncols, T* out1, int64_t ld1,
                                hipStream_t s);

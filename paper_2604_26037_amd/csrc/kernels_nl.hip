@@ -10,8 +10,8 @@
 // a second kernel adds the chunks of each atom in a fixed order (no atomics,
 // deterministic).  The atom-block products (Delta x c, G^{ab} corrections)
 // are small and run in two launches (k_atom_first, k_atom_second).  The add-back
-// sum_a C^a q_a on the support rows is a separate pass per atom colour
-// (k_nl_fixup) after the node-wise kernels that stream the rows.
+// sum_a C^a q_a on the support rows is a pass of its own (k_nl_fixup) before or
+// after the kernels that stream all rows.
 
 #include <cstdint>
 #include <initializer_list>
@@ -539,7 +539,7 @@ __device__ __forceinline__ void vst(T* p, const Lanes<T, V>& r) {
 
 // Streaming parts of the node-wise operations (local terms only); the
 // projector terms sum_a C^a v_a at the support nodes are added afterwards by
-// k_nl_fixup, atom colour by atom colour.
+// k_nl_fixup.
 
 template <typename T, int V, int R>
 __global__ void __launch_bounds__(256) k_node_zero(int64_t M, int ncols, int ncoltiles, T* __restrict__ Y,
@@ -654,42 +654,46 @@ __global__ void __launch_bounds__(256) k_node_finalize(int64_t M, int ncols, int
   ROWS_END
 }
 
-// Projector add-back on the support nodes, for the items of one atom colour
-// (atoms of a colour share no node, so the read-modify-writes never meet):
-//   out1[I] += s1 * w_I * sum_alpha C^a[I][alpha] v1_a[alpha][n]
-//   out2[I] +=              sum_alpha C^a[I][alpha] v2_a[alpha][n]   (if out2)
-// with w_I = M_D^{-1}[I] if minv, else 1.  One workgroup per (item, 256
-// columns): thread <-> column, the atom's coefficient vectors for that column
-// sit in registers, the item's rows (<= 64) are walked kFixUnroll at a time
-// with all loads issued first.
+// Projector add-back on the support nodes:
+//   out1[I] += s1 * w_I * sum_a sum_alpha C^a[I][alpha] v1_a[alpha][n]
+//   out2[I] +=            sum_a sum_alpha C^a[I][alpha] v2_a[alpha][n]   (if out2)
+// with w_I = M_D^{-1}[I] if minv, else 1.  Every row is written by one item, so
+// all atoms go in one launch: workgroups [0, nshared) take the rows shared by
+// several atoms (items of up to kFixShared rows with the same atoms), the rest
+// the rows of one atom alone (items of up to 16 consecutive rows of C^a).
+// Thread <-> column: an atom's coefficient vector for that column sits in
+// registers and serves all rows of the item, kFixUnroll rows at a time with
+// all loads issued first.  Bound by the read-modify-write of scattered rows;
+// one launch per atom colour (atoms of a colour share no row) waited out the
+// latency chain of its items six to eight times (128 atoms x 256 columns FP32
+// 471 -> 354 us, FP64 670 us both ways, 3.6 TB/s; 18 atoms x 200 columns FP32
+// 106 -> 55; 12 atoms x 101 columns 67 -> 17).  Held to as many waves as the
+// lean per-atom walk alone would have.
 constexpr int kFixUnroll = 8;
+static_assert(kFixUnroll == kFixShared, "rows in flight of a shared item");
 
 // CPLX (complex operators): (re, im) column pairs, C v mixes them:
 // + s Ci v[n ^ 1], s = -1 on real and +1 on imaginary columns (partner value
 // from the neighbouring lane).
-template <typename TR, typename TO1, int NPJ, bool MINV, bool HAS2, bool CPLX = false>
-__global__ void __launch_bounds__(256) k_nl_fixup(const int32_t* __restrict__ fatom,
-                                                  const int32_t* __restrict__ frow0,
-                                                  const int32_t* __restrict__ frow1, int ncols,
-                                                  const double* __restrict__ v1, double s1,
+template <typename TR, typename TO1, int NPJ, bool MINV, bool HAS2, bool CPLX>
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu((NPJ <= 18 && !HAS2 && !CPLX) ? (sizeof(TR) == 4 ? 7 : 6) : 1)))
+k_nl_fixup(int nshared, int ncols, const double* __restrict__ v1, double s1,
                                                   TO1* __restrict__ out1, int64_t ld1,
                                                   const double* __restrict__ v2, TR* __restrict__ out2,
                                                   int64_t ld2, const TR* __restrict__ Minv,
                                                   const TR* __restrict__ Cv, DeviceTables d,
-                                                  const TR* __restrict__ Cvi = nullptr) {
+                                                  const TR* __restrict__ Cvi) {
   const int n = blockIdx.y * 256 + threadIdx.x;
   if (n >= ncols) return;
-  const int a = fatom[blockIdx.x];
-  const int r0 = frow0[blockIdx.x], r1 = frow1[blockIdx.x];
-  const int npj = d.nproj[a], po = d.poff[a];
-  const int noff = d.atom_noff[a], coff = d.atom_coff[a];
   // All loads are unconditional (indices clamped into range), so they are in
   // flight together; an atom with exactly NPJ projectors takes the path with
   // plain indices (wide scalar loads of its C rows).
-  auto body = [&](auto full) {
+  TR w1[NPJ], w2[HAS2 ? NPJ : 1], p1[CPLX ? NPJ : 1], p2[CPLX && HAS2 ? NPJ : 1];
+  // the coefficients of one atom for this column
+  auto coeffs = [&](auto full, int po, int npj) {
     constexpr bool FULL = decltype(full)::value;
     auto idx = [&](int al) { return FULL ? al : (al < npj ? al : npj - 1); };
-    TR w1[NPJ], w2[NPJ], p1[CPLX ? NPJ : 1], p2[CPLX ? NPJ : 1];
 #pragma unroll
     for (int al = 0; al < NPJ; ++al) {
       const double x1 = v1[(int64_t)(po + idx(al)) * ncols + n];
@@ -707,51 +711,86 @@ __global__ void __launch_bounds__(256) k_nl_fixup(const int32_t* __restrict__ fa
         if constexpr (HAS2) p2[al] = sg * __shfl_xor(w2[al], 1);
       }
     }
+  };
+  // c1 += C row . v1 (c2 += C row . v2), the row at offset r of Cv
+  auto dot = [&](auto full, int64_t r, int npj, TR& c1, TR& c2) {
+    constexpr bool FULL = decltype(full)::value;
+    auto idx = [&](int al) { return FULL ? al : (al < npj ? al : npj - 1); };
+    const TR* cr = Cv + r;
+#pragma unroll
+    for (int al = 0; al < NPJ; ++al) {
+      const TR cv = cr[idx(al)];
+      c1 += cv * w1[al];
+      if constexpr (HAS2) c2 += cv * w2[al];
+    }
+    if constexpr (CPLX) {
+      const TR* ci = Cvi + r;
+#pragma unroll
+      for (int al = 0; al < NPJ; ++al) {
+        const TR cv = ci[idx(al)];
+        c1 += cv * p1[al];
+        if constexpr (HAS2) c2 += cv * p2[al];
+      }
+    }
+  };
+  TO1 o1[kFixUnroll];
+  TR o2[kFixUnroll], c1[kFixUnroll], c2[kFixUnroll];
+  auto load_rows = [&](const int (&I)[kFixUnroll]) {
+#pragma unroll
+    for (int u = 0; u < kFixUnroll; ++u) {   // rows touched once: non-temporal
+      o1[u] = __builtin_nontemporal_load(out1 + (int64_t)I[u] * ld1 + n);
+      if constexpr (HAS2) o2[u] = __builtin_nontemporal_load(out2 + (int64_t)I[u] * ld2 + n);
+      c1[u] = c2[u] = TR(0);
+    }
+  };
+  auto store_rows = [&](const int (&I)[kFixUnroll], int nrow) {
+#pragma unroll
+    for (int u = 0; u < kFixUnroll; ++u) {
+      if (u >= nrow) break;
+      if constexpr (MINV) c1[u] *= Minv[I[u]];
+      __builtin_nontemporal_store(o1[u] + (TO1)c1[u], out1 + (int64_t)I[u] * ld1 + n);
+      if constexpr (HAS2) __builtin_nontemporal_store(o2[u] + c2[u], out2 + (int64_t)I[u] * ld2 + n);
+    }
+  };
+  int I[kFixUnroll];
+  if ((int)blockIdx.x < nshared) {
+    const int32_t* it = d.fixs_data + d.fixs_ptr[blockIdx.x];
+    const int nat = d.fixs_nat[blockIdx.x];
+#pragma unroll
+    for (int u = 0; u < kFixUnroll; ++u) I[u] = it[u];
+    load_rows(I);
+    for (int k = 0; k < nat; ++k) {
+      const int32_t* e = it + kFixShared + k * (kFixShared + 1);
+      const int a = e[0], npj = d.nproj[a];
+      auto body = [&](auto full) {
+        coeffs(full, d.poff[a], npj);
+#pragma unroll
+        for (int u = 0; u < kFixUnroll; ++u) dot(full, e[1 + u], npj, c1[u], c2[u]);
+      };
+      if (npj == NPJ) body(std::true_type{}); else body(std::false_type{});
+    }
+    store_rows(I, d.fixs_nrow[blockIdx.x]);
+    return;
+  }
+  const int item = blockIdx.x - nshared;
+  const int a = d.fix_atom[item];
+  const int r0 = d.fix_row0[item], r1 = d.fix_row1[item];
+  const int npj = d.nproj[a], noff = d.atom_noff[a];
+  const int64_t coff = d.atom_coff[a];
+  auto body = [&](auto full) {
+    coeffs(full, d.poff[a], npj);
     for (int rb = r0; rb < r1; rb += kFixUnroll) {
-      int I[kFixUnroll];
-      TO1 o1[kFixUnroll];
-      TR o2[kFixUnroll], c1[kFixUnroll], c2[kFixUnroll];
 #pragma unroll
       for (int u = 0; u < kFixUnroll; ++u) I[u] = d.atom_nodes[noff + rb + u];   // list padded
+      load_rows(I);
 #pragma unroll
-      for (int u = 0; u < kFixUnroll; ++u) {   // rows touched once: non-temporal
-        o1[u] = __builtin_nontemporal_load(out1 + (int64_t)I[u] * ld1 + n);
-        if constexpr (HAS2) o2[u] = __builtin_nontemporal_load(out2 + (int64_t)I[u] * ld2 + n);
-      }
-#pragma unroll
-      for (int u = 0; u < kFixUnroll; ++u) {
-        const int r = rb + u < r1 ? rb + u : r1 - 1;
-        const TR* cr = Cv + coff + (int64_t)r * npj;
-        c1[u] = c2[u] = TR(0);
-#pragma unroll
-        for (int al = 0; al < NPJ; ++al) {
-          const TR cv = cr[idx(al)];
-          c1[u] += cv * w1[al];
-          if constexpr (HAS2) c2[u] += cv * w2[al];
-        }
-        if constexpr (CPLX) {
-          const TR* ci = Cvi + coff + (int64_t)r * npj;
-#pragma unroll
-          for (int al = 0; al < NPJ; ++al) {
-            const TR cv = ci[idx(al)];
-            c1[u] += cv * p1[al];
-            if constexpr (HAS2) c2[u] += cv * p2[al];
-          }
-        }
-        if constexpr (MINV) c1[u] *= Minv[I[u]];
-      }
-#pragma unroll
-      for (int u = 0; u < kFixUnroll; ++u) {
-        if (rb + u >= r1) break;
-        __builtin_nontemporal_store(o1[u] + (TO1)c1[u], out1 + (int64_t)I[u] * ld1 + n);
-        if constexpr (HAS2) __builtin_nontemporal_store(o2[u] + c2[u], out2 + (int64_t)I[u] * ld2 + n);
-      }
+      for (int u = 0; u < kFixUnroll; ++u)
+        dot(full, coff + (int64_t)(rb + u < r1 ? rb + u : r1 - 1) * npj, npj, c1[u], c2[u]);
+      store_rows(I, r1 - rb);
     }
   };
   if (npj == NPJ) body(std::true_type{}); else body(std::false_type{});
 }
-
-
 
 template <typename TR, int V, int R>
 __global__ void __launch_bounds__(256) k_cheb_init(int64_t M, int ncols, int ncoltiles,
@@ -1010,7 +1049,7 @@ pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t 
   return PAWFE_OK;
 }
 
-// out1 += s1 w C v1 (w = M_D^{-1} if MINV), out2 += C v2 (if HAS2), atom colour by colour
+// out1 += s1 w C v1 (w = M_D^{-1} if MINV), out2 += C v2 (if HAS2)
 template <typename TR, typename TO1, bool MINV, bool HAS2>
 pawfe_status nl_fixup(const pawfe_op* op, int ncols, const double* v1, double s1, TO1* out1, int64_t ld1,
                       const double* v2, TR* out2, int64_t ld2, hipStream_t s) {
@@ -1018,25 +1057,21 @@ pawfe_status nl_fixup(const pawfe_op* op, int ncols, const double* v1, double s1
   const TR* Cv = pick<TR>(op->d.Cvals, op->d.Cvals_f);
   const TR* Cvi = pick<TR>(op->d.Cvals_im, op->d.Cvals_im_f);
   const TR* Minv = pick<TR>(op->d.Minv, op->d.Minv_f);
-  for (int c = 0; c < op->natom_colours; ++c) {
-    const int i0 = op->fix_colour_off[c], i1 = op->fix_colour_off[c + 1];
-    if (i1 == i0) continue;
-    const dim3 grid(i1 - i0, (ncols + 255) / 256), block(256);
-    const int32_t *fa = op->d.fix_atom + i0, *f0 = op->d.fix_row0 + i0, *f1 = op->d.fix_row1 + i0;
-    auto go = [&](auto cplx) {
-      constexpr bool CX = decltype(cplx)::value;
-      if (op->npj_max <= 8)
-        hipLaunchKernelGGL((k_nl_fixup<TR, TO1, 8, MINV, HAS2, CX>), grid, block, 0, s, fa, f0, f1, ncols, v1, s1,
-                           out1, ld1, v2, out2, ld2, Minv, Cv, op->d, Cvi);
-      else if (op->npj_max <= 18)
-        hipLaunchKernelGGL((k_nl_fixup<TR, TO1, 18, MINV, HAS2, CX>), grid, block, 0, s, fa, f0, f1, ncols, v1, s1,
-                           out1, ld1, v2, out2, ld2, Minv, Cv, op->d, Cvi);
-      else
-        hipLaunchKernelGGL((k_nl_fixup<TR, TO1, 32, MINV, HAS2, CX>), grid, block, 0, s, fa, f0, f1, ncols, v1, s1,
-                           out1, ld1, v2, out2, ld2, Minv, Cv, op->d, Cvi);
-    };
-    if (op->cplx) go(std::true_type{}); else go(std::false_type{});
-  }
+  const int nshared = (int)op->fixs_nat.size(), nitems = nshared + (int)op->fix_atom.size();
+  if (nitems == 0) return PAWFE_OK;
+  const dim3 grid(nitems, (ncols + 255) / 256), block(256);
+  auto go = [&](auto npj, auto cplx) {
+    constexpr int NPJ = decltype(npj)::value;
+    constexpr bool CX = decltype(cplx)::value;
+    hipLaunchKernelGGL((k_nl_fixup<TR, TO1, NPJ, MINV, HAS2, CX>), grid, block, 0, s, nshared, ncols, v1, s1, out1, ld1,
+                       v2, out2, ld2, Minv, Cv, op->d, Cvi);
+  };
+  auto by_npj = [&](auto cplx) {
+    if (op->npj_max <= 8) go(std::integral_constant<int, 8>{}, cplx);
+    else if (op->npj_max <= 18) go(std::integral_constant<int, 18>{}, cplx);
+    else go(std::integral_constant<int, 32>{}, cplx);
+  };
+  if (op->cplx) by_npj(std::true_type{}); else by_npj(std::false_type{});
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }

@@ -37,3 +37,24 @@ def test_reduce_split(channels, cplx):
             got = op.apply_Sinv(x, prec=prec)[:, jd].to(X.dtype).cpu().numpy()
             assert np.max(np.abs(got - want).max(axis=0) / scale) <= tol, (nc, prec)
     op.close()
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("natoms", [1, 2, 5])
+def test_add_back_shared_rows(natoms, cplx):
+    """The one-launch add-back: support rows of one atom alone and rows that
+    up to five overlapping atoms share, H, S and Sinv_hat against the oracle."""
+    from oracle.paw import PAWOperator
+    from paper_2604_26037_amd import Operator
+    from workloads.configs import custom_system
+    pos = np.array([[0.3, 0.2, 0.4], [1.0, 0.8, 0.9], [4.9, 0.1, 0.6], [0.5, 5.5, 1.1], [3.0, 3.1, 2.0]])[:natoms]
+    kw = dict(kpoint=(0.3, -0.2, 0.45), is_complex=True) if cplx else {}
+    s = custom_system((3, 4, 3), (5.4, 6.4, 4.8), 4, 6, pos=pos, rcut=0.9, channels="spd8", wells=pos, s_H=0.5, s_S=0.1,
+                      seed=5, **kw)
+    ref, op = PAWOperator(s), Operator(s)
+    X = torch.randn(op.ndof, 19, device="cuda", dtype=torch.complex128 if cplx else torch.float64,
+                    generator=torch.Generator(device="cuda").manual_seed(natoms))
+    x = X.cpu().numpy()
+    for got, want in ((op.apply_H(X), ref.apply_H(x)), (op.apply_S(X), ref.apply_S(x)), (op.apply_Sinv(X), ref.apply_Sinv(x))):
+        assert np.max(np.abs(got.cpu().numpy() - want).max(axis=0) / np.abs(want).max(axis=0)) <= 1e-12
+    op.close()
