@@ -19,8 +19,8 @@
 // Bound by the memory system and the vector ALU about equally (degree 6,
 // 1000 cells x 256 columns a launch): FP32 step 1.54e9 B of HBM traffic (1.03x
 // its algorithmic bytes) and 146,000 vector instructions per SIMD.  Per launch,
-// against the workgroup kernel: step FP32 0.538 -> 0.393 ms (3.9 TB/s), FP64
-// 0.988 -> 0.718; K + V FP32 0.436 -> 0.298, FP64 0.852 -> 0.586; mass FP32
+// against the workgroup kernel: step FP32 0.538 -> 0.387 ms (4.0 TB/s), FP64
+// 0.988 -> 0.720; K + V FP32 0.436 -> 0.298, FP64 0.852 -> 0.586; mass FP32
 // 0.411 -> 0.267, FP64 0.798 -> 0.504.
 //
 // Slab: element (line L, plane c, col) at (L NP + c) CB + col.  A plane
@@ -422,19 +422,26 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     });
   });
   // ---- assembly ----------------------------------------------------------
-  char* yw = planeptr(A.Y, ldyb);
   const double ly = STEP ? A.sa * A.lamY[nn] : 0.0;
   const T zz = STEP ? (T)A.szz : T(0);
+  // every load before the first store: a load waits for the stores issued
+  // before it (one counter, in order), which cost the step a round trip per row
   sfor<RB>([&](auto r) {
     if constexpr (STEP) {
       if constexpr (r + kAhead < RB) load_y(std::integral_constant<int, (r + kAhead < RB ? r + kAhead : 0)>{});
       first_visits(r, [&](auto a) { yo[r][a] = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly); });
     }
-    if (pl && valid && (H == 1 || NPX == NP || RB * h + r < NP)) {
-      char* q = rowptr(yw, ldyb, r);
-      sfor<NP>([&](auto a) { *(T*)(q + xo[a]) = yo[r][a] + (MASS ? f * acc[r][a] : acc[r][a]); });
-    }
+    sfor<NP>([&](auto a) { yo[r][a] += MASS ? f * acc[r][a] : acc[r][a]; });
   });
+  if (pl && valid) {
+    char* yw = planeptr(A.Y, ldyb);
+    sfor<RB>([&](auto r) {
+      if (H == 1 || NPX == NP || RB * h + r < NP) {
+        char* q = rowptr(yw, ldyb, r);
+        sfor<NP>([&](auto a) { *(T*)(q + xo[a]) = yo[r][a]; });
+      }
+    });
+  }
 }
 
 namespace {
