@@ -14,94 +14,96 @@
 // every cell (the dE/dV of the governing equations), with the columns
 // interpolated to the points by the same three 1-D sweeps as the V term.
 
-#include "kernels.h"
+#include "cell_valu.h"
 
 namespace pawfe {
 
-// Band-energy density: dE/dV[e][q] = W_q sum_n occ_n |u_n(x_q)|^2 for one
-// cell per workgroup, looping over all column tiles so every output is
-// written once (no cell-local state kept across cell batches).
-template <int NP, int NQ, int CB>
-__global__ void __launch_bounds__(256) k_cell_density(DensArgs A, const Tab1D<double>* __restrict__ tabp) {
-  const Tab1D<double>& tab = *tabp;
-  constexpr int NL = NP * NP * NP;
-  constexpr int NLG = 256 / CB;
-  constexpr int NQ3 = NQ * NQ * NQ;
-  __shared__ double U[NL * CB];
-  __shared__ double Q1[NP * NP * NQ * CB];
-  __shared__ double Q2[NP * NQ * NQ * CB];
-  __shared__ double acc[NQ3];
-  const int tid = threadIdx.x, col = tid % CB, lg = tid / CB;
+// Band-energy density: dE/dV[e][q] = W_q sum_n occ_n |u_n(x_q)|^2, one
+// workgroup per cell whose four waves share the column tiles.  A wave takes a
+// tile as the cell operator does (cell_wave.h): planes interpolated in x and y
+// in registers, z lines through its own LDS slab; the sum over its tiles stays
+// in registers (every output has one lane per column of a tile), so the tiles
+// need no barrier, and the waves add up in LDS once at the end.  Bound by the
+// vector ALU and the latency of the gathers: 1728 cells of degree 6 x 256
+// columns 0.32 ms; a workgroup per tile with a barrier per pass and two
+// shuffles per point and tile took 1.80 ms.
+template <int NP, int NQ>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) k_cell_density(DensArgs A) {
+  using W = Wave<double, NP, NQ>;
+  constexpr int H = W::H, CB = W::CB, G = W::G, RB = W::RB, QB = W::QB, NQX = W::NQX;
+  constexpr int NQ2 = NQ * NQ, NQ3 = NQ2 * NQ, LS = NP * CB, ZR = (NQ2 + G - 1) / G;
+  static_assert(W::slab >= NQ3, "the slab holds a wave's sums at the end");
+  __shared__ double slabs[4][W::slab];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* const sl = slabs[wave];
+  const int col = lane % CB, slot = (lane / CB) % W::PS, g = lane / CB;
+  const int h = H == 2 ? lane >> 5 : 0;
+  const bool pl = slot < NP;
+  const int c = pl ? slot : NP - 1;
   const int e = blockIdx.x;
   const int ci = e % A.n0, cj = (e / A.n0) % A.n1, ck = e / (A.n0 * A.n1);
   const int p = NP - 1;
   const int Gx = A.n0 * p, Gy = A.n1 * p, Gz = A.n2 * p;
-  auto dof = [&](int a, int b, int c) -> int64_t {
-    int gx = ci * p + a; gx = gx >= Gx ? gx - Gx : gx;
-    int gy = cj * p + b; gy = gy >= Gy ? gy - Gy : gy;
-    int gz = ck * p + c; gz = gz >= Gz ? gz - Gz : gz;
-    return (int64_t)gx + (int64_t)Gx * ((int64_t)gy + (int64_t)Gy * gz);
-  };
-  for (int q = tid; q < NQ3; q += 256) acc[q] = 0.0;
-  for (int n0 = 0; n0 < A.ncols; n0 += CB) {
+  double* const pb = sl + slot * CB + col;
+  double* const zb = sl + g * LS + col;
+  double acc[ZR][NQ];
+  sfor<ZR>([&](auto i) { sfor<NQ>([&](auto q) { acc[i][q] = 0.0; }); });
+  for (int n0 = wave * CB; n0 < A.ncols; n0 += 4 * CB) {
     const int n = n0 + col;
     const bool valid = n < A.ncols;
-    __syncthreads();
-    for (int l = lg; l < NL; l += NLG) {
-      const int a = l % NP, b = (l / NP) % NP, c = l / (NP * NP);
-      U[l * CB + col] = valid ? A.X[dof(a, b, c) * A.ldx + n] : 0.0;
+    const double w = valid ? (A.occ ? A.occ[n] : 1.0) : 0.0;
+    int gz = ck * p + c;
+    gz = gz >= Gz ? gz - Gz : gz;
+    double u[RB][NQX];
+    sfor<RB>([&](auto r) {
+      const int b = RB * h + r < NP ? RB * h + r : NP - 1;
+      int gy = cj * p + b;
+      gy = gy >= Gy ? gy - Gy : gy;
+      const double* row = A.X + (valid ? n : 0) + (int64_t)(Gx * (gy + Gy * gz)) * A.ldx;
+      double x[NP], y[NQ];
+      sfor<NP>([&](auto a) {
+        int gx = ci * p + a;
+        gx = gx >= Gx ? gx - Gx : gx;
+        x[a] = row[(int64_t)gx * A.ldx];
+      });
+      line_B<NP, NQ>(x, y);
+      sfor<NQX>([&](auto q) { u[r][q] = q < NQ ? y[q < NQ ? (int)q : 0] : 0.0; });
+      if constexpr (H == 2) sfor<QB>([&](auto j) { swap_halves(u[r][j], u[r][QB + j]); });
+    });
+    wave_lds_order();
+    if (pl) {
+      sfor<QB>([&](auto j) {   // qx = QB h + j
+        double xc[NP], y[NQ];
+        sfor<NP>([&](auto b) { xc[b] = u[b % RB][j + QB * (b / RB)]; });
+        line_B<NP, NQ>(xc, y);
+        if (H == 1 || NQX == NQ || QB * h + j < NQ) sfor<NQ>([&](auto q) { pb[(q * NQ + QB * h + j) * LS] = y[q]; });
+      });
     }
-    __syncthreads();
-    for (int ln = lg; ln < NP * NP; ln += NLG) {
-      const int b = ln % NP, c = ln / NP;
-      double u[NP];
-#pragma unroll
-      for (int a = 0; a < NP; ++a) u[a] = U[((c * NP + b) * NP + a) * CB + col];
-#pragma unroll
-      for (int qa = 0; qa < NQ; ++qa) {
-        double s = 0;
-#pragma unroll
-        for (int a = 0; a < NP; ++a) s += tab.B[qa * NP + a] * u[a];
-        Q1[((c * NP + b) * NQ + qa) * CB + col] = s;
+    wave_lds_order();
+    sfor<ZR>([&](auto i) {
+      if (NQ2 % G == 0 || i < ZR - 1 || g + G * i < NQ2) {
+        double m[NP], y[NQ];
+        sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+        line_B<NP, NQ>(m, y);
+        sfor<NQ>([&](auto q) { acc[i][q] = fma(w * y[q], y[q], acc[i][q]); });
       }
-    }
-    __syncthreads();
-    for (int ln = lg; ln < NP * NQ; ln += NLG) {
-      const int qa = ln % NQ, c = ln / NQ;
-      double v[NP];
-#pragma unroll
-      for (int b = 0; b < NP; ++b) v[b] = Q1[((c * NP + b) * NQ + qa) * CB + col];
-#pragma unroll
-      for (int qb = 0; qb < NQ; ++qb) {
-        double s = 0;
-#pragma unroll
-        for (int b = 0; b < NP; ++b) s += tab.B[qb * NP + b] * v[b];
-        Q2[((c * NQ + qb) * NQ + qa) * CB + col] = s;
-      }
-    }
-    __syncthreads();
-    const double w = (valid && A.occ) ? A.occ[n] : (valid ? 1.0 : 0.0);
-    for (int ln = lg; ln < NQ * NQ; ln += NLG) {
-      const int qa = ln % NQ, qb = ln / NQ;
-      double v[NP];
-#pragma unroll
-      for (int c = 0; c < NP; ++c) v[c] = Q2[((c * NQ + qb) * NQ + qa) * CB + col];
-#pragma unroll
-      for (int qc = 0; qc < NQ; ++qc) {
-        double s = 0;
-#pragma unroll
-        for (int c = 0; c < NP; ++c) s += tab.B[qc * NP + c] * v[c];
-        // reduce w |u|^2 over the CB columns of this line (lanes col..)
-        double val = w * s * s;
-#pragma unroll
-        for (int off = CB / 2; off > 0; off >>= 1) val += __shfl_xor(val, off, CB);
-        if (col == 0) acc[(qc * NQ + qb) * NQ + qa] += val;
-      }
-    }
+    });
   }
+  // over the columns of a tile (neighbouring lanes), then over the waves
+  wave_lds_order();
+  sfor<ZR>([&](auto i) {
+    sfor<NQ>([&](auto q) {
+      double v = acc[i][q];
+#pragma unroll
+      for (int o = CB / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, CB);
+      if (col == 0 && g + G * i < NQ2) sl[g + G * i + NQ2 * q] = v;
+    });
+  });
   __syncthreads();
   const double cs = A.cscale ? A.cscale[e] : 1.0;
-  for (int q = tid; q < NQ3; q += 256) A.out[(int64_t)e * NQ3 + q] = A.W3[q] * cs * acc[q];
+  for (int q = threadIdx.x; q < NQ3; q += 256)
+    A.out[(int64_t)e * NQ3 + q] = A.W3[q] * cs * ((slabs[0][q] + slabs[1][q]) + (slabs[2][q] + slabs[3][q]));
 }
 
 template <typename T>
@@ -150,6 +152,7 @@ template pawfe_status launch_cell<float>(const pawfe_op*, int, const float*, int
 
 pawfe_status launch_density(const pawfe_op* op, const double* X, int64_t ldx, int ncols,
                             const double* occ, double* out, hipStream_t s) {
+  if (op->nq != op->p + 2) return fail(PAWFE_EUNSUPPORTED, "nq must be p + 2");
   DensArgs a{};
   a.X = X;
   a.ldx = ldx;
@@ -161,14 +164,13 @@ pawfe_status launch_density(const pawfe_op* op, const double* X, int64_t ldx, in
   a.n0 = op->n[0];
   a.n1 = op->n[1];
   a.n2 = op->n[2];
-  const Tab1D<double>* tab = op->d.tab64;
   const dim3 grid(op->E), block(256);
   switch (op->p) {
-    case 2: hipLaunchKernelGGL((k_cell_density<3, 4, 8>), grid, block, 0, s, a, tab); break;
-    case 3: hipLaunchKernelGGL((k_cell_density<4, 5, 8>), grid, block, 0, s, a, tab); break;
-    case 4: hipLaunchKernelGGL((k_cell_density<5, 6, 8>), grid, block, 0, s, a, tab); break;
-    case 5: hipLaunchKernelGGL((k_cell_density<6, 7, 8>), grid, block, 0, s, a, tab); break;
-    case 6: hipLaunchKernelGGL((k_cell_density<7, 8, 8>), grid, block, 0, s, a, tab); break;
+    case 2: hipLaunchKernelGGL((k_cell_density<3, 4>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_cell_density<4, 5>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((k_cell_density<5, 6>), grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL((k_cell_density<6, 7>), grid, block, 0, s, a); break;
+    case 6: hipLaunchKernelGGL((k_cell_density<7, 8>), grid, block, 0, s, a); break;
     default: return fail(PAWFE_EUNSUPPORTED, "degree not compiled");
   }
   PAWFE_HIP(hipGetLastError());
