@@ -202,14 +202,17 @@ struct Tables {
   double ME[PC][PC] = {};
   double MO[PH > 0 ? PH : 1][PH > 0 ? PH : 1] = {};
   double DG[NQ][NQ] = {};  // DG[i][j] = g_j'(eta_i), g_j the Lagrange basis through the Gauss points
-  double G1[NP][NP] = {};  // G1[a][b] = sum_q w_q l_a(eta_q) l_b'(eta_q) (imaginary k term)
+  // G1[a][b] = sum_q w_q l_a(eta_q) l_b'(eta_q) (imaginary k term);
+  // G1[NP-1-a][NP-1-b] = -G1[a][b]: with GE/GO as BE/BO, a < PC
+  double GE[PC][PC] = {};
+  double GO[PC][PH > 0 ? PH : 1] = {};
 };
 
 template <int NP, int NQ>
 constexpr Tables<NP, NQ> make_tables(bool sc) {
   constexpr Rule<NP> xi = gll<NP - 1>();
   constexpr Rule<NQ> g = gauss<NQ>();
-  double B[NQ][NP] = {}, D[NQ][NP] = {}, K[NP][NP] = {}, M[NP][NP] = {};
+  double B[NQ][NP] = {}, D[NQ][NP] = {}, K[NP][NP] = {}, M[NP][NP] = {}, G1[NP][NP] = {};
   for (int q = 0; q < NQ; ++q)
     for (int a = 0; a < NP; ++a) {
       double v = 1.0, d = 0.0;
@@ -236,7 +239,7 @@ constexpr Tables<NP, NQ> make_tables(bool sc) {
       }
       K[a][b] = k;
       M[a][b] = m;
-      t.G1[a][b] = gi;
+      G1[a][b] = gi;
     }
   for (int i = 0; i < NQ; ++i)
     for (int jj = 0; jj < NQ; ++jj) {
@@ -261,7 +264,7 @@ constexpr Tables<NP, NQ> make_tables(bool sc) {
       for (int r = 0; r < NP; ++r) {
         K[r][a] *= inv;
         M[r][a] *= inv;
-        t.G1[r][a] *= inv;
+        G1[r][a] *= inv;
       }
     }
   }
@@ -274,7 +277,10 @@ constexpr Tables<NP, NQ> make_tables(bool sc) {
     for (int a = 0; a < PC; ++a) {
       t.KE[r][a] = a < PH ? 0.5 * (K[r][a] + K[r][NP - 1 - a]) : K[r][a];
       t.ME[r][a] = a < PH ? 0.5 * (M[r][a] + M[r][NP - 1 - a]) : M[r][a];
+      t.GE[r][a] = a < PH ? 0.5 * (G1[r][a] + G1[r][NP - 1 - a]) : G1[r][a];
     }
+  for (int r = 0; r < PC; ++r)
+    for (int a = 0; a < PH; ++a) t.GO[r][a] = 0.5 * (G1[r][a] - G1[r][NP - 1 - a]);
   for (int r = 0; r < PH; ++r)
     for (int a = 0; a < PH; ++a) {
       t.KO[r][a] = 0.5 * (K[r][a] - K[r][NP - 1 - a]);
@@ -415,18 +421,31 @@ __host__ __device__ __forceinline__ void line_sym(const EOIn<NP, T>& in, T (&y)[
   });
 }
 
-// y = G1 x on one line of NP node values (G1 is not symmetric: a plain
-// product with compile-time coefficients; SC: the scaled table)
+// y = G1 x on one line of NP node values, from the even / odd parts of x: the
+// even part of x gives the odd part of y and the odd part the even one
+// (SC: the scaled table)
 template <int NP, int NQ, bool SC = false, typename T>
-__host__ __device__ __forceinline__ void line_g1(const T (&x)[NP], T (&y)[NP]) {
+__host__ __device__ __forceinline__ void line_g1(const EOIn<NP, T>& in, T (&y)[NP]) {
   using TB = ref1d::Tab<NP, NQ>;
-  sfor<NP>([&](auto a) {
-    T acc = T(0);
-    sfor<NP>([&](auto b) {
-      constexpr T c = (T)(SC ? TB::ts.G1[a][b] : TB::t.G1[a][b]);
-      acc = fma_t(c, x[b], acc);
+  constexpr const ref1d::Tables<NP, NQ>& tb = SC ? TB::ts : TB::t;
+  constexpr int PH = NP / 2, PC = (NP + 1) / 2;
+  sfor<PC>([&](auto a) {
+    T ye = T(0);
+    sfor<PH>([&](auto b) {
+      constexpr T c = (T)tb.GO[a][b];
+      ye = fma_t(c, in.o[b], ye);
     });
-    y[a] = acc;
+    if constexpr (a < PH) {
+      T yo = T(0);
+      sfor<PC>([&](auto b) {
+        constexpr T c = (T)tb.GE[a][b];
+        yo = fma_t(c, in.e[b], yo);
+      });
+      y[a] = ye + yo;
+      y[NP - 1 - a] = ye - yo;
+    } else {
+      y[a] = ye;
+    }
   });
 }
 
@@ -848,7 +867,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
         if (!ln.on[r]) continue;
         if constexpr (CPLX) {
           T yi[NP];
-          line_g1<NP, NQ, SC>(xp[r], yi);
+          line_g1<NP, NQ, SC>(split_eo<NP>(xp[r]), yi);
           sfor<NP>([&](auto a) { sI[offK<T>(a, ln.u[r], ln.v[r]) + col] = yi[a]; });
         }
         // each result is stored as soon as it is formed (fewer live registers)
@@ -1039,7 +1058,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
         if constexpr (CPLX) {
           T mi[NP], gm[NP];
           line_sym<NP, NQ, false, SC>(split_eo<NP>(iv[r]), mi);
-          line_g1<NP, NQ, SC>(mp[r], gm);
+          line_g1<NP, NQ, SC>(split_eo<NP>(mp[r]), gm);
           sfor<NP>([&](auto b) { sI[offK<T>(ln.u[r], b, ln.v[r]) + col] = fma_t(A.gk[0], mi[b], A.gk[1] * gm[b]); });
         }
         const EOIn<NP, T> em = split_eo<NP>(m[r]);
@@ -1095,7 +1114,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
           if constexpr (CPLX) {
             T mi[NP], gm[NP];
             line_sym<NP, NQ, false, SC>(split_eo<NP>(iv[r]), mi);
-            line_g1<NP, NQ, SC>(mp[r], gm);
+            line_g1<NP, NQ, SC>(split_eo<NP>(mp[r]), gm);
             const T sg = (col & 1) ? T(1) : T(-1);
             sfor<NP>([&](auto c) { acc[c] = fma_t(sg, fma_t(A.gk[2], gm[c], mi[c]), acc[c]); });
           }

@@ -12,6 +12,8 @@
 //   V:  planes By Bx -> slab, lines Bz, V(q) W_q, Bz^T in place, planes By^T Bx^T
 //   M:  planes My Mx -> slab, lines fz Kz (residual: - lambda det J Mz too)
 //   K:  planes fx My Kx + fy Ky Mx -> slab, lines Mz, added to M's lines
+//   complex operators, before M and K: the same two rounds with G1 for the
+//   imaginary k term, read back from the partner column's place in the slab
 // and the sum is added to Y (first visits of the step as in cell_valu.h).
 // The gathered rows are wave-uniform for x and y, so their addresses are
 // scalar; the lanes only carry the offset of their plane and column.
@@ -94,8 +96,9 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   constexpr int H = W::H, CB = W::CB, G = W::G, RB = W::RB, QB = W::QB, NPX = W::NPX, NQX = W::NQX;
   constexpr bool GEN = is_general_mode(MODE);
   constexpr bool MASS = MODE == kValuGenMass || MODE == kValuMass;
-  constexpr bool RES = MODE == kValuHRes;
-  constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep;
+  constexpr bool RES = MODE == kValuHRes || MODE == kValuHResC;
+  constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep || MODE == kValuStepC;
+  constexpr bool CPLX = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
   constexpr bool SC = STEP;
   constexpr int NQ2 = NQ * NQ, NP2 = NP * NP, NQ3 = NQ * NQ * NQ;
   constexpr int WT = kWaveTiles<MODE>;
@@ -299,8 +302,81 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       });
     });
   }
-  // ---- M and K terms -----------------------------------------------------
   constexpr int ZK = (NP2 + G - 1) / G;
+  // ---- complex: the imaginary k term, added to the partner column ----------
+  if constexpr (CPLX) {
+    T gx[RB][NPX], mx[RB][NPX];
+    sfor<RB>([&](auto r) {
+      T xr[NP], y[NP];
+      row(r, xr);
+      const EOIn<NP, T> eo = split_eo<NP>(xr);
+      line_sym<NP, NQ, false, SC>(eo, y);
+      sfor<NPX>([&](auto a) { mx[r][a] = a < NP ? y[a < NP ? (int)a : 0] : T(0); });
+      line_g1<NP, NQ, SC>(eo, y);
+      sfor<NPX>([&](auto a) { gx[r][a] = a < NP ? y[a < NP ? (int)a : 0] : T(0); });
+      if constexpr (H == 2) sfor<RB>([&](auto j) {
+        swap_halves(mx[r][j], mx[r][RB + j]);
+        swap_halves(gx[r][j], gx[r][RB + j]);
+      });
+    });
+    const T g0 = f * A.gk[0], g1 = f * A.gk[1], g2 = f * A.gk[2];
+    wave_lds_order();
+    // columns: My Mx -> slab, gx My G1x + gy G1y Mx stays in gx
+    if (pl) {
+      sfor<RB>([&](auto j) {
+        T mc[NP], gc[NP], y[NP], z[NP];
+        sfor<NP>([&](auto b) {
+          mc[b] = mx[b % RB][j + RB * (b / RB)];
+          gc[b] = gx[b % RB][j + RB * (b / RB)];
+        });
+        const EOIn<NP, T> em = split_eo<NP>(mc);
+        line_sym<NP, NQ, false, SC>(em, y);
+        if (H == 1 || NPX == NP || RB * h + j < NP) sfor<NP>([&](auto b) { pb[(b * NP + RB * h + j) * LS] = y[b]; });
+        line_sym<NP, NQ, false, SC>(split_eo<NP>(gc), z);
+        line_g1<NP, NQ, SC>(em, y);
+        sfor<NP>([&](auto b) { gx[b % RB][j + RB * (b / RB)] = fma_t(g0, z[b], g1 * y[b]); });
+      });
+    }
+    wave_lds_order();
+    T il[ZK][NP];
+    sfor<ZK>([&](auto i) {
+      if (NP2 % G == 0 || i < ZK - 1 || g + G * i < NP2) {
+        T m[NP], y[NP];
+        sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+        line_g1<NP, NQ, SC>(split_eo<NP>(m), y);
+        sfor<NP>([&](auto k) { il[i][k] = g2 * y[k]; });
+      }
+    });
+    wave_lds_order();
+    if (pl) {
+      sfor<RB>([&](auto j) {
+        if (H == 1 || NPX == NP || RB * h + j < NP)
+          sfor<NP>([&](auto b) { pb[(b * NP + RB * h + j) * LS] = gx[b % RB][j + RB * (b / RB)]; });
+      });
+    }
+    wave_lds_order();
+    sfor<ZK>([&](auto i) {
+      if (NP2 % G == 0 || i < ZK - 1 || g + G * i < NP2) {
+        T m[NP], y[NP];
+        sfor<NP>([&](auto k) { m[k] = zb[(i * G * NP + k) * CB]; });
+        line_sym<NP, NQ, false, SC>(split_eo<NP>(m), y);
+        sfor<NP>([&](auto k) { zb[(i * G * NP + k) * CB] = y[k] + il[i][k]; });
+      }
+    });
+    wave_lds_order();
+    // s_n = -1 on real, +1 on imaginary columns, of the partner column's term
+    const T sg = (col & 1) ? T(1) : T(-1);
+    const T* const pp = sl + slot * CB + (col ^ 1);
+    sfor<RB>([&](auto r) {
+      const int b = lrow(r);
+      sfor<NP>([&](auto a) {
+        acc[r][a] = fma_t(sg, pp[(b * NP + a) * LS], acc[r][a]);
+        opaque(acc[r][a]);
+        opaque(x[r][a]);
+      });
+    });
+  }
+  // ---- M and K terms -----------------------------------------------------
   T mx[RB][NPX], kx[MASS ? 1 : RB][NPX];
   sfor<RB>([&](auto r) {
     T xr[NP], y[NP];
@@ -449,7 +525,7 @@ namespace {
 // Modes that have a one-wave variant.
 constexpr bool is_wave_mode(int mode) {
   return mode == kValuH || mode == kValuHRes || mode == kValuMass || mode == kValuStep || mode == kValuGenH ||
-         mode == kValuGenMass || mode == kValuGenStep;
+         mode == kValuGenMass || mode == kValuGenStep || mode == kValuHC || mode == kValuHResC || mode == kValuStepC;
 }
 
 // Where the one-wave split pays, by the cell columns (cells x columns) of an
@@ -459,14 +535,17 @@ constexpr bool is_wave_mode(int mode) {
 // columns, 39.5 -> 38.9 at 16,400, 74 -> 63 at 32,000; FP64 34.6 -> 35.7 at
 // 8,000, 71.6 -> 63.0 at 16,400; degree 3 FP64 7.7 -> 7.7 at 4,100, FP32 7.4
 // -> 7.5 at 6,900; degree 2 FP32 even at any size, FP64 5.0 -> 5.4 at 2,000
-// and 8.7 -> 5.9 at 6,900.  The mass term is too short to lose: 5.2 -> 4.7 us
+// and 8.7 -> 5.9 at 6,900.  Complex step at degree 6 FP32 22.5 -> 25.6 at 8,000
+// real cell columns, 44.7 -> 41.8 at 16,400; FP64 16.0 -> 19.8 at 2,000, 26.3
+// -> 23.9 at 4,100, 183 -> 131 at 32,000.  The mass term is too short to lose: 5.2 -> 4.7 us
 // at 128 cell columns.
 template <typename T, int NP, int MODE>
 bool wave_pays(const pawfe_op* op, int ncols) {
   if (MODE == kValuMass || MODE == kValuGenMass) return true;
   const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
-  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : 16000)
-                                       : (NP == 3 ? 3000 : NP == 4 ? 4000 : 8000);
+  constexpr bool kCplx = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
+  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : kCplx ? 12000 : 16000)
+                                       : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000);
   return per_colour >= least;
 }
 

@@ -89,3 +89,40 @@ def test_applies_overwrite(p, graded, nc):
         o32 = torch.full(X.shape, float("nan"), device="cuda", dtype=torch.float32)
         _close(apply(X.float(), out=o32, prec="fp32")[:, jd].double().cpu().numpy(), want, 2e-5)
     op.close()
+
+
+@pytest.mark.parametrize("p", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_complex_local_terms(p, prec):
+    """The complex (k-point) variants: H_loc (k), the step and, in FP64, the
+    residual inside a degree-2 filter, on wide blocks of (re, im) pairs."""
+    from oracle.chfsi import rchfsi_filter
+    from oracle.paw import PAWOperator
+    from paper_2604_26037_amd import Operator
+    from workloads.configs import custom_system
+    n, nc = (3, 2, 3), 8009
+    box = tuple(1.6 * v for v in n)
+    pos = [(0.4, 0.5, 0.6), (2.0, 2.2, 3.1)]
+    s = custom_system(n, box, p, p + 2, pos=pos, rcut=0.7, channels="spd8", wells=pos, s_H=0.5, s_S=0.4, seed=p,
+                      kpoint=(0.3, -0.2, 0.45), is_complex=True)
+    ref, op = PAWOperator(s), Operator(s)
+    g = torch.Generator(device="cuda").manual_seed(p)
+    dt, rdt = (torch.complex128, torch.float64) if prec == 0 else (torch.complex64, torch.float32)
+    draw = lambda d: torch.randn(op.ndof, nc, device="cuda", dtype=d, generator=g)  # noqa: E731
+    X, Y, Y64 = draw(dt), draw(dt), draw(torch.complex128)
+    lam = torch.rand(nc, device="cuda", dtype=torch.float64, generator=g)
+    j = torch.from_numpy(np.concatenate([np.arange(5), [4000], np.arange(nc - 6, nc)])).cuda()
+    host = lambda t: t[:, j].to(torch.complex128).cpu().numpy()  # noqa: E731
+    x, y, y64, ln = host(X), host(Y), host(Y64), lam[j].cpu().numpy()
+    tol = 1e-12 if prec == 0 else 2e-5
+    _close(host(op.apply_local(X, Y.clone(), which=0, alpha=0.7, prec=prec)), y + 0.7 * ref.loc.apply_H(x), tol)
+    a, ac, zz = 0.37, -0.81, 0.42
+    real = lambda t: torch.view_as_real(t).reshape(op.ndof, 2 * nc)  # noqa: E731
+    RX = real(Y.clone()).contiguous()
+    op.cheb_step_local(real(X), RX, real(Y64), lam.repeat_interleave(2), a, ac, zz, prec=prec)
+    got = host(torch.view_as_complex(RX.reshape(op.ndof, nc, 2).to(rdt)))
+    _close(got, (-ac * x - zz * y) + a * y64 * ln[None, :] + a * ref.loc.apply_H(ref.MDinv[:, None] * x), tol)
+    if prec == 0:
+        out = op.cheb_filter(X, lam, 2, -1.0, 2.0, 400.0, prec=0)
+        _close(host(out), rchfsi_filter(ref, x, ln, 2, -1.0, 2.0, 400.0), 1e-9)
+    op.close()
