@@ -536,7 +536,8 @@ constexpr bool is_wave_mode(int mode) {
 // 8,000, 71.6 -> 63.0 at 16,400; degree 3 FP64 7.7 -> 7.7 at 4,100, FP32 7.4
 // -> 7.5 at 6,900; degree 2 FP32 even at any size, FP64 5.0 -> 5.4 at 2,000
 // and 8.7 -> 5.9 at 6,900.  Complex step at degree 6 FP32 22.5 -> 25.6 at 8,000
-// real cell columns, 44.7 -> 41.8 at 16,400; FP64 16.0 -> 19.8 at 2,000, 26.3
+// real cell columns, 44.7 -> 41.8 at 16,400, 75 -> 78 at 24,000 (3000 waves are one
+// and a half rounds), 85 -> 75 at 32,000; FP64 16.0 -> 19.8 at 2,000, 26.3
 // -> 23.9 at 4,100, 183 -> 131 at 32,000.  The mass term is too short to lose: 5.2 -> 4.7 us
 // at 128 cell columns.
 template <typename T, int NP, int MODE>
@@ -544,7 +545,7 @@ bool wave_pays(const pawfe_op* op, int ncols) {
   if (MODE == kValuMass || MODE == kValuGenMass) return true;
   const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
   constexpr bool kCplx = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
-  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : kCplx ? 12000 : 16000)
+  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : kCplx ? 30000 : 16000)
                                        : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000);
   return per_colour >= least;
 }

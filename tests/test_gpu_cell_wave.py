@@ -100,7 +100,7 @@ def test_complex_local_terms(p, prec):
     from oracle.paw import PAWOperator
     from paper_2604_26037_amd import Operator
     from workloads.configs import custom_system
-    n, nc = (3, 2, 3), 8009
+    n, nc = (3, 2, 3), 15009   # past the thresholds of both precisions
     box = tuple(1.6 * v for v in n)
     pos = [(0.4, 0.5, 0.6), (2.0, 2.2, 3.1)]
     s = custom_system(n, box, p, p + 2, pos=pos, rcut=0.7, channels="spd8", wells=pos, s_H=0.5, s_S=0.4, seed=p,
