@@ -93,9 +93,27 @@ pawfe_status ensure_scratch(pawfe_op* op, size_t bytes) {
   return PAWFE_OK;
 }
 
+// Scratch of an operator with room for per-cell results (`cell` bytes besides
+// `least`), or without, from then on, where the allocation fails.
+pawfe_status ensure_scratch_cell(pawfe_op* op, size_t least, size_t cell) {
+  if (op->cell_denied) return ensure_scratch(op, least);
+  if (ensure_scratch(op, least + cell) == PAWFE_OK) return PAWFE_OK;
+  (void)hipGetLastError();
+  op->cell_denied = true;
+  return ensure_scratch(op, least);
+}
+
 struct NlBufs {
   double *part, *c, *d, *t;
+  void* cell = nullptr;   // per-cell results (cell_buf_bytes), where there is room for them
 };
+
+// the per-cell results of blocks of ncols columns in what is left of a
+// workspace, if they pay and fit
+void carve_cell(const pawfe_op* op, Carve& cv, int64_t ncols, size_t elem, NlBufs& b) {
+  const size_t n = cell_buf_bytes(op, ncols, elem);
+  if (n && cv.off + align256(n) <= cv.cap) b.cell = cv.take<char>(n);
+}
 
 NlBufs carve_nl(const pawfe_op* op, Carve& cv, int64_t ncols) {
   NlBufs b;
@@ -123,7 +141,7 @@ pawfe_status do_apply(const pawfe_op* op, int which, const T* X, int64_t ldx, T*
       }
     }
     // the first visit of each DOF writes Y, so it needs no clearing before
-    CHECK(launch_cell<T>(op, mode, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, false, true));
+    CHECK(launch_cell<T>(op, mode, X, ldx, Y, ldy, ncols, nullptr, 1.0, s, false, true, b.cell));
     return launch_node_fixup<T>(op, b.d, 1.0, ncols, Y, ldy, s);
   }
   // Sinv_hat
@@ -138,7 +156,7 @@ pawfe_status do_residual(const pawfe_op* op, const double* X, int64_t ldx, const
                          int ncols, const NlBufs& b, hipStream_t s) {
   CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, s));
   CHECK(launch_atom_first(op, b.part, nullptr, op->d.dH, op->d.dS, lam, nullptr, ncols, nullptr, b.d, nullptr, s));
-  CHECK(launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s, false, true));
+  CHECK(launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s, false, true, b.cell));
   return launch_node_fixup<double>(op, b.d, 1.0, ncols, Y, ldy, s);
 }
 
@@ -167,9 +185,13 @@ pawfe_status apply_entry(const pawfe_op* cop, int which, const void* X, int64_t 
   }
   const int64_t chunk = 512;
   const int64_t cmax = std::min<int64_t>(chunk, nvec);
-  CHECK(ensure_scratch(op, nl_scratch_bytes(op, cmax)));
+  const size_t elem = prec == PAWFE_FP64 ? 8 : 4;
+  // room for any smaller call and both types: a graph that holds this call
+  // keeps the scratch that it was captured with whatever narrower calls follow
+  CHECK(ensure_scratch_cell(op, nl_scratch_bytes(op, cmax), align256(cell_buf_most(op, cmax))));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs b = carve_nl(op, cv, cmax);
+  carve_cell(op, cv, cmax, elem, b);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: apply scratch smaller than its carve");
   hipStream_t s = S(stream);
   for (int64_t j0 = 0; j0 < nvec; j0 += chunk) {
@@ -190,7 +212,10 @@ pawfe_status apply_entry(const pawfe_op* cop, int which, const void* X, int64_t 
 // explicit T.
 bool fused_step(const pawfe_op* op, int32_t prec) { return prec != PAWFE_BF16X3 && cell_step_available(op); }
 
-// B: real columns of one block (two per complex column)
+// What a block state must hold (filter_ws_bytes) and what it can use besides
+// (the per-cell results of a small problem, for its step and, in FP64, its
+// residual).  B: real columns of one block (two per complex column).
+size_t filter_ws_extra(const pawfe_op* op, int64_t B, int32_t prec);
 size_t filter_ws_bytes(const pawfe_op* op, int64_t B, int32_t prec) {
   const size_t tr = prec == PAWFE_FP64 ? 8 : 4;
   size_t b = align256((size_t)op->M * B * 8);            // Y
@@ -204,6 +229,20 @@ size_t filter_ws_bytes(const pawfe_op* op, int64_t B, int32_t prec) {
   b += 2 * align256((size_t)B * 8);                      // lamX, lamY
   if (op->cplx) b += align256((size_t)B * 8);             // lambda per real column
   return b + 256;
+}
+
+size_t filter_ws_extra(const pawfe_op* op, int64_t B, int32_t prec) {
+  if (!fused_step(op, prec)) return 0;
+  // FP32 filters form an FP64 residual too: room for that where it pays.
+  // Always less than a block state: a workspace for one block never reads as
+  // two, so a filter given one (in a batch's capture) never forks.
+  const size_t state = filter_ws_bytes(op, B, prec);
+  size_t most = 0;
+  for (const size_t elem : {prec == PAWFE_FP64 ? size_t(8) : size_t(4), size_t(8)}) {
+    const size_t b = align256(cell_buf_bytes(op, B, elem));
+    if (b < state) most = std::max(most, b);
+  }
+  return most;
 }
 
 template <typename TR>
@@ -287,6 +326,11 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
   double* lamX = cv.take<double>(B);
   double* lamY = cv.take<double>(B);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: filter workspace smaller than its carve");
+  // one region for the residual's and the steps' per-cell results
+  NlBufs ns = nb;
+  Carve cw = cv;
+  carve_cell(op, cv, B, 8, nb);
+  carve_cell(op, cw, B, sizeof(TR), ns);
   const int64_t ld = nc;
   // step 1: polynomial scalars
   const double e = (bU - bW) / 2.0, c = (bU + bW) / 2.0;
@@ -316,7 +360,7 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
     CHECK(launch_atom_second(op, nb.c, dk, first ? nullptr : dprev, first ? nullptr : nwp, nullptr, nb.t, nwn, lamX,
                              lamY, lam_in, a, a * c, zz, nc, s));
     CHECK(launch_node_fixup<TR>(op, nb.t, -1.0, nc, RY, ld, s));
-    CHECK(launch_cell_step<TR>(op, RY, RX, ld, Yr, ldyr, lamY, a, a * c, zz, nc, s));
+    CHECK(launch_cell_step<TR>(op, RY, RX, ld, Yr, ldyr, lamY, a, a * c, zz, nc, s, ns.cell));
     std::swap(RX, RY);
     std::swap(lamX, lamY);
     std::swap(dk, dprev);
@@ -897,6 +941,7 @@ pawfe_status pawfe_apply_H_noalloc(const pawfe_op* op, const void* X, int64_t ld
   CHECK(static_scratch(&base));
   Carve cv(base, kStaticScratchBytes);
   NlBufs b = carve_nl(op, cv, chunk);
+  carve_cell(op, cv, chunk, prec == PAWFE_FP64 ? 8 : 4, b);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: static scratch smaller than its carve");
   hipStream_t s = S(stream);
   for (int64_t j0 = 0; j0 < nvec; j0 += chunk) {
@@ -995,7 +1040,8 @@ pawfe_status pawfe_cheb_filter_workspace(const pawfe_op* op, int64_t nvec, int32
   CHECK(check_prec(prec, op));
   const int64_t B = std::min<int64_t>(block, nvec);
   // room for two blocks in flight when there is more than one block
-  *bytes = filter_ws_bytes(op, B * (op->cplx ? 2 : 1), prec) * (nvec > B ? 2 : 1);
+  const int64_t Br = B * (op->cplx ? 2 : 1);
+  *bytes = (filter_ws_bytes(op, Br, prec) + filter_ws_extra(op, Br, prec)) * (nvec > B ? 2 : 1);
   return PAWFE_OK;
 }
 
@@ -1017,16 +1063,18 @@ static pawfe_status cheb_filter_impl(const pawfe_op* op, const void* Xin, int64_
   if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) return fail(PAWFE_EINVAL, "workspace must be 256-byte aligned");
   const int64_t cf = op->cplx ? 2 : 1;   // real columns per column
   const int64_t B = std::min<int64_t>(block, nvec);
-  const size_t one = filter_ws_bytes(op, B * cf, prec);
-  if (ws_bytes < one) return fail(PAWFE_EINVAL, "workspace too small");
+  const size_t least = filter_ws_bytes(op, B * cf, prec), full = least + filter_ws_extra(op, B * cf, prec);
+  if (ws_bytes < least) return fail(PAWFE_EINVAL, "workspace too small");
   hipStream_t s = S(stream);
   // Blocks are uncoupled.  With room for several block states (and more
   // than one block), block b runs on internal stream b mod nconc, forked
   // from and joined back into `s`: one block's projector and node kernels
   // then overlap another's cell kernel.
   const int64_t nblocks = (nvec + B - 1) / B;
-  const int nconc = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kMaxConcBlocks, nblocks,
-                                                                  (int64_t)(ws_bytes / one)}));
+  // two in flight before room for the per-cell results, more only with it
+  const int64_t fit = std::max<int64_t>(std::min<size_t>(2, ws_bytes / least), ws_bytes / full);
+  const int nconc = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kMaxConcBlocks, nblocks, fit}));
+  const size_t one = ws_bytes / nconc & ~size_t(255);   // a block state's share, `least` or more
   pawfe_op* mop = const_cast<pawfe_op*>(op);
   hipStream_t bstream[kMaxConcBlocks] = {};
   if (nconc > 1) {
@@ -1115,10 +1163,15 @@ static size_t rr_ws_bytes(const pawfe_op* op, int64_t N) {
   return b + 256;
 }
 
+// what Rayleigh-Ritz can use besides: the per-cell results of a small block
+static size_t rr_ws_extra(const pawfe_op* op, int64_t N) {
+  return align256(cell_buf_bytes(op, std::min<int64_t>(256, N * (op->cplx ? 2 : 1)), 8));
+}
+
 pawfe_status pawfe_rayleigh_ritz_workspace(const pawfe_op* op, int64_t nvec, size_t* bytes) {
   if (!op || !bytes) return fail(PAWFE_EINVAL, "op or bytes is NULL");
   if (nvec < 1) return fail(PAWFE_EINVAL, "nvec must be >= 1");
-  *bytes = rr_ws_bytes(op, nvec);
+  *bytes = rr_ws_bytes(op, nvec) + rr_ws_extra(op, nvec);
   return PAWFE_OK;
 }
 
@@ -1156,6 +1209,7 @@ static pawfe_status rayleigh_ritz_impl(const pawfe_op* cop, void* Xv, int64_t ld
   rocblas_int* info = cv.take<rocblas_int>(1);
   double* npart_buf = cv.take<double>((size_t)((op->M + 4095) / 4096) * B);
   NlBufs nb = carve_nl(op, cv, B);
+  carve_cell(op, cv, B, 8, nb);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: Rayleigh-Ritz workspace smaller than its carve");
   if (!op->blas) {
     rocblas_handle h;
@@ -1362,12 +1416,13 @@ pawfe_status pawfe_band_energy_grad(const pawfe_op* cop, const void* Xv, int64_t
   const int64_t nchunks = (op->M + 4095) / 4096;
   size_t need = nl_scratch_bytes(op, std::max<int64_t>(N, B)) + align256((size_t)op->M * B * 8) +
                 align256((size_t)nchunks * B * 8) + align256((size_t)N * 8) + 1024;
-  CHECK(ensure_scratch(op, need));
+  CHECK(ensure_scratch_cell(op, need, align256(cell_buf_most(op, 512))));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs nb = carve_nl(op, cv, std::max<int64_t>(N, B));
   double* HXb = cv.take<double>((size_t)op->M * B);
   double* pbuf = cv.take<double>((size_t)nchunks * B);
   double* occ2 = cv.take<double>((size_t)N);
+  carve_cell(op, cv, B, 8, nb);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: gradient scratch smaller than its carve");
   if (op->cplx && occ) {
     CHECK(launch_dup_pairs(occ, occ2, (int)Nc, s));
@@ -1404,7 +1459,7 @@ pawfe_status pawfe_lanczos_bounds(const pawfe_op* cop, int32_t k, uint64_t seed,
   const int64_t M = op->M * cf;
   const int64_t nchunks = (M + 4095) / 4096;
   size_t need = nl_scratch_bytes(op, cf) + 5 * align256((size_t)M * 8) + align256((size_t)nchunks * 8) + 1024;
-  CHECK(ensure_scratch(op, need));
+  CHECK(ensure_scratch_cell(op, need, align256(cell_buf_most(op, cf))));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs nb = carve_nl(op, cv, cf);
   double* v = cv.take<double>(M);
@@ -1414,6 +1469,7 @@ pawfe_status pawfe_lanczos_bounds(const pawfe_op* cop, int32_t k, uint64_t seed,
   double* u = cv.take<double>(M);
   double* pbuf = cv.take<double>(nchunks);
   double* dot = cv.take<double>(2);
+  carve_cell(op, cv, cf, 8, nb);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: Lanczos scratch smaller than its carve");
   // seeded start vector (splitmix64 -> uniform(-1, 1)), generated on the host
   std::vector<double> h(M);
@@ -1504,7 +1560,12 @@ pawfe_status pawfe_chfsi_solve(const pawfe_op* op, void* X, int64_t ldx, int64_t
   CHECK(check_prec(prec, op));
   size_t need = 0;
   CHECK(pawfe_chfsi_solve_workspace(op, nvec, block, prec, &need));
-  if (ws_bytes < need) return fail(PAWFE_EINVAL, "workspace too small");
+  // the room for per-cell results may be missing
+  const int64_t Bb = std::min<int64_t>(block, nvec), Br = Bb * (op->cplx ? 2 : 1);
+  const size_t least = align256(std::max(filter_ws_bytes(op, Br, prec) * (nvec > Bb ? 2 : 1), rr_ws_bytes(op, nvec))) +
+                       align256((size_t)op->M * nvec * (op->cplx ? 2 : 1) * 8);
+  if (ws_bytes < least) return fail(PAWFE_EINVAL, "workspace too small");
+  if (ws_bytes < need) need = least;
   if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) return fail(PAWFE_EINVAL, "workspace must be 256-byte aligned");
   // shared part of the filter and Rayleigh-Ritz, then the residual R of the
   // Ritz pairs (written by each Rayleigh-Ritz, step 2 of the next filter)

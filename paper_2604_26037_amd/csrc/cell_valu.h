@@ -776,6 +776,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     // registers that would hold them across the passes are what the step's
     // own loads need there)
     constexpr bool kLateYo = STEP && sizeof(T) == 4;
+    const bool to_buf = A.cellbuf != nullptr;   // nothing is added to: no old rows, no first visits
     T yo[NJ];
     if constexpr (!kLateYo) {
       int node[NJ];
@@ -791,7 +792,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         yo[j] = T(0);
-        if (STEP || !((cm >> ((cpk >> (5 * j)) & 31u)) & 1u)) yo[j] = *elem(A.Y, ldyb, nn, node[j]);
+        if (!to_buf && (STEP || !((cm >> ((cpk >> (5 * j)) & 31u)) & 1u))) yo[j] = *elem(A.Y, ldyb, nn, node[j]);
       }
     }
     // step mode: which of the thread's nodes this cell visits first (the
@@ -826,7 +827,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     // 0.975 s, where FP32 gains 0.556 -> 0.548 s)
     constexpr bool kEarlyY = STEP && sizeof(T) == 4;
     if constexpr (kEarlyY) {
-      if (valid) {
+      if (valid && !to_buf) {
         int node[NJ];
         nodes_of(cp, node);
         step_loads(node);
@@ -1132,33 +1133,40 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       T f = A.alpha;
       if constexpr (STEP && GEN) f = f / idet;   // the cell's det J of M_D^{-1}
       if constexpr (MASS) f = f * idet * (A.lam ? (T)(-A.lam[n]) : T(1));
-      int node[NJ];
-      nodes_of(cp, node);
-      if constexpr (STEP) {
-        // Node part of the Chebyshev step at the first visit of a DOF, on
-        // the old value before any cell adds to it:
-        //   Y <- (-ac X - zz Y) + a lamY_n Yres
-        // the last product and sum in FP64, rounded once
-        if constexpr (kLateYo) {
+      auto result = [&](int j) {
+        return f * *reinterpret_cast<const T*>(reinterpret_cast<const char*>(sK) + k_of_u(pk[j] & ((1u << kLdsBits) - 1)));
+      };
+      if (to_buf) {
+        T* out = A.cellbuf + ((int64_t)cp.e * NL + slot) * A.ncols + n;
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) yo[j] = lreal(j) ? *elem(A.Y, ldyb, n, node[j]) : T(0);
+        for (int j = 0; j < NJ; ++j)
+          if (lreal(j)) out[(int64_t)(S * j) * A.ncols] = result(j);
+      } else {
+        int node[NJ];
+        nodes_of(cp, node);
+        if constexpr (STEP) {
+          // Node part of the Chebyshev step at the first visit of a DOF, on
+          // the old value before any cell adds to it:
+          //   Y <- (-ac X - zz Y) + a lamY_n Yres
+          // the last product and sum in FP64, rounded once
+          if constexpr (kLateYo) {
+  #pragma unroll
+            for (int j = 0; j < NJ; ++j) yo[j] = lreal(j) ? *elem(A.Y, ldyb, n, node[j]) : T(0);
+          }
+          if constexpr (!kEarlyY) step_loads(node);
+          const double ly = A.sa * A.lamY[n];
+          const T mac = (T)(-A.sac), zz = (T)A.szz;
+  #pragma unroll
+          for (int j = 0; j < NJ; ++j) {   // branch-free: a select per node
+            const T part = mac * sxv[j] - zz * yo[j];
+            const T upd = (T)((double)part + syf[j] * ly);
+            yo[j] = ((sown >> j) & 1u) ? upd : yo[j];
+          }
         }
-        if constexpr (!kEarlyY) step_loads(node);
-        const double ly = A.sa * A.lamY[n];
-        const T mac = (T)(-A.sac), zz = (T)A.szz;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {   // branch-free: a select per node
-          const T part = mac * sxv[j] - zz * yo[j];
-          const T upd = (T)((double)part + syf[j] * ly);
-          yo[j] = ((sown >> j) & 1u) ? upd : yo[j];
-        }
+  #pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          if (lreal(j)) *elem(A.Y, ldyb, n, node[j]) = yo[j] + result(j);
       }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if (lreal(j))
-          *elem(A.Y, ldyb, n, node[j]) =
-              yo[j] + f * *reinterpret_cast<const T*>(reinterpret_cast<const char*>(sK) +
-                                                      k_of_u(pk[j] & ((1u << kLdsBits) - 1)));
     }
     __syncthreads();
     cur_c = nxt_c;
@@ -1210,6 +1218,16 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
   const T fx = (T)(0.5 * op->detJ * (2.0 / op->h[0]) * (2.0 / op->h[0]));
   const T fy = (T)(0.5 * op->detJ * (2.0 / op->h[1]) * (2.0 / op->h[1]));
   const T fz = (T)(0.5 * op->detJ * (2.0 / op->h[2]) * (2.0 / op->h[2]));
+  if (a.cellbuf) {
+    CellArgs<T> ac = a;
+    ac.cells = op->d.cell_pack;
+    const int nitems = op->E * ncoltiles;
+    const dim3 grid(valu_grid<k_cell_valu<T, NP, NQ, MODE>, kNT<T>>(nitems)), block(kNT<T>);
+    hipLaunchKernelGGL((k_cell_valu<T, NP, NQ, MODE>), grid, block, 0, s, ac, ncoltiles, nitems, fx, fy, fz);
+    PAWFE_HIP(hipGetLastError());
+    constexpr bool step = MODE == kValuStep || MODE == kValuStepC || MODE == kValuGenStep || MODE == kValuGenStepG;
+    return launch_cell_gather<T>(op, ac, step, s);
+  }
   bool wave = false;
   if constexpr (is_wave_mode(MODE)) wave = wave_pays<T, NP, MODE>(op, a.ncols);
   for (int c = 0; c < op->ncolour; ++c) {

@@ -162,6 +162,7 @@ struct pawfe_op {
   // scratch of the stand-alone applies
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
+  bool cell_denied = false;   // no memory for per-cell results in it
   // dense solver handle (rocBLAS handle, opaque here)
   void* blas = nullptr;
   // fork/join events of the filter's overlap of column blocks (the block

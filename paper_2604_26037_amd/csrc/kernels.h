@@ -36,6 +36,10 @@ struct CellArgs {
   int64_t ldy64;
   const double* lamY;    // per-column Lambda_Y
   double sa, sac, szz;   // a, a c, zeta zeta'
+  // launches of all cells at once: each cell's result goes to its own rows
+  // [E][nloc][ncols] here and k_cell_gather adds them up per DOF (null: one
+  // launch per cell colour, results added into Y)
+  T* cellbuf;
   const T* frho;         // general step: [E][6] face factors (x lo, x hi, y lo, y hi, z lo, z hi)
 };
 
@@ -61,9 +65,22 @@ struct DensArgs {
 //  bf3: (FP32 only) the cell contractions as bf16x3 split products on the
 //  bf16 matrix cores, FP32 accumulation.
 //  overwrite: Y = alpha * A_loc X instead, whatever Y held (not with bf3).
+//  cellbuf: room for every cell's result (cell_buf_bytes), or null.
 template <typename T>
 pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy, int ncols,
-                         const double* lam, double alpha, hipStream_t s, bool bf3 = false, bool overwrite = false);
+                         const double* lam, double alpha, hipStream_t s, bool bf3 = false, bool overwrite = false,
+                         void* cellbuf = nullptr);
+
+// Bytes of the per-cell results of a block of ncols real columns where a launch
+// of all cells and a gather pay against one launch per cell colour, else 0.
+size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem);
+// the most of any block of up to ncols columns, FP64 or FP32
+size_t cell_buf_most(const pawfe_op* op, int64_t ncols);
+
+// Y of a launch with a.cellbuf: the sum of the cells' results per DOF, plus Y
+// (a.own null), alone (a.own set), or plus the node part of the filter's step.
+template <typename T>
+pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, hipStream_t s);
 
 // bf16x3 split products on the matrix cores (kernels_cell_mfma.hip): K + V
 // (kModeH), the mass term (kModeMass) and the imaginary k term (kModeImg) of
@@ -92,7 +109,8 @@ pawfe_status launch_cell_gen(const pawfe_op* op, int mode, const CellArgs<T>& a,
 bool cell_step_available(const pawfe_op* op);
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
-                              const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s);
+                              const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
+                              void* cellbuf = nullptr);
 
 // the same on general operators (kernels_cell_step_gen.hip; the arguments
 // already carry the per-cell tables)

@@ -108,7 +108,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 template <typename T>
 pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy,
-                         int ncols, const double* lam, double alpha, hipStream_t s, bool bf3, bool overwrite) {
+                         int ncols, const double* lam, double alpha, hipStream_t s, bool bf3, bool overwrite,
+                         void* cellbuf) {
   if (ncols <= 0) return PAWFE_OK;
   if (bf3 && overwrite) return fail(PAWFE_EUNSUPPORTED, "internal: the matrix-core cell kernel adds to Y");
   if (bf3 && sizeof(T) != 4) return fail(PAWFE_EINVAL, "bf16x3 needs FP32 data");
@@ -127,6 +128,7 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   a.n1 = op->n[1];
   a.n2 = op->n[2];
   a.own = overwrite ? op->d.cell_own : nullptr;
+  a.cellbuf = bf3 ? nullptr : (T*)cellbuf;
   if (op->general) {   // graded mesh / GGA term: every local term on the vector-ALU variants
     if (bf3) return fail(PAWFE_EUNSUPPORTED, "bf16x3 is not built for graded meshes or the GGA term");
     return launch_cell_gen<T>(op, mode, a, s);
@@ -145,10 +147,113 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   return launch_cell_mfma<T>(op, kModeImg, a, s);
 }
 
+// Y[I][n] = sum over the (up to eight) cells sharing DOF I of their results,
+// in a fixed order: with KIND 1 plus Y, with KIND 2 (the filter's step) plus
+// -a c X - zeta zeta' Y + a lamY_n Yres (the last product and sum in FP64,
+// rounded once).  CW lanes share a row (its cells are found once per lane and
+// serve all of its columns); all loads are issued before the sum.
+template <typename T, int KIND, int P>
+__global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, int M) {
+  constexpr int NP = P + 1, NL = NP * NP * NP;
+  const int CW = 1 << cw_log;
+  const int I = (int)blockIdx.x * (256 >> cw_log) + (int)(threadIdx.x >> cw_log);
+  if (I >= M) return;
+  const int Gx = A.n0 * P, Gy = A.n1 * P;
+  const int g[3] = {I % Gx, (I / Gx) % Gy, I / (Gx * Gy)}, nc[3] = {A.n0, A.n1, A.n2};
+  int cell[3][2], node[3][2];
+  bool two[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    cell[d][0] = g[d] / P;
+    node[d][0] = g[d] - cell[d][0] * P;
+    two[d] = node[d][0] == 0;                                     // also the last node of the cell before
+    cell[d][1] = cell[d][0] == 0 ? nc[d] - 1 : cell[d][0] - 1;
+    node[d][1] = P;
+  }
+  int64_t off[8];
+  bool on[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int i = k & 1, j = (k >> 1) & 1, l = k >> 2;
+    on[k] = (!i || two[0]) && (!j || two[1]) && (!l || two[2]);
+    const int e = cell[0][i] + A.n0 * (cell[1][j] + A.n1 * cell[2][l]);
+    const int q = node[0][i] + NP * (node[1][j] + NP * node[2][l]);
+    off[k] = ((int64_t)e * NL + q) * A.ncols;
+  }
+  for (int n = threadIdx.x & (CW - 1); n < A.ncols; n += CW) {
+    T v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = on[k] ? A.cellbuf[off[k] + n] : T(0);
+    T* y = A.Y + (int64_t)I * A.ldy + n;
+    T base = T(0);
+    if constexpr (KIND == 1) base = *y;
+    if constexpr (KIND == 2) {
+      const T part = (T)(-A.sac) * A.X[(int64_t)I * A.ldx + n] - (T)A.szz * *y;
+      base = (T)((double)part + A.y64[(int64_t)I * A.ldy64 + n] * (A.sa * A.lamY[n]));
+    }
+    T s = T(0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+    *y = base + s;
+  }
+}
+
+// One launch per colour is latency (4-10 us each, 8 to 27 of them) until a
+// colour holds several thousand cell columns; below that one launch of all
+// cells and a gather pay.  K + V, launches per colour against launch and
+// gather: degree 6, 64 cells in 8 colours, FP64 76 -> 27 us at 500 cell columns
+// per colour, 118 -> 88 at 3,000; 512 cells 159 -> 149 at 4,500 and 197 -> 210
+// at 7,000 (FP32 114 -> 94 and 129 -> 118); 125 cells in 27 colours FP32
+// 235 -> 55 at 1,000; degree 2, 512 cells, FP64 41 -> 33 at 4,500 and 41 -> 45
+// at 7,000.  The bytes bound the scratch (142 MB: 296 -> 208 us).
+constexpr int64_t kCellBufCols = 4500, kCellBufBytes = int64_t(192) << 20;
+
+size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem) {
+  if (op->nq != op->p + 2 || op->p < 2 || op->p > 6 || ncols <= 0) return 0;
+  const int64_t bytes = (int64_t)op->E * op->nloc * ncols * (int64_t)elem;
+  return (int64_t)op->E * ncols <= kCellBufCols * op->ncolour && bytes <= kCellBufBytes ? (size_t)bytes : 0;
+}
+
+size_t cell_buf_most(const pawfe_op* op, int64_t ncols) {
+  const int64_t fits = std::min(ncols, kCellBufCols * op->ncolour / op->E);   // columns that the first bound admits
+  size_t most = 0;
+  for (const int64_t elem : {4, 8}) {
+    const int64_t held = kCellBufBytes / ((int64_t)op->E * op->nloc * elem);   // and the second
+    most = std::max(most, cell_buf_bytes(op, std::min(fits, held), (size_t)elem));
+  }
+  return most;
+}
+
+template <typename T>
+pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, hipStream_t s) {
+  int cw = 2;   // lanes per row: the columns, at most a wave
+  while (cw < 6 && (1 << cw) < a.ncols) ++cw;
+  const int rows = 256 >> cw;
+  const dim3 grid((unsigned)((op->M + rows - 1) / rows)), block(256);
+  auto go = [&](auto p) {
+    constexpr int P = decltype(p)::value;
+    if (step) hipLaunchKernelGGL((k_cell_gather<T, 2, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else if (a.own) hipLaunchKernelGGL((k_cell_gather<T, 0, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else hipLaunchKernelGGL((k_cell_gather<T, 1, P>), grid, block, 0, s, a, cw, (int)op->M);
+  };
+  switch (op->p) {
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 6: go(std::integral_constant<int, 6>{}); break;
+    default: return fail(PAWFE_EUNSUPPORTED, "degree not compiled");
+  }
+  PAWFE_HIP(hipGetLastError());
+  return PAWFE_OK;
+}
+template pawfe_status launch_cell_gather<double>(const pawfe_op*, const CellArgs<double>&, bool, hipStream_t);
+template pawfe_status launch_cell_gather<float>(const pawfe_op*, const CellArgs<float>&, bool, hipStream_t);
+
 template pawfe_status launch_cell<double>(const pawfe_op*, int, const double*, int64_t, double*, int64_t,
-                                          int, const double*, double, hipStream_t, bool, bool);
+                                          int, const double*, double, hipStream_t, bool, bool, void*);
 template pawfe_status launch_cell<float>(const pawfe_op*, int, const float*, int64_t, float*, int64_t,
-                                         int, const double*, double, hipStream_t, bool, bool);
+                                         int, const double*, double, hipStream_t, bool, bool, void*);
 
 pawfe_status launch_density(const pawfe_op* op, const double* X, int64_t ldx, int ncols,
                             const double* occ, double* out, hipStream_t s) {

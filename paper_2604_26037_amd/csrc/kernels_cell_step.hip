@@ -23,7 +23,8 @@ bool cell_step_available(const pawfe_op* op) {
 
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
-                              const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s) {
+                              const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
+                              void* cellbuf) {
   if (ncols <= 0) return PAWFE_OK;
   if (!cell_step_available(op)) return fail(PAWFE_EUNSUPPORTED, "internal: no step variant for this operator");
   if (ld < ncols || ldy < ncols || ld * (int64_t)sizeof(T) >= (int64_t(1) << 32))
@@ -41,6 +42,7 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
   c.n1 = op->n[1];
   c.n2 = op->n[2];
   c.own = op->d.cell_own;
+  c.cellbuf = (T*)cellbuf;
   c.y64 = Y;
   c.ldy64 = ldy;
   c.lamY = lamY;
@@ -73,8 +75,9 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
 }
 
 template pawfe_status launch_cell_step<float>(const pawfe_op*, const float*, float*, int64_t, const double*, int64_t,
-                                              const double*, double, double, double, int, hipStream_t);
+                                              const double*, double, double, double, int, hipStream_t, void*);
 template pawfe_status launch_cell_step<double>(const pawfe_op*, const double*, double*, int64_t, const double*,
-                                               int64_t, const double*, double, double, double, int, hipStream_t);
+                                               int64_t, const double*, double, double, double, int, hipStream_t,
+                                               void*);
 
 }  // namespace pawfe
