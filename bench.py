@@ -35,7 +35,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_VALU_F32_TFLOPS = 157.3
 # the same without packed FP32 instructions (also the FP64 vector peak)
 PEAK_VALU_F32_SCALAR_TFLOPS = 78.6
-CELL_KERNEL_SRC = os.path.join(ROOT, "paper_2604_26037_amd", "csrc", "cell_valu.h")
+CELL_KERNEL_SRCS = [os.path.join(ROOT, "paper_2604_26037_amd", "csrc", f) for f in ("cell_valu.h", "cell_wave.h")]
 # node part of the fused step per DOF-column: -ac x, -zz y, their sum, and
 # the FP64 a lamY Y product-sum
 STEP_NODE_FLOPS = 5
@@ -53,11 +53,11 @@ def local_flops_per_cell_col(np1, nq):
 def measured_traffic():
     """HBM bytes per launch of the cell kernel from the committed counter
     summary (FETCH_SIZE + WRITE_SIZE, copy-calibrated), or None when the
-    kernel source changed since the counters were taken."""
+    kernel's sources changed since the counters were taken."""
     import hashlib
     try:
         text = open(COUNTERS_FILE).read()
-        src = hashlib.sha256(open(CELL_KERNEL_SRC, "rb").read()).hexdigest()
+        src = hashlib.sha256(b"".join(open(f, "rb").read() for f in CELL_KERNEL_SRCS)).hexdigest()
     except OSError:
         return None
     fields = {}
@@ -711,7 +711,7 @@ def main():
     t_launch = step_t["fp32"]
     achieved = per_launch_flops / t_launch / 1e12
     roof = {
-        "kernel": "k_cell_valu<float,7,8,Step> (filter step: cell-local K + V on M_D^-1 R_Y, node part at the "
+        "kernel": "k_cell_wave<float,7,8,Step> (filter step: cell-local K + V on M_D^-1 R_Y, node part at the "
                   "first visit; one colour per launch)",
         "bound": "alu",
         "achieved": achieved,
