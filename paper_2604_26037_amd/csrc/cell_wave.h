@@ -48,6 +48,12 @@ struct Wave {
   static constexpr int QB = (NQ + H - 1) / H;                     // Gauss columns of a half plane
   static constexpr int NPX = RB * H, NQX = QB * H;
   static constexpr int slab = NQ * NQ * NP * CB;
+  // slab element of line 0 in a lane's plane (lanes past the last plane: the
+  // last one, which they may read; line L adds L NP CB)
+  static constexpr __host__ __device__ int plane_at(int lane) {
+    const int s = (lane / CB) % PS;
+    return (s < NP ? s : NP - 1) * CB + lane % CB;
+  }
 };
 // Waves (neighbouring column tiles of one cell) per workgroup.  The mass term,
 // which is all memory, takes four: they read the same 128-byte lines through
@@ -226,7 +232,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   };
 
   // slab addresses
-  T* const pb = sl + slot * CB + col;                        // plane accesses: + line * NP CB
+  T* const pb = sl + W::plane_at(lane);                      // plane accesses: + line * NP CB
   T* const zb = sl + g * NP * CB + col;                      // line accesses: + round * G NP CB + plane * CB
   constexpr int LS = NP * CB;
 
@@ -366,7 +372,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     wave_lds_order();
     // s_n = -1 on real, +1 on imaginary columns, of the partner column's term
     const T sg = (col & 1) ? T(1) : T(-1);
-    const T* const pp = sl + slot * CB + (col ^ 1);
+    const T* const pp = sl + W::plane_at(lane ^ 1);
     sfor<RB>([&](auto r) {
       const int b = lrow(r);
       sfor<NP>([&](auto a) {

@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int ci = e % A.n0, cj = (e / A.n0) % A.n1, ck = e / (A.n0 * A.n1);
   const int p = NP - 1;
   const int Gx = A.n0 * p, Gy = A.n1 * p, Gz = A.n2 * p;
-  double* const pb = sl + slot * CB + col;
+  double* const pb = sl + W::plane_at(lane);
   double* const zb = sl + g * LS + col;
   double acc[ZR][NQ];
   sfor<ZR>([&](auto i) { sfor<NQ>([&](auto q) { acc[i][q] = 0.0; }); });
