@@ -706,6 +706,9 @@ pawfe_status build_host(const pawfe_op_desc* d, pawfe_op* op) {
     }
     op->item_ptr[a + 1] = (int32_t)op->item_atom.size();
   }
+  // end mark: an atom without support rows reads the offset at its item_ptr,
+  // which for the last atom is one past the items
+  op->item_poff.push_back((int32_t)prow);
   op->nitems = (int)op->item_atom.size();
   op->item_rows_total = prow;
 
