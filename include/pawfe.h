@@ -35,7 +35,14 @@
  *           the operator's tables (allocated by pawfe_build_operator, freed
  *           by pawfe_destroy_operator) and a per-operator scratch area for
  *           the stand-alone applies.  Calls on one operator must not run
- *           concurrently (they share that scratch).
+ *           concurrently (they share that scratch).  Applies of H and S,
+ *           the gradient and the Lanczos bounds of small problems (up to
+ *           4500 cells x columns per cell colour) also take room for the
+ *           results of every cell: at most 192 MiB for
+ *           the widest such call and below twice that in all, kept until
+ *           the operator is destroyed, never moved, and never taken while
+ *           the stream is captured or when the device has no room (the call
+ *           then runs one launch per cell colour).
  */
 #ifndef PAWFE_H
 #define PAWFE_H

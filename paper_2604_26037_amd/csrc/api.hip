@@ -93,14 +93,44 @@ pawfe_status ensure_scratch(pawfe_op* op, size_t bytes) {
   return PAWFE_OK;
 }
 
-// Scratch of an operator with room for per-cell results (`cell` bytes besides
-// `least`), or without, from then on, where the allocation fails.
-pawfe_status ensure_scratch_cell(pawfe_op* op, size_t least, size_t cell) {
-  if (op->cell_denied) return ensure_scratch(op, least);
-  if (ensure_scratch(op, least + cell) == PAWFE_OK) return PAWFE_OK;
-  (void)hipGetLastError();
-  op->cell_denied = true;
-  return ensure_scratch(op, least);
+// Room for the per-cell results of a stand-alone call (cell_buf_bytes of its
+// columns), or null: the call then runs one launch per cell colour.  An
+// allocation of its own that stays where it is until the operator is destroyed
+// (a captured graph may hold it): growing takes another one, at least twice as
+// large, so all of them together stay below twice the largest.  It is not grown
+// while `s` is captured, and a size that the device could not give is not asked
+// for again.
+void* cell_room(pawfe_op* op, size_t bytes, hipStream_t s) {
+  if (!bytes) return nullptr;
+  if (bytes <= op->cell_bytes) return op->cell;
+  if (op->cell_denied && bytes >= op->cell_denied) return nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  try {
+    op->allocations.reserve(op->allocations.size() + 1);
+  } catch (...) {
+    return nullptr;
+  }
+  // a capture on another thread is not disturbed by an allocation here
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void* p = nullptr;
+  size_t n = std::max(bytes, std::min(2 * op->cell_bytes, cell_buf_limit()));
+  hipError_t e = hipMalloc(&p, n);
+  if (e != hipSuccess && n > bytes) e = hipMalloc(&p, n = bytes);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (e == hipErrorOutOfMemory) op->cell_denied = bytes;
+    return nullptr;
+  }
+  op->allocations.push_back(p);
+  op->cell = p;
+  op->cell_bytes = n;
+  return p;
 }
 
 struct NlBufs {
@@ -186,14 +216,12 @@ pawfe_status apply_entry(const pawfe_op* cop, int which, const void* X, int64_t 
   const int64_t chunk = 512;
   const int64_t cmax = std::min<int64_t>(chunk, nvec);
   const size_t elem = prec == PAWFE_FP64 ? 8 : 4;
-  // room for any smaller call and both types: a graph that holds this call
-  // keeps the scratch that it was captured with whatever narrower calls follow
-  CHECK(ensure_scratch_cell(op, nl_scratch_bytes(op, cmax), align256(cell_buf_most(op, cmax))));
+  CHECK(ensure_scratch(op, nl_scratch_bytes(op, cmax)));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs b = carve_nl(op, cv, cmax);
-  carve_cell(op, cv, cmax, elem, b);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: apply scratch smaller than its carve");
   hipStream_t s = S(stream);
+  if (which != 2 && prec != PAWFE_BF16X3) b.cell = cell_room(op, cell_buf_bytes(op, cmax, elem), s);
   for (int64_t j0 = 0; j0 < nvec; j0 += chunk) {
     const int nc = (int)std::min<int64_t>(chunk, nvec - j0);
     if (prec == PAWFE_FP64)
@@ -1416,19 +1444,19 @@ pawfe_status pawfe_band_energy_grad(const pawfe_op* cop, const void* Xv, int64_t
   const int64_t nchunks = (op->M + 4095) / 4096;
   size_t need = nl_scratch_bytes(op, std::max<int64_t>(N, B)) + align256((size_t)op->M * B * 8) +
                 align256((size_t)nchunks * B * 8) + align256((size_t)N * 8) + 1024;
-  CHECK(ensure_scratch_cell(op, need, align256(cell_buf_most(op, 512))));
+  CHECK(ensure_scratch(op, need));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs nb = carve_nl(op, cv, std::max<int64_t>(N, B));
   double* HXb = cv.take<double>((size_t)op->M * B);
   double* pbuf = cv.take<double>((size_t)nchunks * B);
   double* occ2 = cv.take<double>((size_t)N);
-  carve_cell(op, cv, B, 8, nb);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: gradient scratch smaller than its carve");
   if (op->cplx && occ) {
     CHECK(launch_dup_pairs(occ, occ2, (int)Nc, s));
     occ = occ2;
   }
   if (E) {
+    nb.cell = cell_room(op, cell_buf_bytes(op, B, 8), s);
     CHECK(launch_fill<double>(E, 1, 0.0, s));
     for (int64_t j0 = 0; j0 < N; j0 += B) {
       const int nc = (int)std::min<int64_t>(B, N - j0);
@@ -1459,7 +1487,7 @@ pawfe_status pawfe_lanczos_bounds(const pawfe_op* cop, int32_t k, uint64_t seed,
   const int64_t M = op->M * cf;
   const int64_t nchunks = (M + 4095) / 4096;
   size_t need = nl_scratch_bytes(op, cf) + 5 * align256((size_t)M * 8) + align256((size_t)nchunks * 8) + 1024;
-  CHECK(ensure_scratch_cell(op, need, align256(cell_buf_most(op, cf))));
+  CHECK(ensure_scratch(op, need));
   Carve cv(op->scratch, op->scratch_bytes);
   NlBufs nb = carve_nl(op, cv, cf);
   double* v = cv.take<double>(M);
@@ -1469,8 +1497,8 @@ pawfe_status pawfe_lanczos_bounds(const pawfe_op* cop, int32_t k, uint64_t seed,
   double* u = cv.take<double>(M);
   double* pbuf = cv.take<double>(nchunks);
   double* dot = cv.take<double>(2);
-  carve_cell(op, cv, cf, 8, nb);
   if (!cv.ok()) return fail(PAWFE_EINVAL, "internal: Lanczos scratch smaller than its carve");
+  nb.cell = cell_room(op, cell_buf_bytes(op, cf, 8), s);
   // seeded start vector (splitmix64 -> uniform(-1, 1)), generated on the host
   std::vector<double> h(M);
   uint64_t st = seed;

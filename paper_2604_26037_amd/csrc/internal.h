@@ -162,7 +162,9 @@ struct pawfe_op {
   // scratch of the stand-alone applies
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
-  bool cell_denied = false;   // no memory for per-cell results in it
+  // room for their per-cell results (one of `allocations`)
+  void* cell = nullptr;
+  size_t cell_bytes = 0, cell_denied = 0;   // cell_denied: a size that could not be had (0: none)
   // dense solver handle (rocBLAS handle, opaque here)
   void* blas = nullptr;
   // fork/join events of the filter's overlap of column blocks (the block

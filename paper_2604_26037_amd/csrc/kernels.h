@@ -74,8 +74,8 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
 // Bytes of the per-cell results of a block of ncols real columns where a launch
 // of all cells and a gather pay against one launch per cell colour, else 0.
 size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem);
-// the most of any block of up to ncols columns, FP64 or FP32
-size_t cell_buf_most(const pawfe_op* op, int64_t ncols);
+// no result of it is larger
+size_t cell_buf_limit();
 
 // Y of a launch with a.cellbuf: the sum of the cells' results per DOF, plus Y
 // (a.own null), alone (a.own set), or plus the node part of the filter's step.

@@ -214,15 +214,7 @@ size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem) {
   return (int64_t)op->E * ncols <= kCellBufCols * op->ncolour && bytes <= kCellBufBytes ? (size_t)bytes : 0;
 }
 
-size_t cell_buf_most(const pawfe_op* op, int64_t ncols) {
-  const int64_t fits = std::min(ncols, kCellBufCols * op->ncolour / op->E);   // columns that the first bound admits
-  size_t most = 0;
-  for (const int64_t elem : {4, 8}) {
-    const int64_t held = kCellBufBytes / ((int64_t)op->E * op->nloc * elem);   // and the second
-    most = std::max(most, cell_buf_bytes(op, std::min(fits, held), (size_t)elem));
-  }
-  return most;
-}
+size_t cell_buf_limit() { return (size_t)kCellBufBytes; }
 
 template <typename T>
 pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, hipStream_t s) {
