@@ -293,19 +293,26 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     typedef const __attribute__((address_space(4))) unsigned* ConstUP;
     cm = ((ConstUP)A.own)[e] >> (c == 0 ? 0 : (c == NP - 1 ? 18 : 9));
   }
-  // step: the rows' part of the node update (-a c R_Y' at first visits)
-  if constexpr (STEP) {
+  // step: the rows' part of the node update, -a c R_Y' at first visits.  FP32
+  // adds it to the whole local sum at the end: added here, between the V and
+  // the K terms, it costs a filter of degree 20 up to 12 % in accuracy (degree 6
+  // complex 4.79e-7 -> 5.38e-7 from the workgroup kernel's order, 4.50e-7 at
+  // the end).  FP64 has no registers left to carry x that far (5.76 -> 6.44 ms
+  // on 8000 cells x 256 columns) and shows no difference.
+  constexpr bool kLateX = STEP && sizeof(T) == 4;
+  auto add_x = [&](auto r) {
     const T mac = (T)(-A.sac);
+    const unsigned cr = cm >> row_class(r);
+    const T m0 = cr & 1u ? mac : T(0), m1 = cr & 2u ? mac : T(0), m2 = cr & 4u ? mac : T(0);
+    sfor<NP>([&](auto a) { acc[r][a] = fma_t(a == 0 ? m0 : (a == NP - 1 ? m2 : m1), x[r][a], acc[r][a]); });
+  };
+  if constexpr (STEP) {
     sfor<RB>([&](auto r) {
-      // opaque: the products are formed here, not kept beside x from the load
-      // on, and the sums not left until the end
+      // opaque: products of x are formed here or at the end, not kept beside
+      // it from the load on, and the sums not left until the end
       sfor<NP>([&](auto a) { opaque(x[r][a]); });
-      const unsigned cr = cm >> row_class(r);
-      const T m0 = cr & 1u ? mac : T(0), m1 = cr & 2u ? mac : T(0), m2 = cr & 4u ? mac : T(0);
-      sfor<NP>([&](auto a) {
-        acc[r][a] = fma_t(a == 0 ? m0 : (a == NP - 1 ? m2 : m1), x[r][a], acc[r][a]);
-        opaque(acc[r][a]);
-      });
+      if constexpr (!kLateX) add_x(r);
+      sfor<NP>([&](auto a) { opaque(acc[r][a]); });
     });
   }
   constexpr int ZK = (NP2 + G - 1) / G;
@@ -483,7 +490,10 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     const char* q = rowptr(y6, ld64b, r);
     first_visits(r, [&](auto a) { yr[r][a] = *(const double*)(q + x64[a]); });
   };
-  constexpr int kAhead = sizeof(T) == 4 ? 2 : 1;   // rows ahead (4 and 2: 1 % slower)
+  // rows ahead, as many as fit the registers (degree 6 FP32, 8000 cells x 256
+  // columns: 3.10 ms with none, 3.12 with one, 3.43 and spills with two; complex
+  // 1.91, 1.88 and 1.98 on 4096 cells; degree 5 1.12, 1.09 and 1.06 ms)
+  constexpr int kAhead = sizeof(T) == 8 || (NP == 7 && CPLX) ? 1 : (NP == 7 ? 0 : 2);
   if constexpr (STEP) sfor<kAhead>([&](auto r) { load_y(r); });
   if constexpr (!MASS) {
     sfor<ZK>([&](auto i) {
@@ -502,6 +512,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       const T k = pb[(b * NP + a) * LS];
       if constexpr (MASS) acc[r][a] = k; else acc[r][a] += k;
     });
+    if constexpr (kLateX) add_x(r);
   });
   // ---- assembly ----------------------------------------------------------
   const double ly = STEP ? A.sa * A.lamY[nn] : 0.0;
