@@ -765,11 +765,19 @@ k_nl_fixup(int nshared, int ncols, const double* __restrict__ v1, double s1,
       auto body = [&](auto full) {
         coeffs(full, d.poff[a], npj);
 #pragma unroll
-        for (int u = 0; u < kFixUnroll; ++u) dot(full, e[1 + u], npj, c1[u], c2[u]);
+        for (int u = 0; u < kFixUnroll; ++u) {
+          dot(full, e[1 + u], npj, c1[u], c2[u]);
+          // FP64 rows of an FP32 filter: the atoms' terms are summed in FP64
+          if constexpr (sizeof(TO1) > sizeof(TR)) {
+            if constexpr (MINV) c1[u] *= Minv[I[u]];
+            o1[u] += (TO1)c1[u];
+            c1[u] = TR(0);
+          }
+        }
       };
       if (npj == NPJ) body(std::true_type{}); else body(std::false_type{});
     }
-    store_rows(I, d.fixs_nrow[blockIdx.x]);
+    store_rows(I, d.fixs_nrow[blockIdx.x]);   // (c1 is zero where the terms are in o1)
     return;
   }
   const int item = blockIdx.x - nshared;
