@@ -1134,8 +1134,10 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       if constexpr (STEP && GEN) f = f / idet;   // the cell's det J of M_D^{-1}
       if constexpr (MASS) f = f * idet * (A.lam ? (T)(-A.lam[n]) : T(1));
       auto result = [&](int j) {
-        return f * *reinterpret_cast<const T*>(reinterpret_cast<const char*>(sK) + k_of_u(pk[j] & ((1u << kLdsBits) - 1)));
+        return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(sK) + k_of_u(pk[j] & ((1u << kLdsBits) - 1)));
       };
+      // the products and sums below are spelled out as k_cell_gather's, which
+      // repeats them on the stored results (the factor f with them)
       if (to_buf) {
         T* out = A.cellbuf + ((int64_t)cp.e * NL + slot) * A.ncols + n;
 #pragma unroll
@@ -1150,22 +1152,22 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
           //   Y <- (-ac X - zz Y) + a lamY_n Yres
           // the last product and sum in FP64, rounded once
           if constexpr (kLateYo) {
-  #pragma unroll
+#pragma unroll
             for (int j = 0; j < NJ; ++j) yo[j] = lreal(j) ? *elem(A.Y, ldyb, n, node[j]) : T(0);
           }
           if constexpr (!kEarlyY) step_loads(node);
           const double ly = A.sa * A.lamY[n];
           const T mac = (T)(-A.sac), zz = (T)A.szz;
-  #pragma unroll
+#pragma unroll
           for (int j = 0; j < NJ; ++j) {   // branch-free: a select per node
-            const T part = mac * sxv[j] - zz * yo[j];
-            const T upd = (T)((double)part + syf[j] * ly);
+            const T part = fma_t(mac, sxv[j], -(zz * yo[j]));
+            const T upd = (T)fma(syf[j], ly, (double)part);
             yo[j] = ((sown >> j) & 1u) ? upd : yo[j];
           }
         }
-  #pragma unroll
+#pragma unroll
         for (int j = 0; j < NJ; ++j)
-          if (lreal(j)) *elem(A.Y, ldyb, n, node[j]) = yo[j] + result(j);
+          if (lreal(j)) *elem(A.Y, ldyb, n, node[j]) = fma_t(f, result(j), yo[j]);
       }
     }
     __syncthreads();
@@ -1225,11 +1227,16 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     const dim3 grid(valu_grid<k_cell_valu<T, NP, NQ, MODE>, kNT<T>>(nitems)), block(kNT<T>);
     hipLaunchKernelGGL((k_cell_valu<T, NP, NQ, MODE>), grid, block, 0, s, ac, ncoltiles, nitems, fx, fy, fz);
     PAWFE_HIP(hipGetLastError());
-    constexpr bool step = MODE == kValuStep || MODE == kValuStepC || MODE == kValuGenStep || MODE == kValuGenStepG;
-    return launch_cell_gather<T>(op, ac, step, s);
+    constexpr bool gen_step = MODE == kValuGenStep || MODE == kValuGenStepG;
+    constexpr bool step = MODE == kValuStep || MODE == kValuStepC || gen_step;
+    constexpr bool mass = MODE == kValuMass || MODE == kValuGenMass;
+    return launch_cell_gather<T>(op, ac, step, mass ? kByMass : gen_step ? kByDetJ : kByAlpha, s);
   }
+  // without the room that it would have, a block takes the workgroup kernel
+  // colour by colour, whose result is the gather's bit for bit
   bool wave = false;
-  if constexpr (is_wave_mode(MODE)) wave = wave_pays<T, NP, MODE>(op, a.ncols);
+  if constexpr (is_wave_mode(MODE))
+    wave = !(a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T))) && wave_pays<T, NP, MODE>(op, a.ncols);
   for (int c = 0; c < op->ncolour; ++c) {
     const int c0 = op->colour_off[c], c1 = op->colour_off[c + 1];
     if (c1 == c0) continue;

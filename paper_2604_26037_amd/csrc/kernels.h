@@ -38,8 +38,11 @@ struct CellArgs {
   double sa, sac, szz;   // a, a c, zeta zeta'
   // launches of all cells at once: each cell's result goes to its own rows
   // [E][nloc][ncols] here and k_cell_gather adds them up per DOF (null: one
-  // launch per cell colour, results added into Y)
+  // launch per cell colour, results added into Y).  gathers: the caller gives
+  // that room to blocks that want it where it can; the result is the same
+  // either way
   T* cellbuf;
+  bool gathers;
   const T* frho;         // general step: [E][6] face factors (x lo, x hi, y lo, y hi, z lo, z hi)
 };
 
@@ -78,9 +81,12 @@ size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem);
 size_t cell_buf_limit();
 
 // Y of a launch with a.cellbuf: the sum of the cells' results per DOF, plus Y
-// (a.own null), alone (a.own set), or plus the node part of the filter's step.
+// (a.own null), alone (a.own set), or plus the node part of the filter's step;
+// each result times its factor: alpha (kByAlpha), alpha / det J of the cell
+// (kByDetJ: general steps) or alpha det J [-lambda_n] (kByMass).
+enum CellFactor { kByAlpha, kByDetJ, kByMass };
 template <typename T>
-pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, hipStream_t s);
+pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, CellFactor fk, hipStream_t s);
 
 // bf16x3 split products on the matrix cores (kernels_cell_mfma.hip): K + V
 // (kModeH), the mass term (kModeMass) and the imaginary k term (kModeImg) of
@@ -110,7 +116,7 @@ bool cell_step_available(const pawfe_op* op);
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
                               const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
-                              void* cellbuf = nullptr);
+                              bool gathers = false, void* cellbuf = nullptr);
 
 // the same on general operators (kernels_cell_step_gen.hip; the arguments
 // already carry the per-cell tables)

@@ -129,6 +129,7 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   a.n2 = op->n[2];
   a.own = overwrite ? op->d.cell_own : nullptr;
   a.cellbuf = bf3 ? nullptr : (T*)cellbuf;
+  a.gathers = overwrite;
   if (op->general) {   // graded mesh / GGA term: every local term on the vector-ALU variants
     if (bf3) return fail(PAWFE_EUNSUPPORTED, "bf16x3 is not built for graded meshes or the GGA term");
     return launch_cell_gen<T>(op, mode, a, s);
@@ -147,12 +148,16 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   return launch_cell_mfma<T>(op, kModeImg, a, s);
 }
 
-// Y[I][n] = sum over the (up to eight) cells sharing DOF I of their results,
-// in a fixed order: with KIND 1 plus Y, with KIND 2 (the filter's step) plus
-// -a c X - zeta zeta' Y + a lamY_n Yres (the last product and sum in FP64,
-// rounded once).  CW lanes share a row (its cells are found once per lane and
-// serve all of its columns); all loads are issued before the sum.
-template <typename T, int KIND, int P>
+// Y[I][n] = sum over the (up to eight) cells sharing DOF I of their results
+// times their factors (CellFactor F), added one after another in the order of
+// the cells' colours to 0 (KIND 0), to Y (KIND 1) or to the node part of the
+// filter's step (KIND 2: -a c X - zeta zeta' Y + a lamY_n Yres, the last product
+// and sum in FP64, rounded once): product by product what the launches per
+// colour do, so the two give the same bits and a block's result does not depend
+// on whether there was room for this.  CW lanes share a row (its cells are
+// found once per lane and serve all of its columns); all loads are issued
+// before the sum.
+template <typename T, int KIND, int F, int P>
 __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, int M) {
   constexpr int NP = P + 1, NL = NP * NP * NP;
   const int CW = 1 << cw_log;
@@ -164,37 +169,48 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
   bool two[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    cell[d][0] = g[d] / P;
-    node[d][0] = g[d] - cell[d][0] * P;
-    two[d] = node[d][0] == 0;                                     // also the last node of the cell before
-    cell[d][1] = cell[d][0] == 0 ? nc[d] - 1 : cell[d][0] - 1;
-    node[d][1] = P;
+    const int c0 = g[d] / P, q0 = g[d] - c0 * P, c1 = c0 == 0 ? nc[d] - 1 : c0 - 1;
+    two[d] = q0 == 0;                                     // also the last node of the cell before
+    // the cell of the lower colour (i mod 2; the last of an odd direction 2) first
+    auto colour = [&](int i) { return (nc[d] & 1) && i == nc[d] - 1 ? 2 : i & 1; };
+    const bool turn = two[d] && colour(c1) < colour(c0);
+    cell[d][0] = turn ? c1 : c0;
+    node[d][0] = turn ? P : q0;
+    cell[d][1] = turn ? c0 : c1;
+    node[d][1] = turn ? q0 : P;
   }
   int64_t off[8];
   bool on[8];
+  T f[F == kByAlpha ? 1 : 8];
+  if constexpr (F == kByAlpha) f[0] = A.alpha;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < 8; ++k) {   // ascending colours: z most significant
     const int i = k & 1, j = (k >> 1) & 1, l = k >> 2;
     on[k] = (!i || two[0]) && (!j || two[1]) && (!l || two[2]);
     const int e = cell[0][i] + A.n0 * (cell[1][j] + A.n1 * cell[2][l]);
     const int q = node[0][i] + NP * (node[1][j] + NP * node[2][l]);
     off[k] = ((int64_t)e * NL + q) * A.ncols;
+    if constexpr (F == kByDetJ) f[k] = A.alpha / A.geo[4 * e + 3];
+    if constexpr (F == kByMass) f[k] = A.alpha * (A.geo ? A.geo[4 * e + 3] : A.detJ);
   }
   for (int n = threadIdx.x & (CW - 1); n < A.ncols; n += CW) {
     T v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = on[k] ? A.cellbuf[off[k] + n] : T(0);
     T* y = A.Y + (int64_t)I * A.ldy + n;
-    T base = T(0);
-    if constexpr (KIND == 1) base = *y;
-    if constexpr (KIND == 2) {
-      const T part = (T)(-A.sac) * A.X[(int64_t)I * A.ldx + n] - (T)A.szz * *y;
-      base = (T)((double)part + A.y64[(int64_t)I * A.ldy64 + n] * (A.sa * A.lamY[n]));
-    }
     T s = T(0);
+    if constexpr (KIND == 1) s = *y;
+    if constexpr (KIND == 2) {
+      const T part = fma_t((T)(-A.sac), A.X[(int64_t)I * A.ldx + n], -((T)A.szz * *y));
+      s = (T)fma(A.y64[(int64_t)I * A.ldy64 + n], A.sa * A.lamY[n], (double)part);
+    }
+    const T w = F == kByMass && A.lam ? (T)(-A.lam[n]) : T(1);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += v[k];
-    *y = base + s;
+    for (int k = 0; k < 8; ++k) {
+      const T fk = F == kByAlpha ? f[0] : (F == kByMass ? f[k] * w : f[k]);
+      s = fma_t(fk, v[k], s);   // (a cell that is not there adds zero)
+    }
+    *y = s;
   }
 }
 
@@ -217,16 +233,19 @@ size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem) {
 size_t cell_buf_limit() { return (size_t)kCellBufBytes; }
 
 template <typename T>
-pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, hipStream_t s) {
+pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, CellFactor fk, hipStream_t s) {
+  if (!step && fk != kByMass && !a.own) return fail(PAWFE_EUNSUPPORTED, "internal: no gather that adds to Y");
   int cw = 2;   // lanes per row: the columns, at most a wave
   while (cw < 6 && (1 << cw) < a.ncols) ++cw;
   const int rows = 256 >> cw;
   const dim3 grid((unsigned)((op->M + rows - 1) / rows)), block(256);
   auto go = [&](auto p) {
     constexpr int P = decltype(p)::value;
-    if (step) hipLaunchKernelGGL((k_cell_gather<T, 2, P>), grid, block, 0, s, a, cw, (int)op->M);
-    else if (a.own) hipLaunchKernelGGL((k_cell_gather<T, 0, P>), grid, block, 0, s, a, cw, (int)op->M);
-    else hipLaunchKernelGGL((k_cell_gather<T, 1, P>), grid, block, 0, s, a, cw, (int)op->M);
+    if (step && fk == kByDetJ) hipLaunchKernelGGL((k_cell_gather<T, 2, kByDetJ, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else if (step) hipLaunchKernelGGL((k_cell_gather<T, 2, kByAlpha, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else if (fk == kByMass && a.own) hipLaunchKernelGGL((k_cell_gather<T, 0, kByMass, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else if (fk == kByMass) hipLaunchKernelGGL((k_cell_gather<T, 1, kByMass, P>), grid, block, 0, s, a, cw, (int)op->M);
+    else hipLaunchKernelGGL((k_cell_gather<T, 0, kByAlpha, P>), grid, block, 0, s, a, cw, (int)op->M);
   };
   switch (op->p) {
     case 2: go(std::integral_constant<int, 2>{}); break;
@@ -239,8 +258,9 @@ pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool s
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }
-template pawfe_status launch_cell_gather<double>(const pawfe_op*, const CellArgs<double>&, bool, hipStream_t);
-template pawfe_status launch_cell_gather<float>(const pawfe_op*, const CellArgs<float>&, bool, hipStream_t);
+template pawfe_status launch_cell_gather<double>(const pawfe_op*, const CellArgs<double>&, bool, CellFactor,
+                                                 hipStream_t);
+template pawfe_status launch_cell_gather<float>(const pawfe_op*, const CellArgs<float>&, bool, CellFactor, hipStream_t);
 
 template pawfe_status launch_cell<double>(const pawfe_op*, int, const double*, int64_t, double*, int64_t,
                                           int, const double*, double, hipStream_t, bool, bool, void*);

@@ -24,7 +24,7 @@ bool cell_step_available(const pawfe_op* op) {
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
                               const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
-                              void* cellbuf) {
+                              bool gathers, void* cellbuf) {
   if (ncols <= 0) return PAWFE_OK;
   if (!cell_step_available(op)) return fail(PAWFE_EUNSUPPORTED, "internal: no step variant for this operator");
   if (ld < ncols || ldy < ncols || ld * (int64_t)sizeof(T) >= (int64_t(1) << 32))
@@ -43,6 +43,7 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
   c.n2 = op->n[2];
   c.own = op->d.cell_own;
   c.cellbuf = (T*)cellbuf;
+  c.gathers = gathers;
   c.y64 = Y;
   c.ldy64 = ldy;
   c.lamY = lamY;
@@ -75,9 +76,9 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
 }
 
 template pawfe_status launch_cell_step<float>(const pawfe_op*, const float*, float*, int64_t, const double*, int64_t,
-                                              const double*, double, double, double, int, hipStream_t, void*);
+                                              const double*, double, double, double, int, hipStream_t, bool, void*);
 template pawfe_status launch_cell_step<double>(const pawfe_op*, const double*, double*, int64_t, const double*,
                                                int64_t, const double*, double, double, double, int, hipStream_t,
-                                               void*);
+                                               bool, void*);
 
 }  // namespace pawfe

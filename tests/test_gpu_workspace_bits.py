@@ -1,0 +1,96 @@
+"""The room for per-cell results (one launch of all cells and a gather) changes
+no bit: the gather adds a DOF's cells in the order of their colours, product by
+product what the launches per colour do.  A filter gives the same result in the
+smallest workspace (no room), with room and with more blocks in flight, and
+Rayleigh-Ritz and the applies (eager with room, static scratch) do too; uniform, graded
+with the GGA term and complex operators, odd meshes (three colours an axis), on
+both sides of the limit."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _system(p, kind, n):
+    from workloads.configs import custom_system, with_two_level_gga
+    kw = dict(kpoint=(0.3, -0.2, 0.45), is_complex=True) if kind == "complex" else {}
+    pos = np.array([[1.0, 2.0, 3.0], [3.4, 0.2, 4.0]])
+    s = custom_system(n, tuple(1.7 * v for v in n), p, p + 2, pos=pos, rcut=1.1, channels="spd8", wells=pos, s_H=0.5,
+                      s_S=0.2, seed=3, **kw)
+    return with_two_level_gga(s, r_fine=0.6, gga=kind == "gga") if kind in ("graded", "gga") else s
+
+
+def _least(call, full):
+    from paper_2604_26037_amd import PawfeError
+    lo, hi = 0, full // 256      # sizes are whole multiples of 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            call(mid * 256)
+            hi = mid
+        except PawfeError:
+            lo = mid
+    return hi * 256
+
+
+@pytest.mark.parametrize("p,kind,n", [(2, "uniform", (3, 4, 3)), (3, "graded", (2, 3, 5)), (4, "complex", (3, 4, 3)),
+                                      (5, "gga", (3, 2, 4)), (6, "uniform", (3, 4, 3)), (6, "graded", (4, 2, 2)),
+                                      (2, "complex", (3, 4, 3))])
+def test_room_changes_no_bit(p, kind, n):
+    from paper_2604_26037_amd import Operator
+    op = Operator(_system(p, kind, n))
+    cplx = kind == "complex"
+    lo, hi, beta = op.lanczos_bounds(12)
+    bU, bW, b0 = hi + beta, lo + 0.3 * (hi - lo), lo - 0.1
+    N = 24
+    X = torch.randn(op.ndof, N, device="cuda", dtype=torch.complex128 if cplx else torch.float64,
+                    generator=torch.Generator(device="cuda").manual_seed(p))
+    lam = torch.linspace(lo, lo + 0.3 * (hi - lo), N, device="cuda", dtype=torch.float64)
+    for prec in ("fp64", "fp32"):
+        for block in (N, 9):
+            run = lambda b: op.cheb_filter(X, lam, 6, b0, bW, bU, block=block, prec=prec, ws=op.workspace(b))  # noqa: E731
+            one, full = op.cheb_filter_workspace(block, block, prec), op.cheb_filter_workspace(N, block, prec)
+            low = _least(run, full)
+            want = run(low)
+            for b in (one, full, 2 * low, 4 * full):
+                assert torch.equal(run(b), want), (prec, block, b)
+        x = X if prec == "fp64" else X.to(torch.complex64 if cplx else torch.float32)
+        # static scratch of 64 MB: its room is the same, without any where it is spent
+        assert torch.equal(op.apply_H_noalloc(x, torch.empty_like(x), prec=prec), op.apply_H(x, prec=prec))
+    run = lambda b: op.rayleigh_ritz(X.clone(), ws=op.workspace(b))[0]  # noqa: E731
+    full = op.rayleigh_ritz_workspace(N)
+    assert torch.equal(run(_least(run, full)), run(full))
+    op.close()
+
+
+@pytest.mark.parametrize("p,kind", [(2, "uniform"), (3, "complex"), (4, "graded"), (6, "gga")])
+def test_apply_in_a_capture_without_room(p, kind):
+    """No room is taken under capture: a graph captured before any eager call of
+    its width runs one launch per colour and gives the eager result's bits."""
+    from paper_2604_26037_amd import Operator
+    s = _system(p, kind, (3, 4, 3))
+    op, other = Operator(s), Operator(s)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    X = torch.randn(op.ndof, 40, device="cuda", dtype=torch.complex128 if kind == "complex" else torch.float64, generator=g)
+    Y, Z = torch.zeros_like(X), torch.zeros_like(X)
+    eager = (other.apply_H(X), other.apply_S(X))
+    op.apply_Sinv(X)          # projector scratch of 40 columns, no room
+    # the launches per colour, once, outside the capture
+    other.apply_local(X, Y, which=0)
+    other.apply_local(X, Z, which=1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        op.apply_H(X, out=Y)
+        op.apply_S(X, out=Z)
+    for _ in range(2):
+        Y.fill_(float("nan"))
+        Z.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager[0]) and torch.equal(Z, eager[1])
+    op.close()
+    other.close()
