@@ -23,7 +23,12 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libpawfe.so")
 
 SOURCES = ["builder.cpp", "kernels_cell.hip", "kernels_cell_mfma.hip", "kernels_cell_valu.hip",
-           "kernels_cell_gen_f32.hip", "kernels_cell_gen_f64.hip", "kernels_cell_step.hip", "kernels_cell_step_gen.hip", "kernels_nl.hip", "kernels_halo.hip", "api.hip", "batch.cpp"]
+           "kernels_cell_gen_f32.hip", "kernels_cell_gen_f64.hip", "kernels_cell_step.hip",
+           "kernels_cell_step_gen.hip", "kernels_nl.hip", "kernels_halo.hip", "api.hip", "batch.cpp"]
+# compiled once per data type (-DPAWFE_T), the longest first: the cell kernels
+# are most of the build
+PER_TYPE = ["kernels_cell_valu.hip", "kernels_cell_step.hip", "kernels_cell_step_gen.hip"]
+UNITS = [(s, t) for t in ("double", "float") for s in PER_TYPE] + [(s, None) for s in SOURCES if s not in PER_TYPE]
 ARCH = os.environ.get("PAWFE_OFFLOAD_ARCH", "gfx950")
 
 
@@ -40,9 +45,15 @@ def _flags():
             "-I", INCLUDE, "-I", CSRC, "-Wno-unused-command-line-argument"]
 
 
-def _compile(src):
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc()] + _flags() + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _object(unit):
+    src, dtype = unit
+    return os.path.join(BUILD, os.path.splitext(src)[0] + (f"_{dtype}" if dtype else "") + ".o")
+
+
+def _compile(unit):
+    src, dtype = unit
+    obj = _object(unit)
+    cmd = [hipcc()] + _flags() + ([f"-DPAWFE_T={dtype}"] if dtype else []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
@@ -51,9 +62,9 @@ def _compile(src):
 
 def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
-    jobs = min(len(SOURCES), int(os.environ.get("MAX_JOBS", "8")))
+    jobs = min(len(UNITS), int(os.environ.get("MAX_JOBS", "8")))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs + \
         ["-L", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib"),

@@ -106,6 +106,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     A.out[(int64_t)e * NQ3 + q] = A.W3[q] * cs * ((slabs[0][q] + slabs[1][q]) + (slabs[2][q] + slabs[3][q]));
 }
 
+bool cell_step_available(const pawfe_op* op) {
+  return op->nq == op->p + 2 && op->p >= 2 && op->p <= 6 && op->d.cell_own != nullptr &&
+         (!op->general || (op->d.frho != nullptr && !op->cplx));
+}
+
 template <typename T>
 pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, T* Y, int64_t ldy,
                          int ncols, const double* lam, double alpha, hipStream_t s, bool bf3, bool overwrite,

@@ -1,6 +1,6 @@
 // The Chebyshev step of the filter: the vector-ALU kernel of cell_valu.h in
 // its step variants (cells of one size here; graded meshes and the GGA term
-// in kernels_cell_step_gen.hip).
+// in kernels_cell_step_gen.hip), for data type PAWFE_T.
 //
 // One step of Algorithm 2 (R_Y the current block, R_X the previous one,
 // T = M_D^{-1} R_Y' with R_Y' = R_Y - sum_a C^a d_a already formed in R_Y):
@@ -15,11 +15,6 @@
 #include "cell_valu.h"
 
 namespace pawfe {
-
-bool cell_step_available(const pawfe_op* op) {
-  return op->nq == op->p + 2 && op->p >= 2 && op->p <= 6 && op->d.cell_own != nullptr &&
-         (!op->general || (op->d.frho != nullptr && !op->cplx));
-}
 
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
@@ -75,10 +70,8 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
   }
 }
 
-template pawfe_status launch_cell_step<float>(const pawfe_op*, const float*, float*, int64_t, const double*, int64_t,
-                                              const double*, double, double, double, int, hipStream_t, bool, void*);
-template pawfe_status launch_cell_step<double>(const pawfe_op*, const double*, double*, int64_t, const double*,
-                                               int64_t, const double*, double, double, double, int, hipStream_t,
-                                               bool, void*);
+template pawfe_status launch_cell_step<PAWFE_T>(const pawfe_op*, const PAWFE_T*, PAWFE_T*, int64_t, const double*,
+                                                int64_t, const double*, double, double, double, int, hipStream_t,
+                                                bool, void*);
 
 }  // namespace pawfe

@@ -1,6 +1,7 @@
 // The Chebyshev step of the filter on general operators (graded meshes,
 // the GGA term): the vector-ALU kernel of cell_valu.h in its general step
-// variants (per-cell geometry, face factors of the lumped mass).
+// variants (per-cell geometry, face factors of the lumped mass), for data type
+// PAWFE_T.
 
 #include "cell_valu.h"
 
@@ -26,7 +27,6 @@ pawfe_status launch_cell_step_gen(const pawfe_op* op, const CellArgs<T>& c, hipS
   }
 }
 
-template pawfe_status launch_cell_step_gen<float>(const pawfe_op*, const CellArgs<float>&, hipStream_t);
-template pawfe_status launch_cell_step_gen<double>(const pawfe_op*, const CellArgs<double>&, hipStream_t);
+template pawfe_status launch_cell_step_gen<PAWFE_T>(const pawfe_op*, const CellArgs<PAWFE_T>&, hipStream_t);
 
 }  // namespace pawfe

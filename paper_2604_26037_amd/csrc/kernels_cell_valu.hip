@@ -1,6 +1,6 @@
 // K + V (and the residual K + V - lambda M) on the vector ALUs for operators
 // whose cells share one geometry
-// (the kernel and its tables are in cell_valu.h).
+// (the kernel and its tables are in cell_valu.h), for data type PAWFE_T.
 
 #include "cell_valu.h"
 
@@ -51,7 +51,6 @@ pawfe_status launch_cell_valu(const pawfe_op* op, int mode, const CellArgs<T>& a
   }
 }
 
-template pawfe_status launch_cell_valu<float>(const pawfe_op*, int, const CellArgs<float>&, hipStream_t, bool*);
-template pawfe_status launch_cell_valu<double>(const pawfe_op*, int, const CellArgs<double>&, hipStream_t, bool*);
+template pawfe_status launch_cell_valu<PAWFE_T>(const pawfe_op*, int, const CellArgs<PAWFE_T>&, hipStream_t, bool*);
 
 }  // namespace pawfe
