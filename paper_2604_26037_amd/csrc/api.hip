@@ -181,10 +181,11 @@ pawfe_status do_apply(const pawfe_op* op, int which, const T* X, int64_t ldx, T*
   return launch_node_sinv<T>(op, X, ldx, b.d, ncols, Y, ldy, s);
 }
 
-// Y = H X - S X diag(lam), FP64
+// Y = H X - S X diag(lam), FP64; a column's bits do not depend on the block's
+// width nor on the room in b
 pawfe_status do_residual(const pawfe_op* op, const double* X, int64_t ldx, const double* lam, double* Y, int64_t ldy,
                          int ncols, const NlBufs& b, hipStream_t s) {
-  CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, s));
+  CHECK(launch_nl_reduce<double>(op, X, ldx, ncols, false, b.part, s, false, true));
   CHECK(launch_atom_first(op, b.part, nullptr, op->d.dH, op->d.dS, lam, nullptr, ncols, nullptr, b.d, nullptr, s));
   CHECK(launch_cell<double>(op, kModeHRes, X, ldx, Y, ldy, ncols, lam, 1.0, s, false, true, b.cell));
   return launch_node_fixup<double>(op, b.d, 1.0, ncols, Y, ldy, s);

@@ -1220,23 +1220,35 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
   const T fx = (T)(0.5 * op->detJ * (2.0 / op->h[0]) * (2.0 / op->h[0]));
   const T fy = (T)(0.5 * op->detJ * (2.0 / op->h[1]) * (2.0 / op->h[1]));
   const T fz = (T)(0.5 * op->detJ * (2.0 / op->h[2]) * (2.0 / op->h[2]));
+  bool wave = false;
+  if constexpr (is_wave_mode(MODE)) {
+    // a block that would gather its cells' results if it had room for them takes
+    // the workgroup kernel colour by colour without it: the same bits
+    const bool small = a.cellbuf || (a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T)));
+    wave = a.by_op ? wave_pays<T, NP, MODE>(op, kResidualCols) : !small && wave_pays<T, NP, MODE>(op, a.ncols);
+  }
   if (a.cellbuf) {
-    CellArgs<T> ac = a;
-    ac.cells = op->d.cell_pack;
-    const int nitems = op->E * ncoltiles;
-    const dim3 grid(valu_grid<k_cell_valu<T, NP, NQ, MODE>, kNT<T>>(nitems)), block(kNT<T>);
-    hipLaunchKernelGGL((k_cell_valu<T, NP, NQ, MODE>), grid, block, 0, s, ac, ncoltiles, nitems, fx, fy, fz);
-    PAWFE_HIP(hipGetLastError());
     constexpr bool gen_step = MODE == kValuGenStep || MODE == kValuGenStepG;
     constexpr bool step = MODE == kValuStep || MODE == kValuStepC || gen_step;
     constexpr bool mass = MODE == kValuMass || MODE == kValuGenMass;
+    CellArgs<T> ac = a;
+    ac.cells = op->d.cell_pack;
+    bool done = false;
+    if constexpr (is_wave_buf_mode(MODE)) {
+      if (wave) {
+        launch_wave<T, NP, NQ, MODE>(ac, op->E, fx, fy, fz, s);
+        if (!mass) ac.alpha = T(1);   // (the one-wave kernel's results hold it)
+        done = true;
+      }
+    }
+    if (!done) {
+      const int nitems = op->E * ncoltiles;
+      const dim3 grid(valu_grid<k_cell_valu<T, NP, NQ, MODE>, kNT<T>>(nitems)), block(kNT<T>);
+      hipLaunchKernelGGL((k_cell_valu<T, NP, NQ, MODE>), grid, block, 0, s, ac, ncoltiles, nitems, fx, fy, fz);
+    }
+    PAWFE_HIP(hipGetLastError());
     return launch_cell_gather<T>(op, ac, step, mass ? kByMass : gen_step ? kByDetJ : kByAlpha, s);
   }
-  // without the room that it would have, a block takes the workgroup kernel
-  // colour by colour, whose result is the gather's bit for bit
-  bool wave = false;
-  if constexpr (is_wave_mode(MODE))
-    wave = !(a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T))) && wave_pays<T, NP, MODE>(op, a.ncols);
   for (int c = 0; c < op->ncolour; ++c) {
     const int c0 = op->colour_off[c], c1 = op->colour_off[c + 1];
     if (c1 == c0) continue;

@@ -38,6 +38,12 @@ namespace pawfe {
 
 namespace {
 
+// Modes whose one-wave variant can store each cell's result by itself
+// (CellArgs::cellbuf): those of the residual.
+constexpr bool is_wave_buf_mode(int mode) {
+  return mode == kValuHRes || mode == kValuHResC || mode == kValuGenH || mode == kValuGenMass;
+}
+
 template <typename T, int NP, int NQ>
 struct Wave {
   static constexpr int H = (sizeof(T) == 8 && NP >= 6) ? 2 : 1;   // halves of a plane
@@ -106,6 +112,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep || MODE == kValuStepC;
   constexpr bool CPLX = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
   constexpr bool SC = STEP;
+  constexpr bool BUF = is_wave_buf_mode(MODE);
   constexpr int NQ2 = NQ * NQ, NP2 = NP * NP, NQ3 = NQ * NQ * NQ;
   constexpr int WT = kWaveTiles<MODE>;
   static_assert(MASS || WT == 1, "V(q) W_q is staged by one wave");
@@ -459,6 +466,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   // old rows (except at a first visit that overwrites them) and, of the step,
   // the first FP64 residual rows: requested here, used after the last z pass
   opaque(cm);
+  const bool to_buf = BUF && A.cellbuf != nullptr;   // the cell's own result only
   T yo[RB][NP];
   xoffs(ldyb, xo);
   const char* yp = planeptr((const T*)A.Y, ldyb);
@@ -468,7 +476,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     if constexpr (STEP) {
       sfor<NP>(get);
     } else {
-      const unsigned cr = cm >> row_class(r);
+      const unsigned cr = to_buf ? ~0u : cm >> row_class(r);
       sfor<NP>([&](auto a) { yo[r][a] = T(0); });
       if (!(cr & 1u)) get(std::integral_constant<int, 0>{});
       if (!(cr & 2u)) sfor<NP - 2>([&](auto a) { get(std::integral_constant<int, a + 1>{}); });
@@ -524,9 +532,19 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       if constexpr (r + kAhead < RB) load_y(std::integral_constant<int, (r + kAhead < RB ? r + kAhead : 0)>{});
       first_visits(r, [&](auto a) { yo[r][a] = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly); });
     }
-    sfor<NP>([&](auto a) { yo[r][a] += MASS ? f * acc[r][a] : acc[r][a]; });
+    if (to_buf) sfor<NP>([&](auto a) { yo[r][a] = acc[r][a]; });
+    else sfor<NP>([&](auto a) { yo[r][a] = MASS ? fma_t(f, acc[r][a], yo[r][a]) : yo[r][a] + acc[r][a]; });
   });
-  if (pl && valid) {
+  if (to_buf) {
+    if (pl && valid) {
+      T* out = A.cellbuf + (int64_t)e * (NP * NP * NP) * A.ncols + n;
+      sfor<RB>([&](auto r) {
+        const int b = RB * h + r;
+        if (H == 1 || NPX == NP || b < NP)
+          sfor<NP>([&](auto a) { out[(int64_t)(a + NP * (b + NP * c)) * A.ncols] = yo[r][a]; });
+      });
+    }
+  } else if (pl && valid) {
     char* yw = planeptr(A.Y, ldyb);
     sfor<RB>([&](auto r) {
       if (H == 1 || NPX == NP || RB * h + r < NP) {

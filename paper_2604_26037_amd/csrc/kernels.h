@@ -43,6 +43,7 @@ struct CellArgs {
   // either way
   T* cellbuf;
   bool gathers;
+  bool by_op;   // the route is chosen by the operator alone, not by ncols (residual)
   const T* frho;         // general step: [E][6] face factors (x lo, x hi, y lo, y hi, z lo, z hi)
 };
 
@@ -131,6 +132,12 @@ pawfe_status launch_density(const pawfe_op* op, const double* X, int64_t ldx, in
 // per real column of the (re, im) pairs)
 pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t s);
 
+// A column's residual H x - lambda S x has the same bits in a block of any
+// width (Rayleigh-Ritz forms it in blocks of its own and hands it to the
+// filter), so its kernels are chosen for blocks of this many columns, whatever
+// the block's.
+constexpr int kResidualCols = 256;
+
 // ---- non-local / node-wise kernels (kernels_nl.hip) ----
 
 // Partial sums (per work item of an atom's rows) of
@@ -139,9 +146,10 @@ pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t 
 // part: >= item_rows_total*ncols doubles.
 // Real operators in FP32 run on the matrix cores (FP32, or bf16x3 split
 // products when bf3); FP64 and complex operators on the vector ALUs.
+// by_op: the split of the rows is chosen by the operator alone (residual).
 template <typename T>
 pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int ncols, bool scale_minv,
-                              double* part, hipStream_t s, bool bf3 = false);
+                              double* part, hipStream_t s, bool bf3 = false, bool by_op = false);
 
 // From the partials of launch_nl_reduce: c_a (- sum_b G^{ab} nw_b when nw is
 // given), d_a = (D1 - lam_n D2) c_a per atom block (D2 may be null), v = nw + d.

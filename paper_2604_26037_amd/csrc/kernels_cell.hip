@@ -135,6 +135,7 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   a.own = overwrite ? op->d.cell_own : nullptr;
   a.cellbuf = bf3 ? nullptr : (T*)cellbuf;
   a.gathers = overwrite;
+  a.by_op = mode == kModeHRes;
   if (op->general) {   // graded mesh / GGA term: every local term on the vector-ALU variants
     if (bf3) return fail(PAWFE_EUNSUPPORTED, "bf16x3 is not built for graded meshes or the GGA term");
     return launch_cell_gen<T>(op, mode, a, s);

@@ -986,14 +986,14 @@ const T* pick(const double* d64, const float* d32) {
 
 template <typename T>
 pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int ncols, bool scale_minv, double* part,
-                              hipStream_t s, bool bf3) {
+                              hipStream_t s, bool bf3, bool by_op) {
   if (op->natoms == 0 || ncols <= 0) return PAWFE_OK;
   const T* Cv = pick<T>(op->d.Cvals, op->d.Cvals_f);
   const T* Minv = pick<T>(op->d.Minv, op->d.Minv_f);
   const T* Cvi = pick<T>(op->d.Cvals_im, op->d.Cvals_im_f);
   // fewer than three waves per SIMD without the split: take it
   static_assert(kRowsPerWaveGroup == 4, "waves of a reduction workgroup");
-  const bool split = (int64_t)op->nitems * ((ncols + 63) / 64) < 3000;
+  const bool split = (int64_t)op->nitems * (((by_op ? kResidualCols : ncols) + 63) / 64) < 3000;
   const dim3 grid(op->nitems, split ? (ncols + 63) / 64 : (ncols + 255) / 256), block(256);
   if constexpr (std::is_same<T, float>::value) {
     if (!op->cplx) {   // real operators in FP32: the matrix-core reduction
@@ -1037,9 +1037,9 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   return PAWFE_OK;
 }
 template pawfe_status launch_nl_reduce<double>(const pawfe_op*, const double*, int64_t, int, bool, double*,
-                                               hipStream_t, bool);
+                                               hipStream_t, bool, bool);
 template pawfe_status launch_nl_reduce<float>(const pawfe_op*, const float*, int64_t, int, bool, double*, hipStream_t,
-                                              bool);
+                                              bool, bool);
 
 pawfe_status launch_atom_first(const pawfe_op* op, const double* part, const double* nw, const double* D1,
                                const double* D2, const double* lam, const double* D1i, int ncols, double* c,
