@@ -563,26 +563,41 @@ constexpr bool is_wave_mode(int mode) {
          mode == kValuGenMass || mode == kValuGenStep || mode == kValuHC || mode == kValuHResC || mode == kValuStepC;
 }
 
-// Where the one-wave split pays, by the cell columns (cells x columns) of an
-// average colour: an item takes one wave longer than it takes a workgroup, so
-// a launch has to hold enough items to fill the chip.  Measured per launch
-// (workgroup -> wave): step at degree 6 FP32 19.0 -> 21.1 us at 6,900 cell
-// columns, 39.5 -> 38.9 at 16,400, 74 -> 63 at 32,000; FP64 34.6 -> 35.7 at
-// 8,000, 71.6 -> 63.0 at 16,400; degree 3 FP64 7.7 -> 7.7 at 4,100, FP32 7.4
-// -> 7.5 at 6,900; degree 2 FP32 even at any size, FP64 5.0 -> 5.4 at 2,000
-// and 8.7 -> 5.9 at 6,900.  Complex step at degree 6 FP32 22.5 -> 25.6 at 8,000
-// real cell columns, 44.7 -> 41.8 at 16,400, 75 -> 78 at 24,000 (3000 waves are one
-// and a half rounds), 85 -> 75 at 32,000; FP64 16.0 -> 19.8 at 2,000, 26.3
-// -> 23.9 at 4,100, 183 -> 131 at 32,000.  The mass term is too short to lose: 5.2 -> 4.7 us
-// at 128 cell columns.
+// Where the one-wave split pays.  An item takes one wave longer than it takes a
+// workgroup, so a launch has to hold enough items to fill the chip: two waves on
+// each of 1024 SIMDs run at once, and a last round of them that is nearly empty
+// costs as much as a full one.  One-wave over workgroup time per launch, by the
+// rounds of an average colour (512 cells in 8 colours, step / K + V):
+//   rounds             0.5       0.75      1.0       1.12      1.5       2.12      3.12
+//   degree 6 FP32    1.11/1.15 0.97/0.89 0.92/0.88 1.22/1.12 0.96/0.95 1.00/1.00 0.94/0.92
+//   degree 5 FP32    1.13/1.17 0.91/0.90 0.99/0.95 1.21/1.12 1.04/0.94 1.11/1.02 1.00/0.93
+//   degree 4 FP32    1.12/1.16 0.86/0.87 0.91/0.88 1.09/1.09 0.93/0.92 1.10/0.99 1.00/0.89
+//   6, complex FP32  1.20/1.23 1.03/0.94 0.97/0.89 1.30/1.25 1.02/1.05 1.07/1.05 0.95/0.94
+//   5, complex FP32  1.13/1.17 0.90/0.91 0.84/0.85 1.23/1.18 0.97/0.94 1.02/1.01 0.93/0.92
+//   4, complex FP32  1.07/1.11 0.84/0.87 0.78/0.79 1.12/1.12 0.87/0.88 0.99/0.93 0.90/0.85
+//   6, complex FP64  1.04/1.01 0.99/1.01 0.91/0.89 1.12/1.09 0.91/0.96 0.96/1.00 0.90/0.94
+// so there the rounds decide, as the share of them that is filled: from 0.72 on,
+// from 0.9 on at degree 6 complex FP32 (1.05 at 0.88 rounds, 0.99 at 1.88), and
+// always from three rounds on.  The others gain more than a round can cost and go
+// by cell columns (cells x columns): degree 3 FP32 even at 8,000 (0.95), FP64
+// at 4,000 (0.87); degree 2 FP32 at any size (0.82 at 4,000), FP64 at 4,000
+// (0.74); degree 6 FP64 0.97/0.84 at 6,100 and at most 0.99 from there, degree 5
+// 0.92/0.89 at 4,100, degree 4 0.89/0.92; complex FP64 degree 5 0.87/0.81 at
+// 4,100, degree 4 0.96/0.90, degree 3 0.89/0.96.  The mass term is too short to
+// lose: 5.2 -> 4.7 us at 128 cell columns.
+constexpr double kWavesAtOnce = 2048.0;
 template <typename T, int NP, int MODE>
 bool wave_pays(const pawfe_op* op, int ncols) {
   if (MODE == kValuMass || MODE == kValuGenMass) return true;
-  const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
   constexpr bool kCplx = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
-  const int64_t least = sizeof(T) == 4 ? (NP == 3 ? 0 : NP == 4 ? 7000 : kCplx ? 30000 : 16000)
-                                       : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000);
-  return per_colour >= least;
+  constexpr bool f32 = sizeof(T) == 4;
+  if ((f32 && NP >= 5) || (kCplx && NP == 7)) {
+    constexpr int CB = Wave<T, NP, NP + 1>::CB;
+    const double rounds = (double)op->E / std::max(op->ncolour, 1) * ((ncols + CB - 1) / CB) / kWavesAtOnce;
+    return rounds >= 3.0 || rounds >= (f32 && kCplx && NP == 7 ? 0.9 : 0.72) * std::ceil(rounds);
+  }
+  const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
+  return per_colour >= (f32 ? (NP == 3 ? 0 : 7000) : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000));
 }
 
 template <typename T, int NP, int NQ, int MODE>

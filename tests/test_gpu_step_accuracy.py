@@ -3,7 +3,7 @@ filtered in wide blocks (one-wave kernel) and in narrow ones (workgroup kernel,
 whose node part -a c R_Y' meets the local sum only at the end) have the same
 error against the FP64 filter.  The order of the step's sum decides it: with
 -a c R_Y' added between the local terms the wide blocks are 4 to 12 % worse,
-at the end never worse.  The mean over 640 columns is stable to 0.5 %."""
+at the end never worse.  The mean over 592 columns is stable to 0.5 %."""
 
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 def test_wide_blocks_are_as_accurate(p, kind):
     from paper_2604_26037_amd import Operator
     from workloads.configs import custom_system, with_two_level_gga
-    n, N = (6, 6, 6), 640                    # 17,280 cell columns per colour (complex: twice that, real)
+    n, N = (6, 6, 6), 592                    # 1,998 waves per colour (complex: twice that), close to full rounds
     pos = np.random.default_rng(p).uniform(0, 1, (4, 3)) * 2.0 * np.asarray(n)
     kw = dict(kpoint=(0.2, 0.1, -0.3), is_complex=True) if kind == "complex" else {}
     s = custom_system(n, tuple(2.0 * v for v in n), p, p + 2, pos=pos, rcut=0.9, channels="spd8", wells=pos, s_H=0.5,
