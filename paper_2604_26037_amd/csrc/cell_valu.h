@@ -1268,7 +1268,8 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     }
     if (!done) launch_group(ac, op->E);
     PAWFE_HIP(hipGetLastError());
-    return launch_cell_gather<T>(op, ac, step, mass ? kByMass : gen_step ? kByDetJ : kByAlpha, s);
+    if (MODE == kValuMass) ac.alpha = a.alpha * a.detJ;
+    return launch_cell_gather<T>(op, ac, step, MODE == kValuGenMass ? kByMass : gen_step ? kByDetJ : kByAlpha, s);
   }
   for (int c = 0; c < op->ncolour; ++c) {
     const int c0 = op->colour_off[c], c1 = op->colour_off[c + 1];

@@ -84,7 +84,8 @@ size_t cell_buf_limit();
 // Y of a launch with a.cellbuf: the sum of the cells' results per DOF, plus Y
 // (a.own null), alone (a.own set), or plus the node part of the filter's step;
 // each result times its factor: alpha (kByAlpha), alpha / det J of the cell
-// (kByDetJ: general steps) or alpha det J [-lambda_n] (kByMass).
+// (kByDetJ: general steps) or alpha det J of the cell [-lambda_n] (kByMass:
+// general mass terms).
 enum CellFactor { kByAlpha, kByDetJ, kByMass };
 template <typename T>
 pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, CellFactor fk, hipStream_t s);

@@ -154,6 +154,16 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
   return launch_cell_mfma<T>(op, kModeImg, a, s);
 }
 
+// One launch per colour is latency (4-10 us each, 8 to 27 of them) until a
+// colour holds several thousand cell columns; below that one launch of all
+// cells and a gather pay.  K + V, launches per colour against launch and
+// gather: degree 6, 64 cells in 8 colours, FP64 76 -> 27 us at 500 cell columns
+// per colour, 118 -> 88 at 3,000; 512 cells 159 -> 149 at 4,500 and 197 -> 210
+// at 7,000 (FP32 114 -> 94 and 129 -> 118); 125 cells in 27 colours FP32
+// 235 -> 55 at 1,000; degree 2, 512 cells, FP64 41 -> 33 at 4,500 and 41 -> 45
+// at 7,000.  The bytes bound the scratch (142 MB: 296 -> 208 us).
+constexpr int64_t kCellBufCols = 4500, kCellBufBytes = int64_t(192) << 20;
+
 // Y[I][n] = sum over the (up to eight) cells sharing DOF I of their results
 // times their factors (CellFactor F), added one after another in the order of
 // the cells' colours to 0 (KIND 0), to Y (KIND 1) or to the node part of the
@@ -171,21 +181,24 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
   if (I >= M) return;
   const int Gx = A.n0 * P, Gy = A.n1 * P;
   const int g[3] = {I % Gx, (I / Gx) % Gy, I / (Gx * Gy)}, nc[3] = {A.n0, A.n1, A.n2};
-  int cell[3][2], node[3][2];
+  const int cs[3] = {1, A.n0, A.n0 * A.n1}, qs[3] = {1, NP, NP * NP};
+  // per axis the cells' shares of the cell index and of the row of the results
+  int ce[3][2], row[3][2];
   bool two[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int c0 = g[d] / P, q0 = g[d] - c0 * P, c1 = c0 == 0 ? nc[d] - 1 : c0 - 1;
     two[d] = q0 == 0;                                     // also the last node of the cell before
-    // the cell of the lower colour (i mod 2; the last of an odd direction 2) first
-    auto colour = [&](int i) { return (nc[d] & 1) && i == nc[d] - 1 ? 2 : i & 1; };
-    const bool turn = two[d] && colour(c1) < colour(c0);
-    cell[d][0] = turn ? c1 : c0;
-    node[d][0] = turn ? P : q0;
-    cell[d][1] = turn ? c0 : c1;
-    node[d][1] = turn ? q0 : P;
+    // the cell of the lower colour (i mod 2; the last of an odd direction 2)
+    // first: the one before an odd cell and before the last of an odd direction
+    const bool turn = two[d] && ((c0 & 1) || ((nc[d] & 1) && c0 == nc[d] - 1));
+    const int e0 = cs[d] * c0, e1 = cs[d] * c1, r0 = e0 * NL + qs[d] * q0, r1 = e1 * NL + qs[d] * P;
+    ce[d][0] = turn ? e1 : e0;
+    ce[d][1] = turn ? e0 : e1;
+    row[d][0] = turn ? r1 : r0;
+    row[d][1] = turn ? r0 : r1;
   }
-  int64_t off[8];
+  uint32_t off[8];   // (kCellBufBytes: well inside 32 bits)
   bool on[8];
   T f[F == kByAlpha ? 1 : 8];
   if constexpr (F == kByAlpha) f[0] = A.alpha;
@@ -193,11 +206,11 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
   for (int k = 0; k < 8; ++k) {   // ascending colours: z most significant
     const int i = k & 1, j = (k >> 1) & 1, l = k >> 2;
     on[k] = (!i || two[0]) && (!j || two[1]) && (!l || two[2]);
-    const int e = cell[0][i] + A.n0 * (cell[1][j] + A.n1 * cell[2][l]);
-    const int q = node[0][i] + NP * (node[1][j] + NP * node[2][l]);
-    off[k] = ((int64_t)e * NL + q) * A.ncols;
-    if constexpr (F == kByDetJ) f[k] = A.alpha / A.geo[4 * e + 3];
-    if constexpr (F == kByMass) f[k] = A.alpha * (A.geo ? A.geo[4 * e + 3] : A.detJ);
+    off[k] = (uint32_t)(row[0][i] + row[1][j] + row[2][l]) * (uint32_t)A.ncols;
+    if constexpr (F != kByAlpha) {
+      const T dj = A.geo[4 * (ce[0][i] + ce[1][j] + ce[2][l]) + 3];
+      f[k] = F == kByDetJ ? A.alpha / dj : A.alpha * dj;
+    }
   }
   for (int n = threadIdx.x & (CW - 1); n < A.ncols; n += CW) {
     T v[8];
@@ -220,16 +233,6 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
   }
 }
 
-// One launch per colour is latency (4-10 us each, 8 to 27 of them) until a
-// colour holds several thousand cell columns; below that one launch of all
-// cells and a gather pay.  K + V, launches per colour against launch and
-// gather: degree 6, 64 cells in 8 colours, FP64 76 -> 27 us at 500 cell columns
-// per colour, 118 -> 88 at 3,000; 512 cells 159 -> 149 at 4,500 and 197 -> 210
-// at 7,000 (FP32 114 -> 94 and 129 -> 118); 125 cells in 27 colours FP32
-// 235 -> 55 at 1,000; degree 2, 512 cells, FP64 41 -> 33 at 4,500 and 41 -> 45
-// at 7,000.  The bytes bound the scratch (142 MB: 296 -> 208 us).
-constexpr int64_t kCellBufCols = 4500, kCellBufBytes = int64_t(192) << 20;
-
 size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem) {
   if (op->nq != op->p + 2 || op->p < 2 || op->p > 6 || ncols <= 0) return 0;
   const int64_t bytes = (int64_t)op->E * op->nloc * ncols * (int64_t)elem;
@@ -241,6 +244,7 @@ size_t cell_buf_limit() { return (size_t)kCellBufBytes; }
 template <typename T>
 pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, CellFactor fk, hipStream_t s) {
   if (!step && fk != kByMass && !a.own) return fail(PAWFE_EUNSUPPORTED, "internal: no gather that adds to Y");
+  if (fk != kByAlpha && !a.geo) return fail(PAWFE_EINVAL, "internal: gather without geometry");
   int cw = 2;   // lanes per row: the columns, at most a wave
   while (cw < 6 && (1 << cw) < a.ncols) ++cw;
   const int rows = 256 >> cw;
