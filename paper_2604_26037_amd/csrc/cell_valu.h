@@ -1248,19 +1248,25 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     }
     go(std::false_type{});
   };
-  bool wave = false;
-  if constexpr (is_wave_mode(MODE)) {
-    // a block that would gather its cells' results if it had room for them takes
-    // the workgroup kernel colour by colour without it: the same bits
-    const bool small = a.cellbuf || (a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T)));
-    wave = a.by_op ? wave_pays<T, NP, MODE>(op, kResidualCols) : !small && wave_pays<T, NP, MODE>(op, a.ncols);
-  }
+  // the one-wave kernel for a launch of ncells cells: a residual takes one
+  // kernel in all launches, chosen for an average colour; a block that would
+  // gather its cells' results if it had room for them takes the workgroup kernel
+  // colour by colour without it (the same bits)
+  auto use_wave = [&](int ncells) {
+    if constexpr (is_wave_mode(MODE)) {
+      if (a.by_op)
+        return wave_pays<T, NP, MODE>((double)op->E / std::max(op->ncolour, 1), op->cplx ? kResidualColsC : kResidualCols);
+      if (a.cellbuf || (a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T)))) return false;
+      return wave_pays<T, NP, MODE>(ncells, a.ncols);
+    }
+    return false;
+  };
   if (a.cellbuf) {
     CellArgs<T> ac = a;
     ac.cells = op->d.cell_pack;
     bool done = false;
     if constexpr (is_wave_buf_mode(MODE)) {
-      if (wave) {
+      if (use_wave(op->E)) {
         launch_wave<T, NP, NQ, MODE>(ac, op->E, fx, fy, fz, s);
         if (!mass) ac.alpha = T(1);   // (the one-wave kernel's results hold it)
         done = true;
@@ -1277,7 +1283,7 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     CellArgs<T> ac = a;
     ac.cells = op->d.cell_pack + c0;
     if constexpr (is_wave_mode(MODE)) {
-      if (wave) {
+      if (use_wave(c1 - c0)) {
         launch_wave<T, NP, NQ, MODE>(ac, c1 - c0, fx, fy, fz, s);
         continue;
       }

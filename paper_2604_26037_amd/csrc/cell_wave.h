@@ -567,7 +567,7 @@ constexpr bool is_wave_mode(int mode) {
 // workgroup, so a launch has to hold enough items to fill the chip: two waves on
 // each of 1024 SIMDs run at once, and a last round of them that is nearly empty
 // costs as much as a full one.  One-wave over workgroup time per launch, by the
-// rounds of an average colour (512 cells in 8 colours, step / K + V):
+// rounds of a launch (512 cells in 8 colours, step / K + V):
 //   rounds             0.5       0.75      1.0       1.12      1.5       2.12      3.12
 //   degree 6 FP32    1.11/1.15 0.97/0.89 0.92/0.88 1.22/1.12 0.96/0.95 1.00/1.00 0.94/0.92
 //   degree 5 FP32    1.13/1.17 0.91/0.90 0.99/0.95 1.21/1.12 1.04/0.94 1.11/1.02 1.00/0.93
@@ -586,18 +586,19 @@ constexpr bool is_wave_mode(int mode) {
 // 4,100, degree 4 0.96/0.90, degree 3 0.89/0.96.  The mass term is too short to
 // lose: 5.2 -> 4.7 us at 128 cell columns.
 constexpr double kWavesAtOnce = 2048.0;
+// Decided launch by launch: an odd mesh has colours of very different sizes (11
+// x 13 x 8 cells: 120, 24, 20 and 4).
 template <typename T, int NP, int MODE>
-bool wave_pays(const pawfe_op* op, int ncols) {
+bool wave_pays(double ncells, int ncols) {
   if (MODE == kValuMass || MODE == kValuGenMass) return true;
   constexpr bool kCplx = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
   constexpr bool f32 = sizeof(T) == 4;
   if ((f32 && NP >= 5) || (kCplx && NP == 7)) {
     constexpr int CB = Wave<T, NP, NP + 1>::CB;
-    const double rounds = (double)op->E / std::max(op->ncolour, 1) * ((ncols + CB - 1) / CB) / kWavesAtOnce;
+    const double rounds = ncells * ((ncols + CB - 1) / CB) / kWavesAtOnce;
     return rounds >= 3.0 || rounds >= (f32 && kCplx && NP == 7 ? 0.9 : 0.72) * std::ceil(rounds);
   }
-  const int64_t per_colour = (int64_t)op->E * ncols / std::max(op->ncolour, 1);
-  return per_colour >= (f32 ? (NP == 3 ? 0 : 7000) : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000));
+  return ncells * ncols >= (f32 ? (NP == 3 ? 0 : 7000) : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000));
 }
 
 template <typename T, int NP, int NQ, int MODE>

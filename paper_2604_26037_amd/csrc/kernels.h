@@ -135,9 +135,13 @@ pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t 
 
 // A column's residual H x - lambda S x has the same bits in a block of any
 // width (Rayleigh-Ritz forms it in blocks of its own and hands it to the
-// filter), so its kernels are chosen for blocks of this many columns, whatever
-// the block's.
-constexpr int kResidualCols = 256;
+// filter), so its kernels are chosen for blocks of one width, whatever the
+// block's: the cell kernel of real operators for 256 columns, where the one-wave
+// kernel costs a narrow block 1.1 times the workgroup kernel; that of complex
+// operators, where it costs up to 1.5 times, and the projector reduction, whose
+// walk without the split costs a narrow block 2.5 times (and the split a wide
+// one 1.4), for 64.
+constexpr int kResidualCols = 256, kResidualColsC = 64, kResidualColsNl = 64;
 
 // ---- non-local / node-wise kernels (kernels_nl.hip) ----
 

@@ -993,7 +993,7 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   const T* Cvi = pick<T>(op->d.Cvals_im, op->d.Cvals_im_f);
   // fewer than three waves per SIMD without the split: take it
   static_assert(kRowsPerWaveGroup == 4, "waves of a reduction workgroup");
-  const bool split = (int64_t)op->nitems * (((by_op ? kResidualCols : ncols) + 63) / 64) < 3000;
+  const bool split = (int64_t)op->nitems * (((by_op ? kResidualColsNl : ncols) + 63) / 64) < 3000;
   const dim3 grid(op->nitems, split ? (ncols + 63) / 64 : (ncols + 255) / 256), block(256);
   if constexpr (std::is_same<T, float>::value) {
     if (!op->cplx) {   // real operators in FP32: the matrix-core reduction
