@@ -25,6 +25,14 @@ namespace {
 
 constexpr int kRowsPerWaveGroup = 4;   // waves per 256-thread block in row-wise kernels
 
+// (items, column tiles): a grid's y extent ends at 65,535, which the narrow tiles
+// reach at a million columns; from there on z counts on
+inline dim3 tile_grid(int64_t items, int64_t tiles) {
+  constexpr int64_t kMaxY = 65535;
+  return dim3((unsigned)items, (unsigned)std::min(tiles, kMaxY), (unsigned)((tiles + kMaxY - 1) / kMaxY));
+}
+__device__ __forceinline__ int tile_index() { return blockIdx.y + blockIdx.z * gridDim.y; }
+
 // A workgroup of four waves takes an item's rows: SPLIT = 1, each wave owns 64
 // of 256 columns and walks all rows; SPLIT = 4, the waves share one 64-column
 // tile, a quarter of the rows each, and their sums meet in LDS, added in FP64.
@@ -64,7 +72,7 @@ __global__ void __launch_bounds__(256) k_nl_reduce(const T* __restrict__ X, int6
   const int item = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tile = SPLIT == 4 ? blockIdx.y : blockIdx.y * kRowsPerWaveGroup + w;
+  const int tile = SPLIT == 4 ? tile_index() : tile_index() * kRowsPerWaveGroup + w;
   if (SPLIT == 1 && tile * 64 >= ncols) return;   // wave-uniform
   const int n = tile * 64 + lane;
   const bool valid = n < ncols;
@@ -165,7 +173,7 @@ __global__ void __launch_bounds__(256) k_nl_reduce_mfma(const float* __restrict_
   const int item = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nbase = (SPLIT == 4 ? blockIdx.y : blockIdx.y * kRowsPerWaveGroup + w) * 64;
+  const int nbase = (SPLIT == 4 ? tile_index() : tile_index() * kRowsPerWaveGroup + w) * 64;
   if (SPLIT == 1 && nbase >= ncols) return;   // wave-uniform
   const int a = d.item_atom[item];
   const int npj = d.nproj[a];
@@ -361,7 +369,7 @@ k_atom_first(const double* __restrict__ part, const double* __restrict__ nw, con
   __shared__ AtomTile L;
   const int a = blockIdx.x;
   const int j = threadIdx.x & 15, s0 = threadIdx.x >> 4;
-  const int n0 = blockIdx.y * 16 + j;
+  const int n0 = tile_index() * 16 + j;
   const bool valid = n0 < ncols;
   const int n = valid ? n0 : (ncols > 1 ? n0 & 1 : 0);   // in range, of the column's parity
   const int npj = d.nproj[a], po = d.poff[a];
@@ -426,7 +434,7 @@ k_atom_second(int natoms, int ncols, const double* __restrict__ c, const double*
   __shared__ AtomTile L;
   const int a = blockIdx.x;
   const int j = threadIdx.x & 15, s0 = threadIdx.x >> 4;
-  const int n0 = blockIdx.y * 16 + j;
+  const int n0 = tile_index() * 16 + j;
   const bool valid = n0 < ncols;
   if (lamX && a == 0 && s0 == 0 && valid)
     lamX[n0] = a_ * lamY[n0] * lam_in[n0] - ac * lamY[n0] - zz * lamX[n0];
@@ -994,7 +1002,7 @@ pawfe_status launch_nl_reduce(const pawfe_op* op, const T* X, int64_t ldx, int n
   // fewer than three waves per SIMD without the split: take it
   static_assert(kRowsPerWaveGroup == 4, "waves of a reduction workgroup");
   const bool split = (int64_t)op->nitems * (((by_op ? kResidualColsNl : ncols) + 63) / 64) < 3000;
-  const dim3 grid(op->nitems, split ? (ncols + 63) / 64 : (ncols + 255) / 256), block(256);
+  const dim3 grid = tile_grid(op->nitems, split ? (ncols + 63) / 64 : (ncols + 255) / 256), block(256);
   if constexpr (std::is_same<T, float>::value) {
     if (!op->cplx) {   // real operators in FP32: the matrix-core reduction
       auto go = [&](auto scale, auto b3) {
@@ -1045,7 +1053,7 @@ pawfe_status launch_atom_first(const pawfe_op* op, const double* part, const dou
                                const double* D2, const double* lam, const double* D1i, int ncols, double* c,
                                double* dv, double* v, hipStream_t s) {
   if (op->natoms == 0 || ncols <= 0) return PAWFE_OK;
-  hipLaunchKernelGGL(k_atom_first, dim3(op->natoms, (ncols + 15) / 16), dim3(256), 0, s, part, nw, D1, D2, lam, D1i,
+  hipLaunchKernelGGL(k_atom_first, tile_grid(op->natoms, (ncols + 15) / 16), dim3(256), 0, s, part, nw, D1, D2, lam, D1i,
                      ncols, c, dv, v, op->d);
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
@@ -1056,7 +1064,7 @@ pawfe_status launch_atom_second(const pawfe_op* op, const double* c, const doubl
                                 const double* lamY, const double* lam_in, double a, double ac, double zz, int ncols,
                                 hipStream_t s) {
   if (ncols <= 0 || (op->natoms == 0 && !lamX)) return PAWFE_OK;
-  hipLaunchKernelGGL(k_atom_second, dim3(std::max(op->natoms, 1), (ncols + 15) / 16), dim3(256), 0, s, op->natoms,
+  hipLaunchKernelGGL(k_atom_second, tile_grid(std::max(op->natoms, 1), (ncols + 15) / 16), dim3(256), 0, s, op->natoms,
                      ncols, c, dv, dprev, nwprev, op->d.dH, qv, v, nw, lamX, lamY, lam_in, a, ac, zz, op->d);
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
