@@ -1254,6 +1254,8 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
   // colour by colour without it (the same bits)
   auto use_wave = [&](int ncells) {
     if constexpr (is_wave_mode(MODE)) {
+      // the one-wave kernel addresses the FP64 rows with 32-bit strides
+      if (step && a.ldy64 * 8 >= (int64_t(1) << 32)) return false;
       if (a.by_op)
         return wave_pays<T, NP, MODE>((double)op->E / std::max(op->ncolour, 1), op->cplx ? kResidualColsC : kResidualCols);
       if (a.cellbuf || (a.gathers && cell_buf_bytes(op, a.ncols, sizeof(T)))) return false;
