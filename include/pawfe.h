@@ -283,7 +283,11 @@ pawfe_status pawfe_cheb_step_local(const pawfe_op* op, const void* RY, void* RX,
  * one.  Any whole number of block states (the query with nvec = block gives
  * one) is accepted by pawfe_cheb_filter: one runs the blocks one after
  * another, k > 1 keeps up to min(k, 4) blocks in flight (two was the
- * fastest on the paper's workload). */
+ * fastest on the paper's workload).  For small problems (up to 4500 cells x
+ * real columns of a block per cell colour) a block state includes room for the
+ * results of every cell, less than the rest of the state and at most 192 MiB;
+ * a workspace that leaves it out is accepted as well and gives the same
+ * bits with more launches (two states before the room, more only with it). */
 pawfe_status pawfe_cheb_filter_workspace(const pawfe_op* op, int64_t nvec, int32_t block,
                                          int32_t prec, size_t* bytes);
 
@@ -326,7 +330,9 @@ pawfe_status pawfe_cheb_filter_res(const pawfe_op* op, const void* Xin, int64_t 
                                    const double* lambda_in, int32_t degree, double b0, double bW,
                                    double bU, int32_t prec, void* ws, size_t ws_bytes, void* stream);
 
-/* Bytes of workspace pawfe_rayleigh_ritz needs. */
+/* Bytes of workspace pawfe_rayleigh_ritz uses (for small problems with room
+ * for the results of every cell as in a filter's block state; a workspace
+ * without it is accepted as well). */
 pawfe_status pawfe_rayleigh_ritz_workspace(const pawfe_op* op, int64_t nvec, size_t* bytes);
 
 /* Rayleigh-Ritz (Algorithm 1 steps 4-6), FP64 throughout:
@@ -455,8 +461,9 @@ typedef struct {
 } pawfe_filter_job;
 
 /* Builds the batch: validates every job (as pawfe_cheb_filter), allocates
- * one workspace per job (device memory owned by the batch), autotunes,
- * captures and instantiates the graph.  `stream` is used for the tuning
+ * one workspace per job (device memory owned by the batch: one block state
+ * of pawfe_cheb_filter_workspace, without the room for per-cell results where
+ * the device has none), autotunes, captures and instantiates the graph.  `stream` is used for the tuning
  * runs and is synchronized before return.  prec: PAWFE_FP64 or PAWFE_FP32
  * (the recurrence precision of every job).  The operators must outlive the
  * batch and must not be used by other calls while the batch runs. */

@@ -555,6 +555,10 @@ __global__ void k_part_reduce(const double* __restrict__ part, int nb, int nc, i
 
 }  // namespace
 
+size_t filter_ws_least(const pawfe_op* op, int64_t block, int32_t prec) {
+  return filter_ws_bytes(op, block * (op->cplx ? 2 : 1), prec);
+}
+
 // ---- upload / free ------------------------------------------------------------
 
 pawfe_status upload_veff(pawfe_op* op, hipStream_t s) {

@@ -281,7 +281,16 @@ pawfe_status build(pawfe_batch* b, const pawfe_filter_job* jobs, int32_t njobs, 
       CHECK(pawfe_cheb_filter_workspace(J.op, std::min<int64_t>(J.nvec, cand[i]), cand[i], b->prec, &wc[i]));
       wmax = std::max(wmax, wc[i]);
     }
-    if (hipMalloc(&b->ws[j], wmax) != hipSuccess) return fail(PAWFE_ENOMEM, "batch workspace allocation failed");
+    if (hipMalloc(&b->ws[j], wmax) != hipSuccess) {
+      // without the room for per-cell results (the same bits, more launches)
+      (void)hipGetLastError();
+      wmax = 0;
+      for (size_t i = 0; i < cand.size(); ++i) {
+        wc[i] = pawfe::filter_ws_least(J.op, std::min<int64_t>(J.nvec, cand[i]), b->prec);
+        wmax = std::max(wmax, wc[i]);
+      }
+      if (hipMalloc(&b->ws[j], wmax) != hipSuccess) return fail(PAWFE_ENOMEM, "batch workspace allocation failed");
+    }
     keys[j] = job_key(J, b->prec, arch);
     TuneEntry hit;
     bool cached = false;

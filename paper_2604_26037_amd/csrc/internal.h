@@ -180,6 +180,8 @@ pawfe_status build_host(const pawfe_op_desc* desc, pawfe_op* op);
 pawfe_status upload(pawfe_op* op, hipStream_t s);
 pawfe_status upload_veff(pawfe_op* op, hipStream_t s);
 void free_device(pawfe_op* op);
+// bytes of one block state of a filter without the room for per-cell results
+size_t filter_ws_least(const pawfe_op* op, int64_t block, int32_t prec);
 
 // Host-side reference-element helpers (builder.cpp)
 void gll_rule(int p, std::vector<double>& x, std::vector<double>& w);

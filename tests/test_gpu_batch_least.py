@@ -1,0 +1,40 @@
+"""The workspace that a batch falls back to when the device has no room for a
+job's per-cell results: exactly the least that the filter accepts, one block
+state (it never reads as two), and the same result as with room."""
+
+import ctypes as C
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("p,cplx,prec", [(4, False, "fp64"), (6, False, "fp32"), (3, True, "fp64")])
+def test_least_workspace(p, cplx, prec):
+    from paper_2604_26037_amd import FP32, FP64, Operator, PawfeError
+    from paper_2604_26037_amd.pawfe import LIB_PATH
+    from workloads.configs import custom_system
+    n, N = (3, 4, 3), 24
+    kw = dict(kpoint=(0.3, -0.2, 0.45), is_complex=True) if cplx else {}
+    pos = np.array([[1.0, 2.0, 3.0], [3.4, 0.2, 4.0]])
+    op = Operator(custom_system(n, tuple(1.7 * v for v in n), p, p + 2, pos=pos, rcut=1.1, channels="spd8", wells=pos,
+                                s_H=0.5, s_S=0.2, seed=3, **kw))
+    names = subprocess.run(["nm", "-D", "--defined-only", LIB_PATH], capture_output=True, text=True, check=True).stdout
+    name, = re.findall(r"\S*filter_ws_least\S*", names)
+    least = getattr(C.CDLL(LIB_PATH), name)
+    least.argtypes, least.restype = [C.c_void_p, C.c_int64, C.c_int32], C.c_size_t
+    low = least(op._h, N, FP64 if prec == "fp64" else FP32)
+    assert low < op.cheb_filter_workspace(N, N, prec) < 2 * low
+    X = torch.randn(op.ndof, N, device="cuda", dtype=torch.complex128 if cplx else torch.float64,
+                    generator=torch.Generator(device="cuda").manual_seed(1))
+    lam = torch.linspace(0.0, 1.0, N, device="cuda", dtype=torch.float64)
+    run = lambda b: op.cheb_filter(X, lam, 6, -1.0, 2.0, 400.0, block=N, prec=prec, ws=op.workspace(b))  # noqa: E731
+    assert torch.equal(run(low), run(op.cheb_filter_workspace(N, N, prec)))
+    with pytest.raises(PawfeError):
+        run(low - 256)
+    op.close()
