@@ -287,7 +287,8 @@ pawfe_status pawfe_cheb_step_local(const pawfe_op* op, const void* RY, void* RX,
  * real columns of a block per cell colour) a block state includes room for the
  * results of every cell, less than the rest of the state and at most 192 MiB;
  * a workspace that leaves it out is accepted as well and gives the same
- * bits with more launches (two states before the room, more only with it). */
+ * result up to rounding, with more launches (two states before the room,
+ * more only with it). */
 pawfe_status pawfe_cheb_filter_workspace(const pawfe_op* op, int64_t nvec, int32_t block,
                                          int32_t prec, size_t* bytes);
 
@@ -308,7 +309,7 @@ pawfe_status pawfe_cheb_filter_workspace(const pawfe_op* op, int64_t nvec, int32
  * created on first use and kept until the process ends), forked from and
  * joined back into `stream`, so that one block's projector and node kernels
  * overlap another block's cell kernel; the results are identical to the
- * one-stream order.  Filters of different operators issued on different
+ * one-stream order, bit for bit, in every workspace of whole block states.  Filters of different operators issued on different
  * streams at the same time run their blocks one after another on those
  * shared streams. */
 pawfe_status pawfe_cheb_filter(const pawfe_op* op, const void* Xin, int64_t ldx, void* Xout,

@@ -389,7 +389,7 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
     CHECK(launch_atom_second(op, nb.c, dk, first ? nullptr : dprev, first ? nullptr : nwp, nullptr, nb.t, nwn, lamX,
                              lamY, lam_in, a, a * c, zz, nc, s));
     CHECK(launch_node_fixup<TR>(op, nb.t, -1.0, nc, RY, ld, s));
-    CHECK(launch_cell_step<TR>(op, RY, RX, ld, Yr, ldyr, lamY, a, a * c, zz, nc, s, true, ns.cell));
+    CHECK(launch_cell_step<TR>(op, RY, RX, ld, Yr, ldyr, lamY, a, a * c, zz, nc, s, ns.cell));
     std::swap(RX, RY);
     std::swap(lamX, lamY);
     std::swap(dk, dprev);

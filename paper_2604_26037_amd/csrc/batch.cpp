@@ -282,7 +282,7 @@ pawfe_status build(pawfe_batch* b, const pawfe_filter_job* jobs, int32_t njobs, 
       wmax = std::max(wmax, wc[i]);
     }
     if (hipMalloc(&b->ws[j], wmax) != hipSuccess) {
-      // without the room for per-cell results (the same bits, more launches)
+      // without the room for per-cell results (more launches)
       (void)hipGetLastError();
       wmax = 0;
       for (size_t i = 0; i < cand.size(); ++i) {

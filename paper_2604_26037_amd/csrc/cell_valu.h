@@ -1149,7 +1149,7 @@ k_cell_valu(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
         return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(sK) + k_of_u(pk[j] & ((1u << kLdsBits) - 1)));
       };
       // the products and sums below are spelled out as k_cell_gather's, which
-      // repeats them on the stored results (the factor f with them)
+      // forms them from the stored results (the factor f with them)
       if (to_buf) {
         T* out = A.cellbuf + ((int64_t)cp.e * NL + slot) * A.ncols + n;
 #pragma unroll
@@ -1249,9 +1249,9 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     go(std::false_type{});
   };
   // the one-wave kernel for a launch of ncells cells: a residual takes one
-  // kernel in all launches, chosen for an average colour; a block that would
-  // gather its cells' results if it had room for them takes the workgroup kernel
-  // colour by colour without it (the same bits)
+  // kernel in all launches, chosen for an average colour; a block of an apply
+  // that would gather its cells' results if it had room for them takes the
+  // workgroup kernel colour by colour without it (the same bits)
   auto use_wave = [&](int ncells) {
     if constexpr (is_wave_mode(MODE)) {
       // the one-wave kernel addresses the FP64 rows with 32-bit strides

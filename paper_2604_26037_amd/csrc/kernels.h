@@ -39,8 +39,8 @@ struct CellArgs {
   // launches of all cells at once: each cell's result goes to its own rows
   // [E][nloc][ncols] here and k_cell_gather adds them up per DOF (null: one
   // launch per cell colour, results added into Y).  gathers: the caller gives
-  // that room to blocks that want it where it can; the result is the same
-  // either way
+  // that room to blocks that want it where it can (applies: the same bits
+  // either way)
   T* cellbuf;
   bool gathers;
   bool by_op;   // the route is chosen by the operator alone, not by ncols (residual)
@@ -118,7 +118,7 @@ bool cell_step_available(const pawfe_op* op);
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
                               const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
-                              bool gathers = false, void* cellbuf = nullptr);
+                              void* cellbuf = nullptr);
 
 // the same on general operators (kernels_cell_step_gen.hip; the arguments
 // already carry the per-cell tables)

@@ -166,13 +166,14 @@ constexpr int64_t kCellBufCols = 4500, kCellBufBytes = int64_t(192) << 20;
 
 // Y[I][n] = sum over the (up to eight) cells sharing DOF I of their results
 // times their factors (CellFactor F), added one after another in the order of
-// the cells' colours to 0 (KIND 0), to Y (KIND 1) or to the node part of the
-// filter's step (KIND 2: -a c X - zeta zeta' Y + a lamY_n Yres, the last product
-// and sum in FP64, rounded once): product by product what the launches per
-// colour do, so the two give the same bits and a block's result does not depend
-// on whether there was room for this.  CW lanes share a row (its cells are
-// found once per lane and serve all of its columns); all loads are issued
-// before the sum.
+// the cells' colours to 0 (KIND 0) or to Y (KIND 1): product by product what the
+// launches per colour do, so applies and residuals have the same bits with and
+// without room for this.  KIND 2, the filter's step: the cells' sum is added to
+// the node part -a c X - zeta zeta' Y + a lamY_n Yres (the last product and sum
+// in FP64, rounded once) at the end; one after another to the node part, as
+// the launches per colour have to, FP32 filters are up to a tenth less accurate.
+// CW lanes share a row (its cells are found once per lane and serve all of its
+// columns); all loads are issued before the sum.
 template <typename T, int KIND, int F, int P>
 __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, int M) {
   constexpr int NP = P + 1, NL = NP * NP * NP;
@@ -217,11 +218,11 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = on[k] ? A.cellbuf[off[k] + n] : T(0);
     T* y = A.Y + (int64_t)I * A.ldy + n;
-    T s = T(0);
+    T s = T(0), node = T(0);
     if constexpr (KIND == 1) s = *y;
     if constexpr (KIND == 2) {
       const T part = fma_t((T)(-A.sac), A.X[(int64_t)I * A.ldx + n], -((T)A.szz * *y));
-      s = (T)fma(A.y64[(int64_t)I * A.ldy64 + n], A.sa * A.lamY[n], (double)part);
+      node = (T)fma(A.y64[(int64_t)I * A.ldy64 + n], A.sa * A.lamY[n], (double)part);
     }
     const T w = F == kByMass && A.lam ? (T)(-A.lam[n]) : T(1);
 #pragma unroll
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(256) k_cell_gather(CellArgs<T> A, int cw_log, 
       const T fk = F == kByAlpha ? f[0] : (F == kByMass ? f[k] * w : f[k]);
       s = fma_t(fk, v[k], s);   // (a cell that is not there adds zero)
     }
-    *y = s;
+    *y = KIND == 2 ? node + s : s;
   }
 }
 

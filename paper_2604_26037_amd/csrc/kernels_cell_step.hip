@@ -19,7 +19,7 @@ namespace pawfe {
 template <typename T>
 pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld, const double* Y, int64_t ldy,
                               const double* lamY, double a, double ac, double zz, int ncols, hipStream_t s,
-                              bool gathers, void* cellbuf) {
+                              void* cellbuf) {
   if (ncols <= 0) return PAWFE_OK;
   if (!cell_step_available(op)) return fail(PAWFE_EUNSUPPORTED, "internal: no step variant for this operator");
   if (ld < ncols || ldy < ncols || ld * (int64_t)sizeof(T) >= (int64_t(1) << 32))
@@ -38,7 +38,6 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
   c.n2 = op->n[2];
   c.own = op->d.cell_own;
   c.cellbuf = (T*)cellbuf;
-  c.gathers = gathers;
   c.y64 = Y;
   c.ldy64 = ldy;
   c.lamY = lamY;
@@ -72,6 +71,6 @@ pawfe_status launch_cell_step(const pawfe_op* op, const T* RY, T* RX, int64_t ld
 
 template pawfe_status launch_cell_step<PAWFE_T>(const pawfe_op*, const PAWFE_T*, PAWFE_T*, int64_t, const double*,
                                                 int64_t, const double*, double, double, double, int, hipStream_t,
-                                                bool, void*);
+                                                void*);
 
 }  // namespace pawfe

@@ -1,6 +1,7 @@
 """The workspace that a batch falls back to when the device has no room for a
 job's per-cell results: exactly the least that the filter accepts, one block
-state (it never reads as two), and the same result as with room."""
+state (it never reads as two), and the same result up to the order of the
+sums."""
 
 import ctypes as C
 import re
@@ -34,7 +35,9 @@ def test_least_workspace(p, cplx, prec):
                     generator=torch.Generator(device="cuda").manual_seed(1))
     lam = torch.linspace(0.0, 1.0, N, device="cuda", dtype=torch.float64)
     run = lambda b: op.cheb_filter(X, lam, 6, -1.0, 2.0, 400.0, block=N, prec=prec, ws=op.workspace(b))  # noqa: E731
-    assert torch.equal(run(low), run(op.cheb_filter_workspace(N, N, prec)))
+    want = run(op.cheb_filter_workspace(N, N, prec))
+    tol = 1e-10 if prec == "fp64" else 1e-5
+    assert ((run(low) - want).abs().amax(0) / want.abs().amax(0)).max().item() <= tol
     with pytest.raises(PawfeError):
         run(low - 256)
     op.close()

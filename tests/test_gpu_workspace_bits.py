@@ -1,10 +1,11 @@
-"""The room for per-cell results (one launch of all cells and a gather) changes
-no bit: the gather adds a DOF's cells in the order of their colours, product by
-product what the launches per colour do.  A filter gives the same result in the
-smallest workspace (no room), with room and with more blocks in flight, and
-Rayleigh-Ritz and the applies (eager with room, static scratch) do too; uniform, graded
-with the GGA term and complex operators, odd meshes (three colours an axis), on
-both sides of the limit."""
+"""What does not depend on the workspace, bit for bit.  A filter in any number of
+whole block states (one after another or several in flight).  Rayleigh-Ritz, the
+residual and the applies also without the room for per-cell results (one launch
+of all cells and a gather, which adds a DOF's cells in the order of their
+colours, product by product what the launches per colour do).  The filter's
+steps sum the cells before the node part where there is room, so a workspace
+without it gives the same up to rounding.  Uniform, graded, GGA and complex
+operators, odd meshes (three colours an axis)."""
 
 import numpy as np
 import pytest
@@ -39,7 +40,7 @@ def _least(call, full):
 @pytest.mark.parametrize("p,kind,n", [(2, "uniform", (3, 4, 3)), (3, "graded", (2, 3, 5)), (4, "complex", (3, 4, 3)),
                                       (5, "gga", (3, 2, 4)), (6, "uniform", (3, 4, 3)), (6, "graded", (4, 2, 2)),
                                       (2, "complex", (3, 4, 3))])
-def test_room_changes_no_bit(p, kind, n):
+def test_workspaces(p, kind, n):
     from paper_2604_26037_amd import Operator
     op = Operator(_system(p, kind, n))
     cplx = kind == "complex"
@@ -49,20 +50,31 @@ def test_room_changes_no_bit(p, kind, n):
     X = torch.randn(op.ndof, N, device="cuda", dtype=torch.complex128 if cplx else torch.float64,
                     generator=torch.Generator(device="cuda").manual_seed(p))
     lam = torch.linspace(lo, lo + 0.3 * (hi - lo), N, device="cuda", dtype=torch.float64)
+    rr_full = op.rayleigh_ritz_workspace(N)
+    rr_low = _least(lambda b: op.rayleigh_ritz(X.clone(), ws=op.workspace(b)), rr_full)
     for prec in ("fp64", "fp32"):
         for block in (N, 9):
             run = lambda b: op.cheb_filter(X, lam, 6, b0, bW, bU, block=block, prec=prec, ws=op.workspace(b))  # noqa: E731
             one, full = op.cheb_filter_workspace(block, block, prec), op.cheb_filter_workspace(N, block, prec)
             low = _least(run, full)
-            want = run(low)
-            for b in (one, full, 2 * low, 4 * full):
+            want = run(full)
+            for b in (one, 4 * full):
                 assert torch.equal(run(b), want), (prec, block, b)
+            tol = 1e-10 if prec == "fp64" else 1e-5
+            for b in (low, 2 * low):
+                assert ((run(b) - want).abs().amax(0) / want.abs().amax(0)).max().item() <= tol, (prec, block, b)
+            # the residual inside: the same with R formed in a Rayleigh-Ritz without room
+            Xr, R = X.clone(), torch.empty_like(X)
+            lam_r, _ = op.rayleigh_ritz(Xr, R=R, ws=op.workspace(rr_low))
+            args = (lam_r, 2, b0, bW, bU)
+            for b in (low, full):
+                assert torch.equal(op.cheb_filter(Xr, *args, block=block, prec=prec, ws=op.workspace(b)),
+                                   op.cheb_filter(Xr, *args, block=block, prec=prec, ws=op.workspace(b), R=R))
         x = X if prec == "fp64" else X.to(torch.complex64 if cplx else torch.float32)
         # static scratch of 64 MB: its room is the same, without any where it is spent
         assert torch.equal(op.apply_H_noalloc(x, torch.empty_like(x), prec=prec), op.apply_H(x, prec=prec))
     run = lambda b: op.rayleigh_ritz(X.clone(), ws=op.workspace(b))[0]  # noqa: E731
-    full = op.rayleigh_ritz_workspace(N)
-    assert torch.equal(run(_least(run, full)), run(full))
+    assert torch.equal(run(rr_low), run(rr_full))
     op.close()
 
 
