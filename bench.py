@@ -11,7 +11,7 @@ norms.  Reported value: seconds per SCF filter pass (mixed precision,
 lower is better).  Also reported: the FP64 filter time per pass and the
 ratio, the HX throughput, the eigenvalue error of the mixed filter against
 the FP64 one after the FP64 Rayleigh-Ritz, the roofline of the dominant
-kernel (the cell-local operator on the vector ALUs) and the oracle timed on
+kernel (the filter's cell-local step) and the oracle timed on
 the host.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline]
@@ -703,26 +703,36 @@ def main():
 
     # roofline of the dominant kernel of the filter pass: its fused step
     # kernel on the vector ALUs (FP32), one colour (1/8 of the cells) x 256
-    # columns per launch; algorithmic flops = 72,668 per cell-column
-    # (sum-factorized K + V) plus 5 per DOF-column for the node part of the
-    # step (on average 1/8 of the DOFs per launch); the launch duration is the
-    # mean of the FP32 launches timed above with events on their stream
+    # columns per launch, bound by the memory system: HBM bytes per launch from
+    # the committed counters, else the algorithmic ones (R_Y' and R_X gathered,
+    # R_X written, V(q) W_q, the FP64 residual rows at the first visits);
+    # algorithmic flops = 72,668 per cell-column (sum-factorized K + V) plus 5
+    # per DOF-column for the node part of the step (on average 1/8 of the DOFs
+    # per launch); the launch duration is the mean of the FP32 launches timed
+    # above with events on their stream
     per_launch_flops = (nloc_flops + STEP_NODE_FLOPS * M) * B / op.ncolour
+    cells = op.ncells / op.ncolour
+    per_launch_bytes = cells * ((s.degree + 1) ** 3 * B * 3 * 4 + s.nq ** 3 * 4) + M / op.ncolour * B * 8
     t_launch = step_t["fp32"]
-    achieved = per_launch_flops / t_launch / 1e12
+    traffic = measured_traffic()
+    achieved = (traffic or per_launch_bytes) / t_launch / 1e9
+    tflops = per_launch_flops / t_launch / 1e12
     roof = {
         "kernel": "k_cell_wave<float,7,8,Step> (filter step: cell-local K + V on M_D^-1 R_Y, node part at the "
                   "first visit; one colour per launch)",
-        "bound": "alu",
+        "bound": "hbm",
         "achieved": achieved,
-        "peak": PEAK_VALU_F32_TFLOPS,
-        "unit": "TFLOP/s",
-        "frac": achieved / PEAK_VALU_F32_TFLOPS,
-        "traffic": measured_traffic(),
-        "per_launch_flops": per_launch_flops,
+        "peak": PEAK_HBM_GBS,
+        "unit": "GB/s",
+        "frac": achieved / PEAK_HBM_GBS,
+        "traffic": traffic,
+        "per_launch_bytes": per_launch_bytes,
         "avg_launch_ms": t_launch * 1e3,
-        "peak_without_packed_fp32": PEAK_VALU_F32_SCALAR_TFLOPS,
-        "frac_without_packed_fp32": achieved / PEAK_VALU_F32_SCALAR_TFLOPS,
+        "per_launch_flops": per_launch_flops,
+        "tflops": tflops,
+        "peak_tflops": PEAK_VALU_F32_TFLOPS,
+        "frac_tflops": tflops / PEAK_VALU_F32_TFLOPS,
+        "frac_tflops_without_packed_fp32": tflops / PEAK_VALU_F32_SCALAR_TFLOPS,
     }
 
     out = {

@@ -242,7 +242,7 @@ pawfe_status apply_entry(const pawfe_op* cop, int which, const void* X, int64_t 
 bool fused_step(const pawfe_op* op, int32_t prec) { return prec != PAWFE_BF16X3 && cell_step_available(op); }
 
 // What a block state must hold (filter_ws_bytes) and what it can use besides
-// (the per-cell results of a small problem, for its step and, in FP64, its
+// (the per-cell results of a small problem, for its steps and for its FP64
 // residual).  B: real columns of one block (two per complex column).
 size_t filter_ws_extra(const pawfe_op* op, int64_t B, int32_t prec);
 size_t filter_ws_bytes(const pawfe_op* op, int64_t B, int32_t prec) {

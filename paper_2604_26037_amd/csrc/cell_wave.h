@@ -14,15 +14,16 @@
 //   K:  planes fx My Kx + fy Ky Mx -> slab, lines Mz, added to M's lines
 //   complex operators, before M and K: the same two rounds with G1 for the
 //   imaginary k term, read back from the partner column's place in the slab
-// and the sum is added to Y (first visits of the step as in cell_valu.h).
+// and the sum is added to Y (first visits of the step as in cell_valu.h), or
+// stored by itself where a small residual gathers its cells' results.
 // The gathered rows are wave-uniform for x and y, so their addresses are
 // scalar; the lanes only carry the offset of their plane and column.
 //
 // Bound by the memory system and the vector ALU about equally (degree 6,
-// 1000 cells x 256 columns a launch): FP32 step 1.54e9 B of HBM traffic (1.03x
-// its algorithmic bytes) and 146,000 vector instructions per SIMD.  Per launch,
-// against the workgroup kernel: step FP32 0.538 -> 0.387 ms (4.0 TB/s), FP64
-// 0.988 -> 0.720; K + V FP32 0.436 -> 0.298, FP64 0.852 -> 0.586; mass FP32
+// 1000 cells x 256 columns a launch): FP32 step 1.53e9 B of HBM traffic (1.02x
+// its algorithmic bytes) and 144,000 vector instructions per SIMD.  Per launch,
+// against the workgroup kernel: step FP32 0.538 -> 0.390 ms (3.9 TB/s), FP64
+// 0.988 -> 0.722; K + V FP32 0.436 -> 0.298, FP64 0.852 -> 0.586; mass FP32
 // 0.411 -> 0.267, FP64 0.798 -> 0.504.
 //
 // Slab: element (line L, plane c, col) at (L NP + c) CB + col.  A plane
