@@ -1267,9 +1267,9 @@ pawfe_status run_cell_valu(const pawfe_op* op, const CellArgs<T>& a0, hipStream_
     CellArgs<T> ac = a;
     ac.cells = op->d.cell_pack;
     bool done = false;
-    if constexpr (is_wave_buf_mode(MODE)) {
+    if constexpr (is_wave_buf_mode<T>(MODE)) {
       if (use_wave(op->E)) {
-        launch_wave<T, NP, NQ, MODE>(ac, op->E, fx, fy, fz, s);
+        launch_wave<T, NP, NQ, MODE, true>(ac, op->E, fx, fy, fz, s);
         if (!mass) ac.alpha = T(1);   // (the one-wave kernel's results hold it)
         done = true;
       }

@@ -39,10 +39,11 @@ namespace pawfe {
 
 namespace {
 
-// Modes whose one-wave variant can store each cell's result by itself
-// (CellArgs::cellbuf): those of the residual.
+// Modes with a one-wave variant that stores each cell's result by itself
+// (CellArgs::cellbuf): those of the residual, which is FP64.
+template <typename T>
 constexpr bool is_wave_buf_mode(int mode) {
-  return mode == kValuHRes || mode == kValuHResC || mode == kValuGenH || mode == kValuGenMass;
+  return sizeof(T) == 8 && (mode == kValuHRes || mode == kValuHResC || mode == kValuGenH || mode == kValuGenMass);
 }
 
 template <typename T, int NP, int NQ>
@@ -102,7 +103,9 @@ __device__ __forceinline__ void swap_halves(T& lo, T& hi) {
 
 }  // namespace
 
-template <typename T, int NP, int NQ, int MODE>
+// BUF: each cell's result is stored in A.cellbuf (a variant of its own: as a
+// test at run time it made the complex residual spill)
+template <typename T, int NP, int NQ, int MODE, bool BUF>
 __global__ void __launch_bounds__(64 * kWaveTiles<MODE>) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   using W = Wave<T, NP, NQ>;
@@ -113,7 +116,6 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   constexpr bool STEP = MODE == kValuStep || MODE == kValuGenStep || MODE == kValuStepC;
   constexpr bool CPLX = MODE == kValuHC || MODE == kValuHResC || MODE == kValuStepC;
   constexpr bool SC = STEP;
-  constexpr bool BUF = is_wave_buf_mode(MODE);
   constexpr int NQ2 = NQ * NQ, NP2 = NP * NP, NQ3 = NQ * NQ * NQ;
   constexpr int WT = kWaveTiles<MODE>;
   static_assert(MASS || WT == 1, "V(q) W_q is staged by one wave");
@@ -312,15 +314,18 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     const T mac = (T)(-A.sac);
     const unsigned cr = cm >> row_class(r);
     const T m0 = cr & 1u ? mac : T(0), m1 = cr & 2u ? mac : T(0), m2 = cr & 4u ? mac : T(0);
-    sfor<NP>([&](auto a) { acc[r][a] = fma_t(a == 0 ? m0 : (a == NP - 1 ? m2 : m1), x[r][a], acc[r][a]); });
+    sfor<NP>([&](auto a) {
+      acc[r][a] = fma_t(a == 0 ? m0 : (a == NP - 1 ? m2 : m1), x[r][a], acc[r][a]);
+      if constexpr (!kLateX) opaque(acc[r][a]);
+    });
   };
   if constexpr (STEP) {
     sfor<RB>([&](auto r) {
       // opaque: products of x are formed here or at the end, not kept beside
       // it from the load on, and the sums not left until the end
       sfor<NP>([&](auto a) { opaque(x[r][a]); });
-      if constexpr (!kLateX) add_x(r);
-      sfor<NP>([&](auto a) { opaque(acc[r][a]); });
+      if constexpr (kLateX) sfor<NP>([&](auto a) { opaque(acc[r][a]); });
+      else add_x(r);
     });
   }
   constexpr int ZK = (NP2 + G - 1) / G;
@@ -387,7 +392,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     wave_lds_order();
     // s_n = -1 on real, +1 on imaginary columns, of the partner column's term
     const T sg = (col & 1) ? T(1) : T(-1);
-    const T* const pp = sl + W::plane_at(lane ^ 1);
+    const T* const pp = pb + ((col & 1) ? -1 : 1);
     sfor<RB>([&](auto r) {
       const int b = lrow(r);
       sfor<NP>([&](auto a) {
@@ -467,7 +472,6 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
   // old rows (except at a first visit that overwrites them) and, of the step,
   // the first FP64 residual rows: requested here, used after the last z pass
   opaque(cm);
-  const bool to_buf = BUF && A.cellbuf != nullptr;   // the cell's own result only
   T yo[RB][NP];
   xoffs(ldyb, xo);
   const char* yp = planeptr((const T*)A.Y, ldyb);
@@ -477,7 +481,7 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
     if constexpr (STEP) {
       sfor<NP>(get);
     } else {
-      const unsigned cr = to_buf ? ~0u : cm >> row_class(r);
+      const unsigned cr = BUF ? ~0u : cm >> row_class(r);   // (BUF: nothing is added to)
       sfor<NP>([&](auto a) { yo[r][a] = T(0); });
       if (!(cr & 1u)) get(std::integral_constant<int, 0>{});
       if (!(cr & 2u)) sfor<NP - 2>([&](auto a) { get(std::integral_constant<int, a + 1>{}); });
@@ -533,10 +537,10 @@ k_cell_wave(CellArgs<T> A, int ncoltiles, int nitems, T fx, T fy, T fz) {
       if constexpr (r + kAhead < RB) load_y(std::integral_constant<int, (r + kAhead < RB ? r + kAhead : 0)>{});
       first_visits(r, [&](auto a) { yo[r][a] = (T)((double)(-zz * yo[r][a]) + yr[r][a] * ly); });
     }
-    if (to_buf) sfor<NP>([&](auto a) { yo[r][a] = acc[r][a]; });
+    if constexpr (BUF) sfor<NP>([&](auto a) { yo[r][a] = acc[r][a]; });
     else sfor<NP>([&](auto a) { yo[r][a] = MASS ? fma_t(f, acc[r][a], yo[r][a]) : yo[r][a] + acc[r][a]; });
   });
-  if (to_buf) {
+  if constexpr (BUF) {
     if (pl && valid) {
       T* out = A.cellbuf + (int64_t)e * (NP * NP * NP) * A.ncols + n;
       sfor<RB>([&](auto r) {
@@ -602,7 +606,7 @@ bool wave_pays(double ncells, int ncols) {
   return ncells * ncols >= (f32 ? (NP == 3 ? 0 : 7000) : (NP == 3 ? 3000 : NP == 4 || kCplx ? 4000 : 8000));
 }
 
-template <typename T, int NP, int NQ, int MODE>
+template <typename T, int NP, int NQ, int MODE, bool BUF = false>
 void launch_wave(const CellArgs<T>& a, int ncells, T fx, T fy, T fz, hipStream_t s) {
   constexpr int CB = Wave<T, NP, NQ>::CB;
   constexpr int WT = kWaveTiles<MODE>;
@@ -612,7 +616,7 @@ void launch_wave(const CellArgs<T>& a, int ncells, T fx, T fy, T fz, hipStream_t
   // the items was slower (degree-6 K + V of 1000 cells x 256 columns, FP32:
   // 0.39 against 0.30 ms)
   const int nitems = ncells * ncoltiles;
-  hipLaunchKernelGGL((k_cell_wave<T, NP, NQ, MODE>), dim3((unsigned)((nitems + 7) / 8) * 8), dim3(64 * WT), 0, s, a,
+  hipLaunchKernelGGL((k_cell_wave<T, NP, NQ, MODE, BUF>), dim3((unsigned)((nitems + 7) / 8) * 8), dim3(64 * WT), 0, s, a,
                      ncoltiles, nitems, fx, fy, fz);
 }
 

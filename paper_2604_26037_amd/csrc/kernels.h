@@ -138,10 +138,13 @@ pawfe_status launch_dup_pairs(const double* in, double* out, int n, hipStream_t 
 // filter), so its kernels are chosen for blocks of one width, whatever the
 // block's: the cell kernel of real operators for 256 columns, where the one-wave
 // kernel costs a narrow block 1.1 times the workgroup kernel; that of complex
-// operators, where it costs up to 1.5 times, and the projector reduction, whose
-// walk without the split costs a narrow block 2.5 times (and the split a wide
-// one 1.4), for 64.
-constexpr int kResidualCols = 256, kResidualColsC = 64, kResidualColsNl = 64;
+// operators, where it costs up to 1.5 times, for 128; the projector reduction,
+// whose walk without the split costs a narrow block 2.5 times (and the split a
+// wide one 1.4), for 64.  FP64 filters of degree 2 on degree-6 operators, against
+// the choice by each block's width: 512 cells real 24 to 64 columns 0.91-0.94,
+// complex 24 to 128 columns 0.93-1.00; the worst, 420 cells of an odd mesh,
+// complex, 128 columns, 1.06.
+constexpr int kResidualCols = 256, kResidualColsC = 128, kResidualColsNl = 64;
 
 // ---- non-local / node-wise kernels (kernels_nl.hip) ----
 
