@@ -98,5 +98,5 @@ def test_room_is_taken_only_by_calls_that_use_it():
     assert taken(lambda: op.apply_H(F[:, :450], out=G[:, :450], prec="bf16x3")) < room // 4
     assert taken(lambda: op.apply_H(X, out=Y)) < room // 4
     assert taken(lambda: op.apply_H(X[:, :450], out=Y[:, :450])) >= room
-    assert taken(lambda: op.apply_S(X[:, :450], out=Y[:, :450])) == 0
+    assert taken(lambda: op.apply_S(X[:, :450], out=Y[:, :450])) < room // 4
     op.close()
