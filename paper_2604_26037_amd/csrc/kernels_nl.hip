@@ -675,17 +675,27 @@ __global__ void __launch_bounds__(256) k_node_finalize(int64_t M, int ncols, int
 // one launch per atom colour (atoms of a colour share no row) waited out the
 // latency chain of its items six to eight times (128 atoms x 256 columns FP32
 // 471 -> 354 us, FP64 670 us both ways, 3.6 TB/s; 18 atoms x 200 columns FP32
-// 106 -> 55; 12 atoms x 101 columns 67 -> 17).  Held to as many waves as the
-// lean per-atom walk alone would have.
+// 106 -> 55; 12 atoms x 101 columns 67 -> 17).
 constexpr int kFixUnroll = 8;
 static_assert(kFixUnroll == kFixShared, "rows in flight of a shared item");
+
+// Waves per SIMD that the kernel is held to: with the items of shared rows it
+// would take more registers than the walk over one atom's rows needs.  128 atoms
+// of 18 projectors x 256 columns, us a launch, left alone -> held: FP64 678 (at
+// six) -> 652 at five, complex 1307 -> 1127 at four; FP32 complex 584 -> 575 at
+// seven, into FP64 rows 804 -> 739 at six.
+constexpr int fix_waves(size_t tr, size_t to, int npj, bool has2, bool cplx) {
+  if (npj > 18 || has2) return 1;
+  if (tr == 8) return cplx && npj > 8 ? 4 : 5;
+  return cplx && npj > 8 && to == 8 ? 6 : 7;
+}
 
 // CPLX (complex operators): (re, im) column pairs, C v mixes them:
 // + s Ci v[n ^ 1], s = -1 on real and +1 on imaginary columns (partner value
 // from the neighbouring lane).
 template <typename TR, typename TO1, int NPJ, bool MINV, bool HAS2, bool CPLX>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu((NPJ <= 18 && !HAS2 && !CPLX) ? (sizeof(TR) == 4 ? 7 : 6) : 1)))
+    __attribute__((amdgpu_waves_per_eu((fix_waves(sizeof(TR), sizeof(TO1), NPJ, HAS2, CPLX)))))
 k_nl_fixup(int nshared, int ncols, const double* __restrict__ v1, double s1,
                                                   TO1* __restrict__ out1, int64_t ld1,
                                                   const double* __restrict__ v2, TR* __restrict__ out2,
@@ -1108,7 +1118,8 @@ pawfe_status nl_fixup(const pawfe_op* op, int ncols, const double* v1, double s1
     else if (op->npj_max <= 18) go(std::integral_constant<int, 18>{}, cplx);
     else go(std::integral_constant<int, 32>{}, cplx);
   };
-  if (op->cplx) by_npj(std::true_type{}); else by_npj(std::false_type{});
+  if (op->cplx) by_npj(std::true_type{});
+  else if constexpr (!HAS2) by_npj(std::false_type{});
   PAWFE_HIP(hipGetLastError());
   return PAWFE_OK;
 }
@@ -1180,8 +1191,14 @@ pawfe_status launch_node_cheb(const pawfe_op* op, const TR* RY, TR* RX, TR* Tb, 
                        RX, Tb, ld, Y, ldy, lamY, lamX, lam_in, a, ac, zz, Minv);
   }
   PAWFE_HIP(hipGetLastError());
-  // T -= M_D^{-1} C d ; R_X += C q  (q already scaled by a)
-  return nl_fixup<TR, TR, true, true>(op, ncols, dv, -1.0, Tb, ld, qv, RX, ld, s);
+  // T -= M_D^{-1} C d ; R_X += C q  (q already scaled by a).  Real operators: one
+  // launch each, which leaves the registers for twice the waves (128 atoms x 256
+  // columns FP32 797 -> 2 x 361 us, 64 atoms of 8 projectors 119 -> 2 x 55);
+  // complex ones read the coefficients of both together (1058 us, else 2 x 575)
+  if (op->cplx) return nl_fixup<TR, TR, true, true>(op, ncols, dv, -1.0, Tb, ld, qv, RX, ld, s);
+  const pawfe_status st = nl_fixup<TR, TR, true, false>(op, ncols, dv, -1.0, Tb, ld, nullptr, (TR*)nullptr, 0, s);
+  if (st != PAWFE_OK) return st;
+  return nl_fixup<TR, TR, false, false>(op, ncols, qv, 1.0, RX, ld, nullptr, (TR*)nullptr, 0, s);
 }
 template pawfe_status launch_node_cheb<double>(const pawfe_op*, const double*, double*, double*, int64_t,
                                                const double*, int64_t, const double*, const double*, const double*,
