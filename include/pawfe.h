@@ -285,7 +285,8 @@ pawfe_status pawfe_cheb_step_local(const pawfe_op* op, const void* RY, void* RX,
  * another, k > 1 keeps up to min(k, 4) blocks in flight (two was the
  * fastest on the paper's workload).  For small problems (up to 4500 cells x
  * real columns of a block per cell colour) a block state includes room for the
- * results of every cell, less than the rest of the state and at most 192 MiB;
+ * results of every cell (at degrees 5 and 6 filters of several blocks use it up to
+ * smaller sizes), less than the rest of the state and at most 192 MiB;
  * a workspace that leaves it out is accepted as well and gives the same
  * result up to rounding, with more launches (two states before the room,
  * more only with it). */

@@ -343,7 +343,7 @@ pawfe_status filter_block(const pawfe_op* op, const double* X, int64_t ldx, cons
 template <typename TR>
 pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx, const double* Rin, int64_t ldr,
                                 double* Xo, int64_t ldo, int nc, int64_t B, const double* lam_in, int m, double b0,
-                                double bW, double bU, Carve cv, hipStream_t s) {
+                                double bW, double bU, Carve cv, hipStream_t s, bool several) {
   double* Y = cv.take<double>((size_t)op->M * B);
   TR* RX = cv.take<TR>((size_t)op->M * B);
   TR* RY = cv.take<TR>((size_t)op->M * B);
@@ -359,7 +359,7 @@ pawfe_status filter_block_fused(const pawfe_op* op, const double* X, int64_t ldx
   NlBufs ns = nb;
   Carve cw = cv;
   carve_cell(op, cv, B, 8, nb);
-  carve_cell(op, cw, B, sizeof(TR), ns);
+  if (!several || cell_buf_pays_beside(op, B, sizeof(TR))) carve_cell(op, cw, B, sizeof(TR), ns);
   const int64_t ld = nc;
   // step 1: polynomial scalars
   const double e = (bU - bW) / 2.0, c = (bU + bW) / 2.0;
@@ -1136,9 +1136,9 @@ static pawfe_status cheb_filter_impl(const pawfe_op* op, const void* Xin, int64_
     } else if (fused_step(op, prec)) {
       st = prec == PAWFE_FP64
                ? filter_block_fused<double>(op, X, ldx * cf, Rb, ldr * cf, Xo, ldo * cf, (int)(nc * cf), B * cf, lam,
-                                            degree, b0, bW, bU, cv, sb)
+                                            degree, b0, bW, bU, cv, sb, nblocks > 1)
                : filter_block_fused<float>(op, X, ldx * cf, Rb, ldr * cf, Xo, ldo * cf, (int)(nc * cf), B * cf, lam,
-                                           degree, b0, bW, bU, cv, sb);
+                                           degree, b0, bW, bU, cv, sb, nblocks > 1);
     } else if (prec == PAWFE_FP64) {
       st = filter_block<double>(op, X, ldx * cf, Rb, ldr * cf, Xo, ldo * cf, (int)(nc * cf), B * cf, lam, degree, b0,
                                 bW, bU, cv, sb);

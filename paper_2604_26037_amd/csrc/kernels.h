@@ -80,6 +80,9 @@ pawfe_status launch_cell(const pawfe_op* op, int mode, const T* X, int64_t ldx, 
 size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem);
 // no result of it is larger
 size_t cell_buf_limit();
+// Whether the steps of a filter of several blocks gather (by the block's width,
+// not by how many blocks the workspace lets run at once: the same bits in each).
+bool cell_buf_pays_beside(const pawfe_op* op, int64_t ncols, size_t elem);
 
 // Y of a launch with a.cellbuf: the sum of the cells' results per DOF, plus Y
 // (a.own null), alone (a.own set), or plus the node part of the filter's step;

@@ -242,6 +242,24 @@ size_t cell_buf_bytes(const pawfe_op* op, int64_t ncols, size_t elem) {
 
 size_t cell_buf_limit() { return (size_t)kCellBufBytes; }
 
+// With another block's launches beside them the launches per colour wait for less,
+// so the gather stops paying earlier.  Time of a filter of two blocks of degree
+// 10 with the gather over that without (512 and 840 cells in 8 colours), by cell
+// columns per colour:
+//   degree 6, FP64 graded or GGA  0.98 at 1,500, 1.20 at 2,400; one size 1.01 at
+//   2,400, 1.05 at 2,800; FP32 0.96 to 1.02 at 3,000, 1.20 at 4,000; complex FP32
+//   0.94 at 3,400, 1.08 at 4,000, FP64 0.98 at 4,490
+//   degree 5, FP64 graded 1.04 at 2,800, 1.18 at 3,600; the others 0.99 to 1.06 at
+//   3,600, complex FP64 0.88 there and 1.21 at 4,490
+//   degree 4 at most 0.98 at 4,490
+bool cell_buf_pays_beside(const pawfe_op* op, int64_t ncols, size_t elem) {
+  const bool f64 = elem == 8;
+  int64_t cols = kCellBufCols;
+  if (op->p == 6) cols = !f64 || op->cplx ? 3000 : (op->general ? 1800 : 2400);
+  else if (op->p == 5) cols = f64 && op->general ? 2600 : 3400;
+  return (int64_t)op->E * ncols <= cols * op->ncolour;
+}
+
 template <typename T>
 pawfe_status launch_cell_gather(const pawfe_op* op, const CellArgs<T>& a, bool step, CellFactor fk, hipStream_t s) {
   if (!step && fk != kByMass && !a.own) return fail(PAWFE_EUNSUPPORTED, "internal: no gather that adds to Y");

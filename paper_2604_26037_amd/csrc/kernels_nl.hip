@@ -674,7 +674,7 @@ __global__ void __launch_bounds__(256) k_node_finalize(int64_t M, int ncols, int
 // all loads issued first.  Bound by the read-modify-write of scattered rows;
 // one launch per atom colour (atoms of a colour share no row) waited out the
 // latency chain of its items six to eight times (128 atoms x 256 columns FP32
-// 471 -> 354 us, FP64 670 us both ways, 3.6 TB/s; 18 atoms x 200 columns FP32
+// 471 -> 354 us, FP64 663 -> 652, 3.7 TB/s; 18 atoms x 200 columns FP32
 // 106 -> 55; 12 atoms x 101 columns 67 -> 17).
 constexpr int kFixUnroll = 8;
 static_assert(kFixUnroll == kFixShared, "rows in flight of a shared item");
