@@ -252,11 +252,17 @@ size_t cell_buf_limit() { return (size_t)kCellBufBytes; }
 //   degree 5, FP64 graded 1.04 at 2,800, 1.18 at 3,600; the others 0.99 to 1.06 at
 //   3,600, complex FP64 0.88 there and 1.21 at 4,490
 //   degree 4 at most 0.98 at 4,490
+// Meshes odd along two axes or three (18 or 27 colours) add small colours, launches
+// that the gather saves besides: 504 cells in 18 colours degree 6 FP32 0.93 at
+// 4,490, FP64 graded 0.94 at 3,000 and 1.02 at 4,000; 891 cells in 27 colours GGA
+// FP32 9.2 -> 7.9 ms at 3,300.  Odd along one axis is not enough (924 cells in 12
+// colours GGA FP32 9.4 -> 11.2 ms at 3,700).
 bool cell_buf_pays_beside(const pawfe_op* op, int64_t ncols, size_t elem) {
   const bool f64 = elem == 8;
   int64_t cols = kCellBufCols;
   if (op->p == 6) cols = !f64 || op->cplx ? 3000 : (op->general ? 1800 : 2400);
   else if (op->p == 5) cols = f64 && op->general ? 2600 : 3400;
+  if (op->ncolour >= 18) cols = std::min(cols * 3 / 2, kCellBufCols);
   return (int64_t)op->E * ncols <= cols * op->ncolour;
 }
 
